@@ -215,8 +215,8 @@ int32_t pasta_attn_append_kv(pasta_attn *h, const pasta_append_args *a);
  * Output row i belongs to stream i of the call.                              */
 enum {
   PASTA_DECODE_PLAN_ONLY = 1u, /* validate + plan + fill HOST debug outputs, enqueue nothing */
-  PASTA_DECODE_NO_MFMA = 2u,   /* route the shared prefix through the private-segment
-                                  kernel too (the path F32 always takes) */
+  PASTA_DECODE_NO_MFMA = 2u,   /* no matrix instructions: everything, the shared prefix too, through
+                                  the vector-ALU walker */
   PASTA_DECODE_ROPE_Q = 4u,    /* rotate query row i by position[i] before use (q itself is
                                   not modified; needs position != NULL, rope_theta > 0) */
   /* Two comparison modes, same results, more bytes -- what the segment lists and the shared
@@ -311,7 +311,7 @@ typedef struct {
                                    visible head beyond the common prefix and the range list into pieces separately). */
   void *prof_event_start;       /* hipEvent_t or NULL (both or neither): they receive the start and the */
   void *prof_event_stop;        /* end of the attention-partials kernel's execution (attached to its
-                                   dispatch; with PASTA_DECODE_NO_MFMA or F32: recorded on the stream
+                                   dispatch; with PASTA_DECODE_NO_MFMA: recorded on the stream
                                    before and after that launch) */
 } pasta_decode_args;
 

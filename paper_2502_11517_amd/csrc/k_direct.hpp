@@ -1,0 +1,499 @@
+// The partials launch for element types and head widths other than bf16 x 128 (fp32 pools of either
+// width, bf16 with 64-wide heads): the same work items, split and partial rows as k_attn, other kernel.
+//
+// Operands go STRAIGHT from memory into the registers in which the matrix instructions want them; no K
+// or V ever passes through LDS.  A wave owns whole blocks of tokens and works in 16-row tiles (a private
+// item has at most 8 live rows, so 32-row tiles would double its matrix work -- and fp32 matrix
+// instructions are slow enough for that to show):
+//   * S^T[16 tok x 16 rows] = K Q^T.  A operand: lane (i = lane % 16, q = lane / 16) holds pieces
+//     4 kk + q (16 bytes each) of token i's row, so one load instruction fetches 64 contiguous bytes of
+//     16 rows, and the same lanes of Q's rows are the B operand;
+//   * the accumulator then holds, per lane (row i, quarter q), tokens 4 q + r of each 16-token tile, which
+//     is the B operand of the next product for that token order;
+//   * O^T += V^T P^T.  The lanes of quarter q load exactly those tokens' V rows, whole rows per 16 lanes.
+//     fp32: a loaded element IS an A operand (one per token and M-tile).  bf16: the eight tokens of a lane
+//     are interleaved in registers, one byte-permute per operand register.  Element c of a lane's piece
+//     belongs to M-tile c, so M-tile c is the head dims { (D / 16) m + c } -- a free renaming, undone when
+//     the rows leave through LDS.
+// The rows' addresses are worked out once per item (one thread per token) and left in LDS as 32-bit codes,
+// whatever the list looks like -- contiguous, strided, listed, paged, rows of a deferred append.
+//
+// What bounds it: like k_attn, the latency of a step's one pass over its rows.  It replaces the vector-ALU
+// walker (k_private), whose cost was a chain of lane shuffles per row, which read a shared prefix once per
+// stream and could not take a deferred append along.  Append and decode step, walker -> this kernel (us):
+//   fp32, 4 query heads on 1 x 64, 256 + 2 x 16 tokens           28.7 ->  9.1
+//   fp32, 32 heads on 8 x 128, 1024 tokens + 4 x 32 .. 256       46.0 -> 12.8
+//   bf16, 32 heads on 8 x 64, 4096 tokens + 8 x 64 .. 512        27.9 -> 11.0
+// One block per wave in registers: a second one spilled (fp32 rows with 32 stacked queries need 256 registers
+// without it), and chunks are short enough here that most waves have only one.
+#pragma once
+#include "k_rope.hpp"
+#include "mfma_util.hpp"
+
+namespace pasta {
+
+constexpr int kDirWin = 1024;    // tokens whose address codes are in LDS at a time
+constexpr uint32_t kPendBit = 0x80000000u;  // address code: (byte offset / 16) | kPendBit for a deferred row
+
+// One lane's share of a block of kTok tokens.
+template <typename T, int D> struct DirBlock;
+template <int D> struct DirBlock<uint16_t, D> {
+  static constexpr int kTok = 32, kNT = 2, kNP = D / 32, kNV = 8, kVP = 1;  // kNP pieces of a K row per lane
+  typedef std::conditional_t<D == 128, u32x4, u32x2> vec;
+  u32x4 k[kNT][kNP];
+  vec v[kNV][kVP];
+};
+template <int D> struct DirBlock<float, D> {
+  static constexpr int kTok = D == 64 ? 32 : 16, kNT = kTok / 16, kNP = D / 16, kNV = kTok / 4, kVP = D / 64;
+  typedef f32x4 vec;
+  u32x4 k[kNT][kNP];
+  vec v[kNV][kVP];
+};
+
+// LDS of a work-group of NW waves, row tiles up to RT: address codes and ranges on the way in, the waves'
+// O on the way out ([wave][group of 64 lanes x 16 bytes], groups one piece apart from a multiple of the
+// bank period, so that a row can be read back across groups without conflicts).
+template <int D, int RT, int NW> struct DirLds {
+  static constexpr int kGroups = RT * 4 * (D / 64);
+  f32x4 o[NW][kGroups * 65];
+  float mw[NW][16 * RT], lw[NW][16 * RT];
+  uint32_t off[kDirWin];
+  DevRange ranges[kGatherMax];
+  int sel[2];
+};
+
+// Turns the planes of a row whose pieces 4 kk + q are spread over the quarters' lanes: piece kk and piece
+// kk + NP / 2 of a lane are each other's partners.  The same arithmetic as rope_row_piece.
+template <typename T, int NP>
+__device__ __forceinline__ void rope_lane(u32x4 (&x)[NP], int q, int pos, const double* tab) {
+#pragma unroll
+  for (int kk = 0; kk < NP / 2; ++kk) {
+    const uint32_t a[4] = {x[kk][0], x[kk][1], x[kk][2], x[kk][3]};
+    const uint32_t b[4] = {x[kk + NP / 2][0], x[kk + NP / 2][1], x[kk + NP / 2][2], x[kk + NP / 2][3]};
+    uint32_t lo[4], hi[4];
+    if constexpr (sizeof(T) == 4) {
+      const int f0 = (4 * kk + q) * 4;
+      rope_piece_f32(a, b, lo, false, f0, pos, tab);
+      rope_piece_f32(b, a, hi, true, f0, pos, tab);
+    } else {
+      const int f0 = (4 * kk + q) * 8;
+      rope_piece_bf16<true>(a, b, lo, false, f0, pos, tab);
+      rope_piece_bf16<true>(b, a, hi, true, f0, pos, tab);
+    }
+    x[kk] = u32x4{lo[0], lo[1], lo[2], lo[3]};
+    x[kk + NP / 2] = u32x4{hi[0], hi[1], hi[2], hi[3]};
+  }
+}
+
+// What an item's rows are made of.
+struct DirItem {
+  int n_tok, R, g;
+  long long part_row0;
+  const int32_t* req_streams;  // shared-prefix item: the request's streams (null: stack block s is stream s)
+  int row0;                    // ... its first stacked row
+  int q_stream;                // private item: its stream
+};
+
+// One item, once code_of(j) -- the address code of token j -- can be asked for.  GATHER: the rows are the G
+// heads of one stream; otherwise rows row0 .. of the request's stack.
+template <typename T, int D, int RT, int NW, bool GATHER, bool ROPE, class Lds, class CodeOf>
+__device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, const int32_t* meta, const DirItem& it, CodeOf code_of) {
+  typedef DirBlock<T, D> Blk;
+  constexpr int kTok = Blk::kTok, kNT = Blk::kNT, kNP = Blk::kNP, kMT = D / 16;
+  constexpr int kPieceRow = D * (int)sizeof(T) / 16;
+  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = p.Hq / p.Hkv;
+  const int n_tok = it.n_tok, R = it.R, g = it.g;
+
+  // ---- Q: the B operands, straight into registers (rows past R repeat row 0: computed, never stored)
+  u32x4 qf[RT][kNP];
+  int qpos[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int rr = rt * 16 + i < R ? rt * 16 + i : 0;
+    int s = it.q_stream, hq = rr;
+    if constexpr (!GATHER) {
+      const int ra = it.row0 + rr;
+      s = it.req_streams ? it.req_streams[ra / G] : ra / G;
+      hq = ra % G;
+    }
+    const char* src = reinterpret_cast<const char*>(p.q) + (long long)(s * p.Hq + g * G + hq) * (D * sizeof(T)) + q * 16;
+#pragma unroll
+    for (int kk = 0; kk < kNP; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4*>(src + kk * 64);
+    qpos[rt] = 0;
+    if constexpr (ROPE) {
+      if (p.rope_q) qpos[rt] = reinterpret_cast<const DevStream*>(meta + p.off_streams)[s].pos;
+    }
+  }
+
+  const char* kb = reinterpret_cast<const char*>(p.k);
+  const char* vb = reinterpret_cast<const char*>(p.v);
+  const char* kpend = reinterpret_cast<const char*>(p.k_pend);
+  const char* vpend = reinterpret_cast<const char*>(p.v_pend);
+  auto at = [&](uint32_t code, const char* pool, const char* pend) -> const char* {
+    return ((int)code < 0 ? pend : pool) + ((unsigned long long)(code & ~kPendBit) << 4);
+  };
+  auto load_k = [&](Blk& x, int b) {
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      const char* src = at(lds.off[b * kTok + 16 * t + i], kb, kpend) + q * 16;
+#pragma unroll
+      for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = *reinterpret_cast<const u32x4*>(src + kk * 64);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // (addresses of later loads are not worked out ahead: they would cost the registers the rows need)
+  };
+  auto load_v = [&](Blk& x, int b) {
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      const u32x4 c = *reinterpret_cast<const u32x4*>(&lds.off[b * kTok + 16 * t + 4 * q]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const char* src = at(c[r], vb, vpend) + i * (int)sizeof(typename Blk::vec);
+#pragma unroll
+        for (int h = 0; h < Blk::kVP; ++h) x.v[4 * t + r][h] = *reinterpret_cast<const typename Blk::vec*>(src + h * 256);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  f32x4 O[RT][kMT];
+  float m_run[RT], l_run[RT];  // row rt * 16 + i; l_run covers this lane's quarter of the tokens
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    m_run[rt] = -INFINITY;
+    l_run[rt] = 0.f;
+#pragma unroll
+    for (int c = 0; c < kMT; ++c) O[rt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  // S^T of block x, online softmax in log2 units (the scale is applied inside the exponent); what is left in
+  // `pr` are the weights, fp32
+  auto scores = [&](Blk& x, int b, int n_here, f32x4 (&pr)[kNT][RT]) {
+    if constexpr (ROPE) {  // deferred rows that are to be turned on their way into the pool
+      if (p.pend_rope) {
+#pragma unroll
+        for (int t = 0; t < kNT; ++t) {
+          const uint32_t code = lds.off[b * kTok + 16 * t + i];
+          if (__builtin_amdgcn_ballot_w64((int)code < 0)) {
+            const int row = (int)((code & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
+            if ((int)code < 0) rope_lane<T, kNP>(x.k[t], q, pend_pos_of(p)[row], p.rope_tab);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < kNT; ++t)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) pr[t][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < kNP; ++kk) {
+      if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int t = 0; t < kNT; ++t)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            pr[t][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[t][kk]), __builtin_bit_cast(bf16x8, qf[rt][kk]), pr[t][rt], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < kNT; ++t)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              pr[t][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.k[t][kk][e]), __uint_as_float(qf[rt][kk][e]), pr[t][rt], 0, 0, 0);
+      }
+    }
+    if ((b + 1) * kTok > n_here) {  // tokens past the item's end are hidden (a block holds at least one that exists)
+      const int left = n_here - (b * kTok + 4 * q);
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) pr[t][rt][r] = 16 * t + r < left ? pr[t][rt][r] : -INFINITY;
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, pr[t][rt][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      const float mn = fmaxf(m_run[rt], mx * p.scale_log2e);
+      const float corr = fast_exp2(m_run[rt] - mn);
+      m_run[rt] = mn;
+      float ps = 0.f;
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pr[t][rt][r] = fast_exp2(fmaf(pr[t][rt][r], p.scale_log2e, -mn));
+          ps += pr[t][rt][r];
+        }
+      l_run[rt] = l_run[rt] * corr + ps;
+      if (!__all(corr == 1.f)) {
+#pragma unroll
+        for (int c = 0; c < kMT; ++c) O[rt][c] *= corr;
+      }
+    }
+  };
+  auto weigh = [&](const Blk& x, const f32x4 (&pr)[kNT][RT]) {  // O^T += V^T P^T
+    if constexpr (sizeof(T) == 2) {
+      bf16x8 pb[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+        pb[rt] = __builtin_bit_cast(bf16x8, u32x4{pack_bf16x2(pr[0][rt][0], pr[0][rt][1]), pack_bf16x2(pr[0][rt][2], pr[0][rt][3]),
+                                                  pack_bf16x2(pr[1][rt][0], pr[1][rt][1]), pack_bf16x2(pr[1][rt][2], pr[1][rt][3])});
+#pragma unroll
+      for (int c = 0; c < kMT; ++c) {
+        u32x4 a;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)  // element c of tokens 2 e and 2 e + 1
+          a[e] = __builtin_amdgcn_perm(x.v[2 * e + 1][0][c / 2], x.v[2 * e][0][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), pb[rt], O[rt][c], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < kMT; ++c)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[4 * t + r][c / 4][c % 4], pr[t][rt][r], O[rt][c], 0, 0, 0);
+    }
+  };
+
+  // ---- the item's tokens, in windows of kDirWin
+  bool q_turned = false;
+  for (int w0 = 0; w0 < n_tok; w0 += kDirWin) {
+    const int n_here = min(kDirWin, n_tok - w0);
+    const int nb = (n_here + kTok - 1) / kTok;
+    if (w0) lds_barrier();  // everybody is done with the last window's codes
+    for (int j = tid; j < nb * kTok; j += NW * 64) lds.off[j] = code_of(w0 + min(j, n_here - 1));  // past the end: the last token again
+    lds_barrier();
+    if (w >= nb) continue;
+    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
+    Blk A;
+    f32x4 pr[kNT][RT];
+    auto turn_q = [&]() {
+      if constexpr (ROPE) {
+        if (p.rope_q && !q_turned) {
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) rope_lane<T, kNP>(qf[rt], q, qpos[rt], p.rope_tab);
+        }
+        q_turned = true;
+      }
+    };
+    load_k(A, w);
+    load_v(A, w);
+    turn_q();
+    for (int b = w; b < last; b += NW) {  // the next block is requested half by half, as this one's places fall free
+      scores(A, b, n_here, pr);
+      load_k(A, b + NW);
+      weigh(A, pr);
+      load_v(A, b + NW);
+    }
+    scores(A, last, n_here, pr);
+    weigh(A, pr);
+  }
+
+  // ---- the waves meet once.  Group (rt, r, cg) of a lane: head dims of M-tiles 4 cg .. 4 cg + 3 at m = 4 q + r.
+  const int n_act = min(NW, (min(kDirWin, n_tok) + kTok - 1) / kTok);  // waves that had a block
+  if (w < n_act) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      if (rt * 16 + i < R) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int cg = 0; cg < D / 64; ++cg)
+            lds.o[w][((rt * 4 + r) * (D / 64) + cg) * 65 + lane] = f32x4{O[rt][4 * cg][r], O[rt][4 * cg + 1][r], O[rt][4 * cg + 2][r], O[rt][4 * cg + 3][r]};
+      }
+      float l = l_run[rt] + __shfl_xor(l_run[rt], 16, kWave);
+      l += __shfl_xor(l, 32, kWave);
+      if (q == 0) { lds.mw[w][rt * 16 + i] = m_run[rt]; lds.lw[w][rt * 16 + i] = l; }
+    }
+  }
+  __syncthreads();
+  constexpr int kPR = D / 4, kRows = NW * 64 / kPR;  // pieces of 4 floats per row, rows per pass
+  const int pc = tid % kPR;
+  // which group and quarter piece pc of a row sits in
+  int cg, qq, r;
+  if constexpr (sizeof(T) == 2 && D == 128) { qq = pc >> 3; r = (pc >> 1) & 3; cg = pc & 1; }
+  else { cg = pc >> 4; qq = (pc >> 2) & 3; r = pc & 3; }
+#pragma unroll
+  for (int pass = 0; pass < 16 * RT / kRows; ++pass) {
+    if (pass * kRows >= R) break;
+    const int rr = pass * kRows + tid / kPR;
+    const int slot = (((rr >> 4) * 4 + r) * (D / 64) + cg) * 65 + 16 * qq + (rr & 15);
+    float mk[NW], ma = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      mk[k] = k < n_act ? lds.mw[k][rr] : -INFINITY;
+      ma = fmaxf(ma, mk[k]);
+    }
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      if (k < n_act) {
+        const float sc = fast_exp2(mk[k] - ma);
+        acc += lds.o[k][slot] * sc;
+        l = fmaf(lds.lw[k][rr], sc, l);
+      }
+    }
+    if (rr < R) {
+      *reinterpret_cast<f32x4*>(p.part_acc + (it.part_row0 + rr) * D + 4 * pc) = acc;
+      if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(ma, l);
+    }
+  }
+}
+
+// The copy of a deferred append's rows into the pool (no work-group of the launch reads those pool rows: lists
+// that name them are served from k_pend / v_pend), spread thin over the work-groups' first 16 threads; fewer
+// work-groups than that take more each.  ROPE: K rows are turned on the way.
+template <typename T, int D, bool ROPE>
+__device__ __forceinline__ void direct_copy_pending(const DecodeParams& p) {
+  constexpr int kPieceRow = D * (int)sizeof(T) / 16;
+  const int row_pieces = p.Hkv * kPieceRow, total = p.pend_n * row_pieces;
+  const bool thin = 2 * total <= (int)gridDim.x * 16;
+  const int step = thin ? 2 * total : (int)gridDim.x * (int)blockDim.x;
+  for (int t = thin ? (threadIdx.x < 16 ? (int)blockIdx.x * 16 + (int)threadIdx.x : 2 * total) : (int)(blockIdx.x * blockDim.x + threadIdx.x);
+       t < 2 * total; t += step) {
+    const bool is_v = t >= total;
+    const int u = is_v ? t - total : t;
+    const int row = u / row_pieces, g = (u % row_pieces) / kPieceRow, piece = u % kPieceRow;
+    const uint4* src = reinterpret_cast<const uint4*>(is_v ? p.v_pend : p.k_pend);
+    uint4 val;
+    if (ROPE && p.pend_rope && !is_v)
+      val = rope_row_piece(src + (u - piece), piece, kPieceRow, sizeof(T) == 4, pend_pos_of(p)[row], p.rope_tab);
+    else
+      val = src[u];
+    char* dst = reinterpret_cast<char*>(const_cast<void*>(is_v ? p.v : p.k));
+    *reinterpret_cast<uint4*>(dst + elem_off(p.lay, pend_dst_of(p)[row], g) * (long long)sizeof(T) + piece * 16) = val;
+  }
+}
+
+// Address code of logical slot `slot` of request `req`, kv head g (deferred rows: their place in k_new / v_new).
+template <typename T, int D>
+__device__ __forceinline__ uint32_t direct_code(const DecodeParams& p, int req, int slot, int g, int pend0, int pend_src0, int& phys) {
+  phys = phys_row(p.lay, p.page_table, req, slot);
+  if (slot >= pend0) return kPendBit | (uint32_t)(((pend_src0 + (slot - pend0)) * p.Hkv + g) * (D * (int)sizeof(T) / 16));
+  return (uint32_t)((unsigned long long)(elem_off(p.lay, phys, g) * (long long)sizeof(T)) >> 4);
+}
+
+template <typename T, int D, bool ROPE>
+__global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
+  __shared__ DirLds<D, 2, 4> lds;
+  const int32_t* meta = meta_of(p);
+  const int tid = threadIdx.x;
+  if (p.pend_n > 0) direct_copy_pending<T, D, ROPE>(p);
+  const int n_prefix_wgs = (int)gridDim.x - p.n_mfma_items * p.Hkv;
+  const int G = p.Hq / p.Hkv;
+  DirItem it;
+  it.req_streams = nullptr;
+  it.row0 = 0;
+  it.q_stream = 0;
+  if ((int)blockIdx.x < n_prefix_wgs) {  // a chunk of a request's common prefix, up to 32 stacked rows (work-group order as in k_attn)
+    const int wi = blockIdx.x;
+    DevReq rq;
+    if (p.single_req) {
+      rq = p.req0;
+    } else {
+      const DevReq* reqs = reinterpret_cast<const DevReq*>(meta + p.off_reqs);
+      int qi = 0;
+      for (; qi < p.n_reqs - 1; ++qi) {
+        const int b = reqs[qi].wg_begin;
+        if (wi >= b && wi < b + reqs[qi].n_chunks * p.Hkv * ((reqs[qi].n_streams * G + 31) >> 5)) break;
+      }
+      rq = reqs[qi];
+      it.req_streams = meta + p.off_req_streams + rq.stream0;
+    }
+    const int R_all = rq.n_streams * G, n_rg = (R_all + 31) >> 5;
+    const int wl = wi - rq.wg_begin, t = wl / p.Hkv;
+    const int c = __builtin_amdgcn_readfirstlane(t / n_rg);
+    it.row0 = __builtin_amdgcn_readfirstlane((t % n_rg) * 32);
+    it.g = __builtin_amdgcn_readfirstlane(wl % p.Hkv);
+    it.R = __builtin_amdgcn_readfirstlane(min(32, R_all - it.row0));
+    const int slot0 = c * rq.chunk_tokens;
+    it.n_tok = __builtin_amdgcn_readfirstlane(min(rq.chunk_tokens, rq.pc - slot0));
+    it.part_row0 = rq.part_base + (long long)(it.g * rq.n_chunks + c) * R_all + it.row0;
+    const bool report = p.dbg_rows && it.g == 0 && it.row0 == 0;
+    const DevStream* streams = reinterpret_cast<const DevStream*>(meta + p.off_streams);
+    auto code_of = [&](int j) -> uint32_t {
+      int phys;
+      const uint32_t code = direct_code<T, D>(p, rq.req, slot0 + j, it.g, rq.pend0, rq.pend_src0, phys);
+      if (report)
+        for (int k = 0; k < rq.n_streams; ++k)
+          p.dbg_rows[streams[it.req_streams ? it.req_streams[k] : k].gather_base + slot0 + j] = phys;
+      return code;
+    };
+    if (it.R > 16) direct_rows<T, D, 2, 4, false, ROPE>(p, lds, meta, it, code_of);
+    else direct_rows<T, D, 1, 4, false, ROPE>(p, lds, meta, it, code_of);
+    return;
+  }
+  // ---- a piece of one stream's private list
+  const int wi = (int)blockIdx.x - n_prefix_wgs;
+  const int item = wi / p.Hkv;
+  it.g = __builtin_amdgcn_readfirstlane(wi % p.Hkv);
+  DevItem di;
+  int nr = 0, range0 = 0;
+  bool in_ranges = false;
+  DevStream st{};
+  if (!p.dev_tables) {
+    di = reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
+    nr = di.n_ranges > 1 ? di.n_ranges : 0;
+    range0 = di.range_first;
+  } else {
+    const int si = dev_stream_of_item(p, meta, item);
+    st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[si];
+    di = dev_item(p, st, si, item, in_ranges);
+    if (in_ranges) range0 = dev_item_candidates(p, st, di.tok_begin, di.tok_count, kGatherMax, nr);
+  }
+  int req, pend0, pend_src0;
+  if (p.single_req) {
+    req = p.req0.req; pend0 = p.req0.pend0; pend_src0 = p.req0.pend_src0;
+  } else {
+    const int qi = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream].req_idx;
+    const DevReq rq = reinterpret_cast<const DevReq*>(meta + p.off_reqs)[qi];
+    req = rq.req; pend0 = rq.pend0; pend_src0 = rq.pend_src0;
+  }
+  nr = __builtin_amdgcn_readfirstlane(nr);
+  if (nr > 0) {  // the ranges the piece overlaps (device-resident lists: candidates for it) -> LDS
+    const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
+    for (int k = tid; k < nr; k += kAttnThreads) lds.ranges[k] = p.dev_tables ? dev_range_at(p, st, range0 + k) : ranges[range0 + k];
+    __syncthreads();
+  }
+  it.n_tok = __builtin_amdgcn_readfirstlane(di.tok_count);
+  it.R = G;
+  it.q_stream = di.stream;
+  it.part_row0 = p.priv_part_base + (long long)(item * p.Hkv + it.g) * G;
+  const bool report = p.dbg_rows && it.g == 0;
+  auto code_of = [&](int j) -> uint32_t {
+    int slot;
+    if (nr > 0) {  // the last range with cum <= tok
+      const int tok = di.tok_begin + j;
+      int lo = 0, hi = nr - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (lds.ranges[mid].cum <= tok) lo = mid; else hi = mid - 1;
+      }
+      slot = lds.ranges[lo].start + (tok - lds.ranges[lo].cum) * lds.ranges[lo].stride;
+    } else {
+      slot = di.slot0 + j * di.stride;
+    }
+    int phys;
+    const uint32_t code = direct_code<T, D>(p, req, slot, it.g, pend0, pend_src0, phys);
+    if (report) p.dbg_rows[di.gather_pos + j] = phys;
+    return code;
+  };
+  direct_rows<T, D, 1, 4, true, ROPE>(p, lds, meta, it, code_of);
+}
+
+}  // namespace pasta

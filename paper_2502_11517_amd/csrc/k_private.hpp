@@ -1,8 +1,8 @@
 // K3, vector-ALU form -- per-stream private-segment partial attention (arxiv 2502.11517,
 // Section 3, "Efficiency": a thread attends only to its own rows of the interleaved pool
 // plus the spawning thread's rows that existed before the fork; Figure 2b/2c).  This form
-// serves fp32 pools, D = 64, and the whole visible list when the matrix-core kernel is
-// switched off; bf16 D = 128 private segments normally go through k_attn's gather items.
+// walks the whole visible list when the matrix-core kernels are switched off (and in pools of
+// 32 GiB and more per layer, which they do not address).
 //
 // One wavefront walks one work item = (stream, kv head, chunk of <= 128 tokens of the
 // stream's private list).  The list is a sequence of (start, count, stride) ranges of

@@ -78,7 +78,7 @@ __device__ __forceinline__ uint4 rope_row_piece(const uint4* src, int piece, int
   return make_uint4(out[0], out[1], out[2], out[3]);
 }
 
-// What a decode step has to turn before its attention launch, in one small launch: the Q rows
+// What a decode step with a k_attn launch has to turn before it, in one small launch: the Q rows
 // (into q_rot, [n][Hq][D]) and the K rows of a deferred rotating append (into k_rot,
 // [pend_n][Hkv][D]; the attention launch then reads and copies those instead of the caller's
 // unrotated rows).  One thread per 16-byte piece; pieces [0, n_q_pieces) are Q's.  Rotating

@@ -18,6 +18,7 @@
 #include "../../include/pasta_attn.h"
 #include "k_append.hpp"
 #include "k_attn.hpp"
+#include "k_direct.hpp"
 #include "k_merge.hpp"
 #include "k_private.hpp"
 
@@ -1101,10 +1102,15 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     const bool mfma = c.dtype == PASTA_BF16 && !(a->flags & PASTA_DECODE_NO_MFMA) && attn_kernel_supports(D, G) &&
                       h->layer_elems * h->elem < ((int64_t)1 << 32) - 65536 &&
                       (int64_t)n * c.n_q_heads * D * h->elem < ((int64_t)1 << 31);
-    if ((dense || probe) && !mfma) return PASTA_E_INVAL;  // the mask and the read-only form belong to the matrix-core kernel
+    if ((dense || probe) && !mfma) return PASTA_E_INVAL;  // the mask and the read-only form belong to that kernel
+    // Everything else -- fp32, 64-wide heads, layers too large for 32-bit offsets -- goes through the kernel that
+    // takes its operands straight from memory (its address codes count 16-byte pieces in 31 bits).  The vector-ALU
+    // walker is left with NO_MFMA and what is larger still.
+    const bool direct = !mfma && !(a->flags & PASTA_DECODE_NO_MFMA) && h->layer_elems * h->elem < ((int64_t)1 << 35);
+    const bool matrix = mfma || direct;
     int64_t pc_total = 0, pc_weighted = 0;  // the second counts a prefix once per work-group that reads it
     for (auto& q : reqs) {
-      if (!mfma || q.pc < kTile || no_share) q.pc = 0;
+      if (!matrix || q.pc < kTile || no_share) q.pc = 0;
       pc_total += q.pc;
     }
     // More than 32 stacked rows per request: the rows go in groups of 32.  When EVERY request with a
@@ -1140,7 +1146,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // multiple of the 64-token tile that still gives kNumCUs prefix work-groups.  Private
     // items stay at 128 tokens: they are few and their rows are scattered.
     int64_t priv_chunk = kPrivChunk, chunk_tokens = kTile;
-    if (mfma) {
+    if (matrix) {
       chunk_tokens = std::max<int64_t>(kTile, pc_weighted * Hkv / h->n_cus / kTile * kTile);
       priv_chunk = wide ? 256 : 128;  // (beside the long wide work-groups the private items get one slot per CU: longer items keep more in flight there)
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
@@ -1333,8 +1339,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     int rc = PASTA_OK;
     hipStream_t st = (hipStream_t)c.hip_stream;
     int meta_slot = -1;  // pinned staging slot that this call's kernels read, if any
-    // a deferred append rides along with the matrix-core launch of its layer; otherwise K1 runs now
-    const bool take_pending = h->pending.active && mfma && h->pending.layer == a->layer && !probe && !merge_only;
+    // a deferred append rides along with the partials launch of its layer; otherwise K1 runs now
+    const bool take_pending = h->pending.active && matrix && h->pending.layer == a->layer && !probe && !merge_only;
     if (h->pending.active && !take_pending) {
       rc = flush_pending(h);
       if (rc != PASTA_OK) return rc;
@@ -1415,7 +1421,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     p.n_streams = n;
     p.n_reqs = (int)reqs.size();
     p.n_items = (int)n_items_total;
-    p.n_mfma_items = mfma ? (int)n_items_total : 0;
+    p.n_mfma_items = matrix ? (int)n_items_total : 0;
     p.arena = (const DevRange*)((const char*)c.workspace + h->off_arena);
     p.cidx = (const int32_t*)((const char*)c.workspace + h->off_cidx);
     p.dev_tables = dev_lists ? 1 : 0;
@@ -1438,7 +1444,11 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     }
     p.req0 = reqs[0];
 
-    if (rope_q || p.pend_rope) {
+    const bool rope = rope_q || p.pend_rope;
+    if (rope && direct) {  // that kernel turns what it has to as it loads it
+      p.rope_tab = (const double*)((const char*)c.workspace + h->off_rope);
+      p.rope_q = rope_q ? 1 : 0;
+    } else if (rope) {
       // one small launch turns what has to be turned: Q into its buffer, the deferred K rows into theirs
       p.rope_tab = (const double*)((const char*)c.workspace + h->off_rope);
       p.rope_q = rope_q ? 1 : 0;
@@ -1455,17 +1465,25 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // start and the end of that kernel's execution (what a kernel trace reports) and put no packet of
     // their own on the stream; around the vector-ALU form they are recorded on the stream.
     const hipEvent_t ev0 = (hipEvent_t)a->prof_event_start, ev1 = (hipEvent_t)a->prof_event_stop;
-    const bool ev_in_dispatch = mfma && ev0 && ev1;
+    const bool ev_in_dispatch = matrix && ev0 && ev1;
     if (ev0 && !ev_in_dispatch && hipEventRecord(ev0, st) != hipSuccess) return PASTA_E_DEVICE;
     if (merge_only) {
       // (kernel-isolated test of the merge: the partial buffers are taken as they are)
-    } else if (mfma) {
+    } else if (matrix) {
       const unsigned grid = (unsigned)(n_items_total * Hkv + n_prefix_wgs);
       auto launch = [&](auto kernel) {
         if (ev_in_dispatch) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, ev0, ev1, 0, p);
         else kernel<<<dim3(grid), kAttnThreads, 0, st>>>(p);
       };
-      if (dense) {  // the variant that carries the dense-mask mode
+      if (direct) {
+        if (c.dtype == PASTA_F32) {
+          if (D == 64) { if (rope) launch(k_direct<float, 64, true>); else launch(k_direct<float, 64, false>); }
+          else { if (rope) launch(k_direct<float, 128, true>); else launch(k_direct<float, 128, false>); }
+        } else {
+          if (D == 64) { if (rope) launch(k_direct<uint16_t, 64, true>); else launch(k_direct<uint16_t, 64, false>); }
+          else { if (rope) launch(k_direct<uint16_t, 128, true>); else launch(k_direct<uint16_t, 128, false>); }
+        }
+      } else if (dense) {  // the variant that carries the dense-mask mode
         if (h->lay.paged) launch(k_attn<true, true>);
         else launch(k_attn<false, true>);
       } else {
