@@ -107,6 +107,7 @@ struct pasta_attn {
     int32_t dst_rows[kAppendInline]{};
     bool rope = false;                 // PASTA_APPEND_ROPE: K still to be rotated by pos
     int32_t pos[kAppendInline]{};
+    std::vector<AppendRun> runs;       // the same rows as runs, for the launch that copies them if no decode step does
     std::vector<int32_t> req_pend0, req_src0;  // per request: first deferred slot, its row in k_new
     std::vector<int32_t> stage_p0, stage_s0, stage_last;  // (their buffers while a call is looked at)
   } pending;
@@ -123,7 +124,8 @@ struct pasta_attn {
                 int32_t dev_ranges, dev_cidx; bool dirty; bool replaced; std::vector<Range> saved; };
   std::vector<Undo> undo;                // append_kv: what to restore if a later row of the call fails
   std::vector<int64_t> t2;
-  std::vector<int32_t> dst_rows, slots;
+  std::vector<int32_t> dst_rows;         // destination rows of a call whose runs do not fit the kernel arguments
+  std::vector<AppendRun> runs;           // append_kv: the call's rows as runs
   int tune_prefix_chunk = 0, tune_priv_chunk = 0;  // forced chunk sizes (tokens; 0 = heuristic): set only by -DPASTA_TUNING builds
   // device-side readiness (deferred so that the host logic works without a GPU)
   bool device_ready = false;
@@ -366,6 +368,17 @@ void add_slot(StreamState& s, int32_t slot) {
   s.ranges.push_back({slot, 1, 1});
 }
 
+// Adds n slots from `slot` on.
+void add_slots(StreamState& s, int32_t slot, int32_t n) {
+  int32_t k = 0;
+  for (; k < n && k < 3; ++k) add_slot(s, slot + k);
+  if (k == n) return;
+  // three consecutive slots behind each other: the newest range ends in them with stride 1, or all is still the head
+  if (s.ranges.empty()) { s.prefix_len += n - k; return; }
+  s.ranges.back().count += n - k;
+  s.range_tokens += n - k;
+}
+
 template <typename T, int D>
 int launch_private_g(int G, dim3 grid, hipStream_t st, const DecodeParams& p) {
   switch (G) {
@@ -424,61 +437,63 @@ struct ListPatches {  // entries of the device-resident lists that an append bri
   int32_t c_val[kPatchMax];
 };
 
-int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const void* v_new,
-                  const int32_t* dst_rows, const int32_t* positions = nullptr,  // positions: rotate K
-                  const ListPatches* patches = nullptr) {
+// Launches K1 for n_rows rows that form the given runs.  positions: rotate K by them.
+int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const void* v_new, const std::vector<AppendRun>& runs,
+                  const int32_t* positions = nullptr, const ListPatches* patches = nullptr) {
   const pasta_attn_config& c = h->cfg;
   hipStream_t st = (hipStream_t)c.hip_stream;
   AppendParams p{};
   p.arena = (DevRange*)((char*)c.workspace + h->off_arena);
   p.cidx = (int32_t*)((char*)c.workspace + h->off_cidx);
-  if (patches) {  // (only with rows that travel in the kernel arguments: one launch)
-    p.n_rpatch = patches->n_r;
-    p.n_cpatch = patches->n_c;
-    std::memcpy(p.rp_idx, patches->r_idx, sizeof(int32_t) * patches->n_r);
-    std::memcpy(p.rp_val, patches->r_val, sizeof(DevRange) * patches->n_r);
-    std::memcpy(p.cp_idx, patches->c_idx, sizeof(int32_t) * patches->n_c);
-    std::memcpy(p.cp_val, patches->c_val, sizeof(int32_t) * patches->n_c);
-  }
+  p.page_table = (const int32_t*)((const char*)c.workspace + h->off_page_table);
   p.k = (char*)c.k_pool + (size_t)layer * h->layer_elems * h->elem;
   p.v = (char*)c.v_pool + (size_t)layer * h->layer_elems * h->elem;
   p.lay = h->lay;
   p.Hkv = c.n_kv_heads;
-  p.pieces_per_head = c.head_dim * h->elem / 16;
   p.elem_shift = h->elem == 4 ? 2 : 1;
+  while ((16 << p.pph_log2) < c.head_dim * h->elem) p.pph_log2++;
   const size_t row_bytes = (size_t)c.n_kv_heads * c.head_dim * h->elem;
-  p.rope_tab = positions ? (const double*)((const char*)c.workspace + h->off_rope) : nullptr;
-  p.pos_rows = nullptr;
-  if (n_rows <= kAppendInline) {
-    p.k_new = (const uint4*)k_new;
-    p.v_new = (const uint4*)v_new;
-    p.n_rows = n_rows;
-    p.dst_rows = nullptr;
-    std::memcpy(p.inline_rows, dst_rows, (size_t)n_rows * 4);
-    if (positions) std::memcpy(p.inline_pos, positions, (size_t)n_rows * 4);
-    const long long total = 2ll * n_rows * c.n_kv_heads * p.pieces_per_head;
-    k_append<<<dim3((unsigned)((total + 255) / 256)), 256, 0, st>>>(p);
+  const bool rope = positions != nullptr;
+  p.rope_tab = rope ? (const double*)((const char*)c.workspace + h->off_rope) : nullptr;
+  const long long units_per_row = (long long)row_bytes / 16 / (rope ? 2 : 1);
+  auto launch = [&](size_t lo, size_t n) -> int {  // rows [lo, lo + n) of the call
+    p.n_rows = (int)n;
+    p.k_new = (const u32x4*)((const char*)k_new + lo * row_bytes);
+    p.v_new = (const u32x4*)((const char*)v_new + lo * row_bytes);
+    const long long threads = ((long long)n * units_per_row + append_units(rope) - 1) / append_units(rope);
+    const dim3 grid((unsigned)((threads + 255) / 256));
+    if (rope) k_append<true><<<grid, 256, 0, st>>>(p);
+    else k_append<false><<<grid, 256, 0, st>>>(p);
     return hipGetLastError() == hipSuccess ? PASTA_OK : PASTA_E_DEVICE;
+  };
+  const size_t most = (size_t)(((int64_t)1 << 30) / units_per_row);  // 32-bit piece numbers in the kernel
+  if (runs.size() <= (size_t)kAppendRuns && (size_t)n_rows <= most) {
+    p.n_runs = (int)runs.size();
+    std::memcpy(p.runs, runs.data(), runs.size() * sizeof(AppendRun));
+    if (patches) {
+      p.n_rpatch = patches->n_r;
+      p.n_cpatch = patches->n_c;
+      std::memcpy(p.rp_idx, patches->r_idx, sizeof(int32_t) * patches->n_r);
+      std::memcpy(p.rp_val, patches->r_val, sizeof(DevRange) * patches->n_r);
+      std::memcpy(p.cp_idx, patches->c_idx, sizeof(int32_t) * patches->n_c);
+      std::memcpy(p.cp_val, patches->c_val, sizeof(int32_t) * patches->n_c);
+    }
+    return launch(0, (size_t)n_rows);
   }
-  // large appends (prefill) go in pieces that fit one staging slot
-  const size_t per = h->meta_bytes / 4;
+  // more runs than travel in the kernel arguments: the destination rows as a list, in pieces of one staging slot
+  std::vector<int32_t>& dst = h->dst_rows;
+  dst.resize((size_t)n_rows);
+  for (size_t k = 0; k < runs.size(); ++k) {
+    const int32_t end = k + 1 < runs.size() ? runs[k + 1].row0 : n_rows;
+    for (int32_t i = runs[k].row0; i < end; ++i) dst[(size_t)i] = (int32_t)host_phys(h, runs[k].req, runs[k].slot0 + (i - runs[k].row0));
+  }
+  const size_t per = std::min(h->meta_bytes / 4, most);
   for (size_t lo = 0; lo < (size_t)n_rows; lo += per) {
     const size_t n = std::min(per, (size_t)n_rows - lo);
-    const int32_t* dev = nullptr;
-    int rc = upload_meta(h, dst_rows + lo, n * 4, &dev);
+    int rc = upload_meta(h, dst.data() + lo, n * 4, &p.dst_rows);
+    if (rc == PASTA_OK && rope) rc = upload_meta(h, positions + lo, n * 4, &p.pos_rows);
+    if (rc == PASTA_OK) rc = launch(lo, n);
     if (rc != PASTA_OK) return rc;
-    p.dst_rows = dev;
-    if (positions) {
-      rc = upload_meta(h, positions + lo, n * 4, &dev);
-      if (rc != PASTA_OK) return rc;
-      p.pos_rows = dev;
-    }
-    p.n_rows = (int)n;
-    p.k_new = (const uint4*)((const char*)k_new + lo * row_bytes);
-    p.v_new = (const uint4*)((const char*)v_new + lo * row_bytes);
-    const long long total = 2ll * (long long)n * c.n_kv_heads * p.pieces_per_head;
-    k_append<<<dim3((unsigned)((total + 255) / 256)), 256, 0, st>>>(p);
-    if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
   }
   return PASTA_OK;
 }
@@ -488,7 +503,7 @@ int flush_pending(pasta_attn* h) {
   if (!h->pending.active) return PASTA_OK;
   h->pending.active = false;
   return launch_append(h, h->pending.layer, h->pending.n_rows, h->pending.k_new, h->pending.v_new,
-                       h->pending.dst_rows, h->pending.rope ? h->pending.pos : nullptr);
+                       h->pending.runs, h->pending.rope ? h->pending.pos : nullptr);
 }
 
 }  // namespace
@@ -629,7 +644,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
   // (per touched stream: its state at first touch -- an append only ever changes a list's newest range
   // or adds ranges behind it)
   std::vector<int64_t>& t2 = h->t2;
-  std::vector<int32_t>&dst_rows = h->dst_rows, &slots = h->slots;
+  std::vector<AppendRun>& runs = h->runs;
   std::vector<pasta_attn::Undo>& undo = h->undo;
   auto roll_back = [&]() {
     for (size_t u = undo.size(); u-- > 0;) {
@@ -645,8 +660,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
   };
   try {
     t2 = commit ? h->tail : h->tail_before;
-    dst_rows.resize(a->n_rows);
-    slots.resize(a->n_rows);
+    runs.clear();
     undo.clear();
     auto touch = [&](int req, int sid) -> StreamState& {  // logs the stream's state the first time it is touched
       const int64_t key = (int64_t)req * c.max_streams + sid;
@@ -661,22 +675,32 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       return st;
     };
     auto fail = [&](int code) { roll_back(); return code; };
-    for (int i = 0; i < a->n_rows; ++i) {
+    // rows are taken in groups: one stream's consecutive rows, of which only the first may open it
+    for (int i = 0, end; i < a->n_rows; i = end) {
       const int r = a->request_id[i], s = a->stream_id[i];
       const int par = a->parent_stream ? a->parent_stream[i] : -1;
       if (r < 0 || r >= c.max_requests || s < 0 || s >= c.max_streams) return fail(PASTA_E_INVAL);
       if (par < -1 || par >= c.max_streams || par == s) return fail(PASTA_E_INVAL);
+      end = i + 1;
+      while (end < a->n_rows && a->request_id[end] == r && a->stream_id[end] == s && (!a->parent_stream || a->parent_stream[end] == -1)) end++;
+      const int n_g = end - i;
       const int64_t slot = t2[r];
-      if (slot >= (c.page_tokens ? (int64_t)h->req_pages[r] << h->page_shift : h->req_capacity)) return fail(PASTA_E_CAPACITY);
+      if (slot + n_g > (c.page_tokens ? (int64_t)h->req_pages[r] << h->page_shift : h->req_capacity)) return fail(PASTA_E_CAPACITY);
+      t2[r] = slot + n_g;
+      // the copy's runs: one as long as the request stays the same (and the position ids go on by one)
+      for (int k = i; k < end;) {
+        int ke = end;
+        if (rope) for (ke = k + 1; ke < end && a->position[ke] == a->position[ke - 1] + 1;) ke++;
+        if (k == 0 || a->request_id[k - 1] != r || (rope && a->position[k] != a->position[k - 1] + 1))
+          runs.push_back(AppendRun{k, r, (int32_t)(slot + (k - i)), rope ? a->position[k] : 0});
+        k = ke;
+      }
       if (!commit) {  // replay: same slots as the layer-0 call, lists untouched
-        if (slot >= h->tail[r]) return fail(PASTA_E_STATE);
-        slots[i] = (int32_t)slot;
-        dst_rows[i] = (int32_t)host_phys(h, r, slot);
-        t2[r] = slot + 1;
+        if (slot + n_g > h->tail[r]) return fail(PASTA_E_STATE);
         continue;
       }
       StreamState& st = touch(r, s);
-      if (par >= 0 || !st.open) {  // the row opens the stream: as a fork of `par`, or as a root (empty visible set)
+      if (par >= 0 || !st.open) {  // the first row opens the stream: as a fork of `par`, or as a root (empty visible set)
         if (par >= 0 && st.open) return fail(PASTA_E_INVAL);  // parent only on the row that opens the stream
         const StreamState* ps = nullptr;
         if (par >= 0) {
@@ -700,11 +724,8 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
         st.dirty = true;  // the device copy is rebuilt from the mirror when a decode step wants it
         st.dev_ranges = st.dev_cidx = 0;
       }
-      add_slot(st, (int32_t)slot);
+      add_slots(st, (int32_t)slot, n_g);
       if ((int64_t)st.ranges.size() > c.max_ranges) return fail(PASTA_E_CAPACITY);
-      slots[i] = (int32_t)slot;
-      dst_rows[i] = (int32_t)host_phys(h, r, slot);
-      t2[r] = slot + 1;
     }
   } catch (...) { roll_back(); return PASTA_E_NOMEM; }
 
@@ -758,6 +779,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
 
   // ---- enqueue K1, or leave the copy to the next decode_step (PASTA_APPEND_DEFER)
   int rc = PASTA_OK;
+  bool runs_left_to_pending = false;
   auto fail_dev = [&](int code) { if (commit) roll_back(); return code; };
   // At most one deferred append is outstanding, and the slots it covers are the newest of their
   // requests: any later append -- also one that only reserves slots for the caller's own kernel --
@@ -774,11 +796,11 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       s0.assign(c.max_requests, 0);
       std::vector<int32_t>& last = h->pending.stage_last;
       last.assign(c.max_requests, -2);
-      for (int i = 0; i < a->n_rows && defer; ++i) {
-        const int r = a->request_id[i];
-        if (p0[r] == INT32_MAX) { p0[r] = slots[i]; s0[r] = i; }
-        else if (last[r] != i - 1) defer = false;
-        last[r] = i;
+      for (size_t k = 0; k < runs.size() && defer; ++k) {
+        const AppendRun& rn = runs[k];
+        if (p0[rn.req] == INT32_MAX) { p0[rn.req] = rn.slot0; s0[rn.req] = rn.row0; }
+        else if (last[rn.req] != rn.row0 - 1) defer = false;
+        last[rn.req] = (k + 1 < runs.size() ? runs[k + 1].row0 : a->n_rows) - 1;
       }
     }
     if (defer) {
@@ -788,20 +810,30 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       pd.n_rows = a->n_rows;
       pd.k_new = a->k_new;
       pd.v_new = a->v_new;
-      std::memcpy(pd.dst_rows, dst_rows.data(), (size_t)a->n_rows * 4);
+      pd.runs.swap(runs);
+      for (size_t k = 0; k < pd.runs.size(); ++k) {
+        const AppendRun& rn = pd.runs[k];
+        const int32_t end = k + 1 < pd.runs.size() ? pd.runs[k + 1].row0 : a->n_rows;
+        for (int32_t i = rn.row0; i < end; ++i) pd.dst_rows[i] = (int32_t)host_phys(h, rn.req, rn.slot0 + (i - rn.row0));
+      }
       pd.rope = rope;
       if (rope) std::memcpy(pd.pos, a->position, (size_t)a->n_rows * 4);
       pd.req_pend0.swap(p0);
       pd.req_src0.swap(s0);
+      runs_left_to_pending = true;
     } else {
-      rc = launch_append(h, a->layer, a->n_rows, a->k_new, a->v_new, dst_rows.data(), rope ? a->position : nullptr,
+      rc = launch_append(h, a->layer, a->n_rows, a->k_new, a->v_new, runs, rope ? a->position : nullptr,
                          need_k1 ? &patches : nullptr);
       if (rc != PASTA_OK) return fail_dev(rc);
     }
   }
 
   // ---- commit
-  if (a->out_slot) std::memcpy(a->out_slot, slots.data(), (size_t)a->n_rows * 4);
+  if (a->out_slot) {
+    const std::vector<AppendRun>& rs = runs_left_to_pending ? h->pending.runs : runs;
+    for (size_t k = 0; k < rs.size(); ++k)
+      for (int32_t i = rs[k].row0, end = k + 1 < rs.size() ? rs[k + 1].row0 : a->n_rows; i < end; ++i) a->out_slot[i] = rs[k].slot0 + (i - rs[k].row0);
+  }
   if (commit) {
     h->tail_before = h->tail;
     h->tail.swap(t2);
