@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256) void k_append(AppendParams p) {
   }
 }
 
-// Carries a piece of a decode step's plan to the device inside its own kernel arguments: a plan too large
-// for the attention launch's arguments, but small (a few KB: one fixed-size record per stream), gets to
-// device memory this way in one or two tiny launches -- no copy engine, and no kernel reading host memory.
+// Carries a piece of a decode step's plan to the device inside its own kernel arguments (two launches at
+// most): how a step under stream capture sends a plan that is too large for k_plan's arguments, since a
+// captured launch must not depend on what later calls leave in host memory.
 constexpr int kRelayWords = 960;
 struct RelayParams {
   int32_t* dst;

@@ -39,7 +39,7 @@
 #pragma once
 #include <type_traits>
 
-#include "mfma_util.hpp"
+#include "k_plan.hpp"
 
 namespace pasta {
 
@@ -64,7 +64,6 @@ struct AttnLds {
   u32x4 q[32 * 16];            // stacked Q rows, same swizzle (rows >= R are zero)
   float mw[4][32], lw[4][32];  // per-wave row max / row sum at the end of the item
   uint8_t mask[kGatherMax];    // dense-mask comparison mode: the item's slice of its stream's mask
-  int sel[2];                  // device-resident lists: which candidate ranges hold an item's first and last token
   int rows[kGatherMax];        // listed gather items: row code of every token
   DevRange ranges[kGatherMax]; // listed gather items: the ranges the item overlaps
 };
@@ -73,7 +72,7 @@ struct BlockRegs { u32x4 k[8], v[8]; };  // one lane's share of a 32-token block
 
 // (FORM only keeps the instantiations of different kernels apart: the host pass of the compiler cannot
 // check this body -- it has no device builtins -- and refuses a specialization it has already tried)
-template <bool PAGED, bool GATHER, bool DENSE, bool LONG, bool PROBE, int FORM = 0>
+template <bool PAGED, bool GATHER, bool DENSE, bool LONG, bool PROBE, bool KEPT, int FORM>
 __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi) {
   constexpr int D = 128;
   const int tid = threadIdx.x;
@@ -132,28 +131,18 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
   } else {
     const int item = wi / p.Hkv;
     g = wi % p.Hkv;
-    // the work item: from the blob, or -- device-resident lists -- derived from the stream's record;
-    // a piece of a device-resident range list then finds its ranges among the candidates below
-    DevItem it;
-    int nr = 0, range0 = 0;      // ranges to bring into LDS: [range0, range0 + nr) of the blob or of the stream's arena
-    bool in_ranges = false;
-    DevStream dst{};
-    if (!p.dev_tables) {
-      it = reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
-      nr = it.n_ranges > 1 ? it.n_ranges : 0;
-      range0 = it.range_first;
-    } else {
-      const int si = dev_stream_of_item(p, meta, item);
-      dst = reinterpret_cast<const DevStream*>(meta + p.off_streams)[si];
-      it = dev_item(p, dst, si, item, in_ranges);
-      if (in_ranges) range0 = dev_item_candidates(p, dst, it.tok_begin, it.tok_count, kGatherMax, nr);
-    }
-    if (p.single_req) {  // scalars from the kernel arguments
+    // the work item: of a plan kept on the device its ranges are resolved and its tokens' rows written out
+    // (k_plan); otherwise both are worked out here from the blob
+    const DevItem it = KEPT ? p.items[item] : reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
+    const int nr = it.n_ranges > 1 ? it.n_ranges : 0;  // blob: the ranges to bring into LDS
+    const bool coded = KEPT && (PAGED || it.n_ranges > 0);
+    if (KEPT) {
+      req = coded ? 0 : -it.n_ranges; pend0 = coded ? INT32_MAX : it.range_first; pend_src0 = it.tok_begin;
+    } else if (p.single_req) {  // scalars from the kernel arguments
       req = p.req0.req; pend0 = p.req0.pend0; pend_src0 = p.req0.pend_src0;
     } else {
-      const int qi = reinterpret_cast<const DevStream*>(meta + p.off_streams)[it.stream].req_idx;
-      const DevReq rq = reinterpret_cast<const DevReq*>(meta + p.off_reqs)[qi];
-      req = rq.req; pend0 = rq.pend0; pend_src0 = rq.pend_src0;
+      const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[it.stream];
+      req = st.req; pend0 = st.pend0; pend_src0 = st.pend_src0;
     }
     R = G;
     q_stream = it.stream;
@@ -162,51 +151,34 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
     stride = it.stride;
     part_row0 = p.priv_part_base + (long long)(item * p.Hkv + g) * G;
     gather_pos = it.gather_pos;
-    listed = it.n_ranges > 1;
+    listed = KEPT ? coded : it.n_ranges > 1;
     if (DENSE && p.dense_mask) {  // comparison mode: the list is [0, tail), what may be seen is in the mask
       const int mb = meta_word(p, p.off_streams + it.stream * (int)(sizeof(DevStream) / 4) +
                                       (int)(__builtin_offsetof(DevStream, mask_base) / 4));
       for (int j = tid; j < kGatherMax; j += kAttnThreads)
         lds.mask[j] = j < n_tok ? p.dense_mask[mb + slot0 + j] : 0;  // published by the Q barrier
     }
-    if (p.dev_tables && in_ranges) {
-      // candidates -> LDS; the two that hold the piece's first and last token are found on the way
-      const int t_lo = it.tok_begin, t_hi = it.tok_begin + it.tok_count - 1;
-      for (int r = tid; r < nr; r += kAttnThreads) {
-        const DevRange rg = dev_range_at(p, dst, range0 + r);
-        lds.ranges[r] = rg;
-        if (rg.cum <= t_lo && t_lo < rg.cum + rg.count) lds.sel[0] = r;
-        if (rg.cum <= t_hi && t_hi < rg.cum + rg.count) lds.sel[1] = r;
+    if (KEPT && coded) {
+      const int32_t* codes = p.codes + (long long)item * p.priv_chunk;
+      for (int j = tid; j < n_tok; j += kAttnThreads) {
+        const int code = codes[j];
+        lds.rows[j] = code;
+        if (p.dbg_rows && g == 0) p.dbg_rows[gather_pos + j] = phys_of_code(p, code);
       }
       __syncthreads();
-      const int ra = lds.sel[0], rb = lds.sel[1];
-      const DevRange r0 = lds.ranges[ra];
-      it.slot0 = r0.start + (t_lo - r0.cum) * r0.stride;
-      it.stride = r0.stride;
-      it.n_ranges = rb - ra + 1;
-      slot0 = it.slot0;
-      stride = it.stride;
-      listed = it.n_ranges > 1;
-      range0 = ra;                 // from here on: index into lds.ranges
-      nr = it.n_ranges;
     }
-    if (listed) {  // ranges the item overlaps -> LDS, then every token of the item -> row code
-      const DevRange* lr = lds.ranges;
-      if (!p.dev_tables) {
-        const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
-        for (int r = tid; r < nr; r += kAttnThreads) lds.ranges[r] = ranges[range0 + r];
-        __syncthreads();
-      } else {
-        lr = lds.ranges + range0;
-      }
+    if (!KEPT && listed) {  // ranges the item overlaps -> LDS, then every token of the item -> row code
+      const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
+      for (int r = tid; r < nr; r += kAttnThreads) lds.ranges[r] = ranges[it.range_first + r];
+      __syncthreads();
       for (int j = tid; j < n_tok; j += kAttnThreads) {
         const int tok = it.tok_begin + j;
         int lo = 0, hi = nr - 1;  // last range with cum <= tok
         while (lo < hi) {
           const int mid = (lo + hi + 1) >> 1;
-          if (lr[mid].cum <= tok) lo = mid; else hi = mid - 1;
+          if (lds.ranges[mid].cum <= tok) lo = mid; else hi = mid - 1;
         }
-        const DevRange rg = lr[lo];
+        const DevRange rg = lds.ranges[lo];
         const int slot = rg.start + (tok - rg.cum) * rg.stride;
         const int phys = phys_row(p.lay, p.page_table, req, slot);
         lds.rows[j] = slot >= pend0 ? -1 - (pend_src0 + (slot - pend0)) : phys;  // deferred rows: -(1 + row)
@@ -827,7 +799,7 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
   PASTA_CLK(7);
 }
 
-template <bool PAGED, bool PROBE>
+template <bool PAGED, bool PROBE, bool KEPT>
 __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi);
 
 // One launch for all partials of a decode step; the shared-prefix items' work-groups come
@@ -837,8 +809,10 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
 // steady-state loop addresses plain blocks through buffer loads.  PROBE = the read-only form of the
 // same launch (every request of the real one, no arithmetic, no output): what a plain read of these
 // bytes costs with this split of the work.  WIDE = every request with a shared prefix has more than
-// 32 stacked rows: the shared-prefix work-groups take four row groups each (attn_item_wide).
-template <bool PAGED, bool DENSE, bool LONG = false, bool PROBE = false, bool WIDE = false>
+// 32 stacked rows: the shared-prefix work-groups take four row groups each (attn_item_wide).  KEPT = the plan is
+// on the device, items resolved (k_plan); an instantiation of its own, because carrying both ways to an item made
+// the launch whose plan rides in the kernel arguments slower (8 streams over 8k tokens: +0.3 us).
+template <bool KEPT, bool PAGED, bool DENSE, bool LONG = false, bool PROBE = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
   static_assert(!LONG || !DENSE, "the long-item variant exists for the list mode");
   static_assert(!WIDE || (!DENSE && !LONG), "the wide form replaces the shared-prefix items of the list mode");
@@ -886,9 +860,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
   // first where a SIMD holds a wave of each kind, paid while the private items' compute was heavier;
   // with the present kernel it costs 0.25 us per launch and is gone)
   if ((int)blockIdx.x < n_prefix_wgs) {
-    if constexpr (WIDE) attn_item_wide<PAGED, PROBE>(p, lds, meta, blockIdx.x);
-    else attn_item<PAGED, false, DENSE, LONG, PROBE>(p, lds, meta, blockIdx.x);
-  } else attn_item<PAGED, true, DENSE, LONG, PROBE, WIDE ? 1 : 0>(p, lds, meta, blockIdx.x - n_prefix_wgs);
+    if constexpr (WIDE) attn_item_wide<PAGED, PROBE, KEPT>(p, lds, meta, blockIdx.x);
+    else attn_item<PAGED, false, DENSE, LONG, PROBE, KEPT, 0>(p, lds, meta, blockIdx.x);
+  } else attn_item<PAGED, true, DENSE, LONG, PROBE, KEPT, WIDE ? 1 : 0>(p, lds, meta, blockIdx.x - n_prefix_wgs);
   if (pend_u >= 0) pend_store(pend_u, pend_val);
 }
 
@@ -902,7 +876,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
 // traffic is what that form is bound by), and there is nothing to combine at the end: each wave
 // owns its rows' (m, l, O) for the whole chunk.  Q stays in registers (the B operands of S^T = K Q^T,
 // fetched once per item).
-template <bool PAGED, bool PROBE>
+template <bool PAGED, bool PROBE, bool KEPT>
 __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi) {
   constexpr int D = 128;
   const int tid = threadIdx.x;

@@ -27,8 +27,8 @@
 // One block per wave in registers: a second one spilled (fp32 rows with 32 stacked queries need 256 registers
 // without it), and chunks are short enough here that most waves have only one.
 #pragma once
+#include "k_plan.hpp"
 #include "k_rope.hpp"
-#include "mfma_util.hpp"
 
 namespace pasta {
 
@@ -59,7 +59,6 @@ template <int D, int RT, int NW> struct DirLds {
   float mw[NW][16 * RT], lw[NW][16 * RT];
   uint32_t off[kDirWin];
   DevRange ranges[kGatherMax];
-  int sel[2];
 };
 
 // Turns the planes of a row whose pieces 4 kk + q are spread over the quarters' lanes: piece kk and piece
@@ -442,32 +441,22 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
   const int wi = (int)blockIdx.x - n_prefix_wgs;
   const int item = wi / p.Hkv;
   it.g = __builtin_amdgcn_readfirstlane(wi % p.Hkv);
-  DevItem di;
-  int nr = 0, range0 = 0;
-  bool in_ranges = false;
-  DevStream st{};
-  if (!p.dev_tables) {
-    di = reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
-    nr = di.n_ranges > 1 ? di.n_ranges : 0;
-    range0 = di.range_first;
-  } else {
-    const int si = dev_stream_of_item(p, meta, item);
-    st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[si];
-    di = dev_item(p, st, si, item, in_ranges);
-    if (in_ranges) range0 = dev_item_candidates(p, st, di.tok_begin, di.tok_count, kGatherMax, nr);
-  }
-  int req, pend0, pend_src0;
-  if (p.single_req) {
+  const bool kept = p.codes != nullptr;  // a plan kept on the device: its tokens' rows are written out
+  const DevItem di = kept ? p.items[item] : reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
+  const int32_t* codes = p.codes + (long long)item * p.priv_chunk;
+  int nr = !kept && di.n_ranges > 1 ? di.n_ranges : 0;
+  int req = 0, pend0 = INT32_MAX, pend_src0 = 0;
+  if (kept) {
+  } else if (p.single_req) {
     req = p.req0.req; pend0 = p.req0.pend0; pend_src0 = p.req0.pend_src0;
   } else {
-    const int qi = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream].req_idx;
-    const DevReq rq = reinterpret_cast<const DevReq*>(meta + p.off_reqs)[qi];
-    req = rq.req; pend0 = rq.pend0; pend_src0 = rq.pend_src0;
+    const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream];
+    req = st.req; pend0 = st.pend0; pend_src0 = st.pend_src0;
   }
   nr = __builtin_amdgcn_readfirstlane(nr);
-  if (nr > 0) {  // the ranges the piece overlaps (device-resident lists: candidates for it) -> LDS
+  if (nr > 0) {  // the ranges the piece overlaps -> LDS
     const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
-    for (int k = tid; k < nr; k += kAttnThreads) lds.ranges[k] = p.dev_tables ? dev_range_at(p, st, range0 + k) : ranges[range0 + k];
+    for (int k = tid; k < nr; k += kAttnThreads) lds.ranges[k] = ranges[di.range_first + k];
     __syncthreads();
   }
   it.n_tok = __builtin_amdgcn_readfirstlane(di.tok_count);
@@ -477,6 +466,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
   const bool report = p.dbg_rows && it.g == 0;
   auto code_of = [&](int j) -> uint32_t {
     int slot;
+    if (kept) {
+      const int row = codes[j];
+      if (report) p.dbg_rows[di.gather_pos + j] = phys_of_code(p, row);
+      if (row < 0) return kPendBit | (uint32_t)(((-1 - row) * p.Hkv + it.g) * (D * (int)sizeof(T) / 16));
+      return (uint32_t)((unsigned long long)(elem_off(p.lay, row, it.g) * (long long)sizeof(T)) >> 4);
+    }
     if (nr > 0) {  // the last range with cum <= tok
       const int tok = di.tok_begin + j;
       int lo = 0, hi = nr - 1;

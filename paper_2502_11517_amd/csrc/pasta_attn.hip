@@ -29,6 +29,7 @@ namespace {
 constexpr uint32_t kMagic = 0x50415354u;  // "PAST"
 constexpr int kRing = 8;                  // metadata staging buffers in flight
 constexpr int kRelayMaxWords = 2 * kRelayWords;  // largest plan that travels to the device inside kernel arguments
+constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes)
 constexpr int kNumCUs = 256;              // MI355X; planning default until the device has been asked
 constexpr int kTargetPrefixWgs = 768;     // most shared-prefix work-groups budgeted for
 
@@ -114,12 +115,19 @@ struct pasta_attn {
   PlanBuf pb;
   // device-resident lists: carve-up and bump allocation (entries)
   size_t off_arena = 0, off_cidx = 0;
+  // the plan kept on the device (k_plan): its words, its items and their tokens' rows; and what it was made of
+  size_t off_plan[2] = {}, off_plan_items[2] = {}, off_plan_codes[2] = {};  // [1]: of calls under stream capture
+  int64_t plan_items_cap = 0, plan_codes_cap = 0;
+  std::vector<int32_t> plan_words;       // the words it was made from (empty: none there)
+  uint64_t lists_epoch = 0;              // counts the changes of the maintained lists
   int64_t arena_cap = 0, cidx_cap = 0, arena_top = 0, cidx_top = 0;
   bool tables_reset = false;             // the segments ran out: start over at the next call (all streams dirty)
   bool lists_in_use = false;             // a decode step has read the device copy: appends keep it current from then on
                                          // (before that they only mark what changed, and may be deferred freely)
   std::vector<DevRange> stage_r;         // staging of one stream's lists for a rebuild
   std::vector<int32_t> stage_c;
+  std::vector<ListPiece> stage_pieces;   // ... and of all the lists that one call sends
+  std::vector<int32_t> stage_words;
   struct Undo { int64_t key; bool open; int32_t prefix_len; int32_t n_ranges; Range last; int64_t range_tokens;
                 int32_t dev_ranges, dev_cidx; bool dirty; bool replaced; std::vector<Range> saved; };
   std::vector<Undo> undo;                // append_kv: what to restore if a later row of the call fails
@@ -130,10 +138,10 @@ struct pasta_attn {
   // device-side readiness (deferred so that the host logic works without a GPU)
   bool device_ready = false;
   char* pinned = nullptr;                // kRing * meta_bytes
-  hipEvent_t ring_ev[kRing]{};
-  int ring_ev_made = 0;                  // events created so far (all kRing once the device is ready)
+  hipEvent_t ring_ev[2]{};               // one per half of the ring
+  int ring_ev_made = 0;                  // events created so far (both once the device is ready)
   int device = 0, n_cus = kNumCUs;       // the device current at first use and its compute-unit count
-  bool ring_used[kRing]{};
+  bool ring_used[2]{};
   int ring_next = 0, relay_next = 0;
 };
 
@@ -214,6 +222,20 @@ void carve(pasta_attn* h) {
     h->off_cidx = off;
     off += align_up((size_t)h->cidx_cap * 4, 256);
   }
+  {  // the plan kept on the device; a plan with more private tokens is derived by the attention launch itself
+    const int64_t ns = (int64_t)c.max_requests * c.max_streams;
+    const int64_t cap_tokens = c.page_tokens ? (int64_t)c.pages_per_request * c.page_tokens : c.pool_tokens;
+    h->plan_codes_cap = std::min<int64_t>(ns * (cap_tokens + 2 * kGatherMax), kPlanCodesMax);
+    h->plan_items_cap = h->plan_codes_cap / kPrivChunk;
+    for (int at = 0; at < 2; ++at) {
+      h->off_plan[at] = off;
+      off += h->meta_bytes;
+      h->off_plan_items[at] = off;
+      off += align_up((size_t)h->plan_items_cap * sizeof(DevItem), 256);
+      h->off_plan_codes[at] = off;
+      off += align_up((size_t)h->plan_codes_cap * 4, 256);
+    }
+  }
   if (c.rope_theta > 0.f) {
     h->off_rope = off;
     off += align_up((size_t)(c.head_dim / 2) * sizeof(double), 256);
@@ -233,7 +255,7 @@ int ensure_device(pasta_attn* h) {
     h->pinned = nullptr;
     return PASTA_E_DEVICE;
   }
-  for (; h->ring_ev_made < kRing; ++h->ring_ev_made)
+  for (; h->ring_ev_made < 2; ++h->ring_ev_made)
     if (hipEventCreateWithFlags(&h->ring_ev[h->ring_ev_made], hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
       return PASTA_E_DEVICE;
@@ -267,46 +289,78 @@ int ensure_device(pasta_attn* h) {
   return PASTA_OK;
 }
 
+// The pinned staging slots go round; one is written again only after the work that reads it has completed.
+// That is recorded once per half of the ring, behind its last slot: an event is a packet on the stream.
+int ring_take(pasta_attn* h, int* slot, char** host) {
+  const int s = h->ring_next, half = s / (kRing / 2);
+  if (s % (kRing / 2) == 0 && h->ring_used[half] && hipEventSynchronize(h->ring_ev[half]) != hipSuccess) return PASTA_E_DEVICE;
+  h->ring_next = (s + 1) % kRing;
+  *slot = s;
+  *host = h->pinned + (size_t)s * h->meta_bytes;
+  return PASTA_OK;
+}
+int ring_give(pasta_attn* h, int slot) {  // the work that reads the slot has been enqueued
+  const int half = slot / (kRing / 2);
+  if (slot % (kRing / 2) != kRing / 2 - 1) return PASTA_OK;
+  if (hipEventRecord(h->ring_ev[half], (hipStream_t)h->cfg.hip_stream) != hipSuccess) return PASTA_E_DEVICE;
+  h->ring_used[half] = true;
+  return PASTA_OK;
+}
+
 // Copies `bytes` of host metadata to the next device staging slot, asynchronously on the
 // caller's stream; returns the device address.  A slot is reused only after the copy that
 // last read its pinned half has completed.
 int upload_meta(pasta_attn* h, const void* src, size_t bytes, const int32_t** dev_out) {
   if (bytes > h->meta_bytes) return PASTA_E_CAPACITY;
-  const int s = h->ring_next;
-  h->ring_next = (s + 1) % kRing;
-  if (h->ring_used[s] && hipEventSynchronize(h->ring_ev[s]) != hipSuccess) return PASTA_E_DEVICE;
-  char* host = h->pinned + (size_t)s * h->meta_bytes;
+  int s;
+  char* host;
+  const int rc = ring_take(h, &s, &host);
+  if (rc != PASTA_OK) return rc;
   std::memcpy(host, src, bytes);
   char* dev = (char*)h->cfg.workspace + h->off_meta + (size_t)s * h->meta_bytes;
   hipStream_t st = (hipStream_t)h->cfg.hip_stream;
   if (hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st) != hipSuccess) return PASTA_E_DEVICE;
-  if (hipEventRecord(h->ring_ev[s], st) != hipSuccess) return PASTA_E_DEVICE;
-  h->ring_used[s] = true;
   *dev_out = (const int32_t*)dev;
-  return PASTA_OK;
+  return ring_give(h, s);
 }
 
-// Copies host data to a device address in the workspace, asynchronously on the caller's stream, through
-// the pinned ring (in pieces of one staging slot).
-int upload_to(pasta_attn* h, void* dev_dst, const void* src, size_t bytes) {
+// Sends the staged pieces of lists to their places in the workspace: one pinned slot, one launch.
+int flush_lists(pasta_attn* h) {
+  std::vector<ListPiece>& ps = h->stage_pieces;
+  std::vector<int32_t>& words = h->stage_words;
+  if (ps.empty()) return PASTA_OK;
   hipStream_t st = (hipStream_t)h->cfg.hip_stream;
-  for (size_t lo = 0; lo < bytes; lo += h->meta_bytes) {
-    const size_t n = std::min(h->meta_bytes, bytes - lo);
-    const int sl = h->ring_next;
-    h->ring_next = (sl + 1) % kRing;
-    if (h->ring_used[sl] && hipEventSynchronize(h->ring_ev[sl]) != hipSuccess) return PASTA_E_DEVICE;
-    char* host = h->pinned + (size_t)sl * h->meta_bytes;
-    std::memcpy(host, (const char*)src + lo, n);
-    if (hipMemcpyAsync((char*)dev_dst + lo, host, n, hipMemcpyHostToDevice, st) != hipSuccess) return PASTA_E_DEVICE;
-    if (hipEventRecord(h->ring_ev[sl], st) != hipSuccess) return PASTA_E_DEVICE;
-    h->ring_used[sl] = true;
+  int sl;
+  char* host;
+  const int rc = ring_take(h, &sl, &host);
+  if (rc != PASTA_OK) return rc;
+  std::memcpy(host, ps.data(), ps.size() * sizeof(ListPiece));
+  std::memcpy(host + ps.size() * sizeof(ListPiece), words.data(), words.size() * 4);
+  k_lists<<<dim3((unsigned)ps.size()), 256, 0, st>>>((const ListPiece*)host, (const int32_t*)(host + ps.size() * sizeof(ListPiece)), (int32_t*)h->cfg.workspace);
+  if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
+  ps.clear();
+  words.clear();
+  return ring_give(h, sl);
+}
+
+// Stages n words for place `off` (bytes, a multiple of 4) of the workspace, in pieces of a few KB each.
+int stage_list(pasta_attn* h, size_t off, const int32_t* src, size_t n) {
+  const size_t piece = std::min<size_t>(2048, h->meta_bytes / 4 - sizeof(ListPiece) / 4);
+  for (size_t lo = 0; lo < n; lo += piece) {
+    const size_t k = std::min(piece, n - lo);
+    if ((h->stage_pieces.size() + 1) * sizeof(ListPiece) + (h->stage_words.size() + k) * 4 > h->meta_bytes) {
+      const int rc = flush_lists(h);
+      if (rc != PASTA_OK) return rc;
+    }
+    h->stage_pieces.push_back(ListPiece{(long long)(off / 4 + lo), (int32_t)h->stage_words.size(), (int32_t)k});
+    h->stage_words.insert(h->stage_words.end(), src + lo, src + lo + k);
   }
   return PASTA_OK;
 }
 
 constexpr int kNoRoom = 1;  // rebuild_tables: the segments ran out (not an error: the call plans from the host lists)
 
-// Rebuilds the device copy of one stream's range list and range index from the mirror.
+// Rebuilds the device copy of one stream's range list and range index from the mirror; flush_lists sends it.
 int rebuild_tables(pasta_attn* h, StreamState& st) {
   const int64_t n = (int64_t)st.ranges.size();
   const int64_t n_c = (st.range_tokens + kCidxTokens - 1) / kCidxTokens;
@@ -336,8 +390,8 @@ int rebuild_tables(pasta_attn* h, StreamState& st) {
     cum += g.count;
   }
   int rc = PASTA_OK;
-  if (n) rc = upload_to(h, (char*)h->cfg.workspace + h->off_arena + (size_t)st.seg_off * sizeof(DevRange), sr.data(), (size_t)n * sizeof(DevRange));
-  if (rc == PASTA_OK && n_c) rc = upload_to(h, (char*)h->cfg.workspace + h->off_cidx + (size_t)st.cseg_off * 4, sc.data(), (size_t)n_c * 4);
+  if (n) rc = stage_list(h, h->off_arena + (size_t)st.seg_off * sizeof(DevRange), (const int32_t*)sr.data(), (size_t)n * (sizeof(DevRange) / 4));
+  if (rc == PASTA_OK && n_c) rc = stage_list(h, h->off_cidx + (size_t)st.cseg_off * 4, sc.data(), (size_t)n_c);
   if (rc != PASTA_OK) return rc;
   st.dev_ranges = (int32_t)n;
   st.dev_cidx = (int32_t)n_c;
@@ -599,7 +653,8 @@ extern "C" int32_t pasta_attn_create(pasta_attn_config* cfg, pasta_attn** out) {
     pb.req_idx_of.reserve(cfg->max_requests); pb.reqs.reserve(cfg->max_requests);
     pb.ranges.reserve(std::min<size_t>((size_t)cfg->max_ranges + nsc, kInlineMetaWords));
     pb.items.reserve(kInlineMetaWords / (sizeof(DevItem) / 4));
-    pb.blob.reserve(kInlineMetaWords + 16);
+    pb.blob.reserve(kInlineMetaWords + 16 + (size_t)kInlineMetaWords);  // (and an entry per private item: device-resident lists)
+    h->plan_words.reserve(2 * kInlineMetaWords + 16);
   } catch (...) { return fail(PASTA_E_NOMEM); }
 #if defined(PASTA_TUNING) && PASTA_TUNING >= 2
   std::fprintf(stderr, "PASTA_CLOCKS byte offset in workspace: %zu\n", h->off_ml + (size_t)(h->part_rows_cap - 16 * PASTA_CLK_WGS) * 8);
@@ -835,6 +890,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       for (int32_t i = rs[k].row0, end = k + 1 < rs.size() ? rs[k + 1].row0 : a->n_rows; i < end; ++i) a->out_slot[i] = rs[k].slot0 + (i - rs[k].row0);
   }
   if (commit) {
+    h->lists_epoch++;
     h->tail_before = h->tail;
     h->tail.swap(t2);
     undo.clear();
@@ -861,6 +917,7 @@ extern "C" int32_t pasta_attn_sync(pasta_attn* h, const pasta_sync_args* a) {
       if (a->join_stream[k] == j) return PASTA_E_INVAL;
     if (!sstate(h, a->request_id, j).open) return PASTA_E_STATE;
   }
+  h->lists_epoch++;
   try {
     if (a->stream_id >= 0) {
       StreamState& dst = sstate(h, a->request_id, a->stream_id);
@@ -1191,13 +1248,16 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // kernels no dependent loads -- unless the caller asks for the device lists.
     bool dev_lists = false;
     if (!explicit_mode && !a->causal_skip && !dense) {
+      int64_t dev_items = 0;
       int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (sizeof(DevReq) / 4) + 8;
       for (int i = 0; i < n; ++i) {
         const StreamState& ss = sstate(h, a->request_id[i], a->stream_id[i]);
         const int64_t priv = (int64_t)lv[i].prefix_len - reqs[stream_req_idx[i]].pc + ss.range_tokens;
         words += ((int64_t)lv[i].n_ranges + 1) * 4 + (priv + priv_chunk - 1) / priv_chunk * (sizeof(DevItem) / 4);
+        dev_items += (priv + priv_chunk - 1) / priv_chunk + 1;
       }
       dev_lists = (a->flags & PASTA_DECODE_DEVICE_LISTS) || words > kInlineMetaWords;
+      if (dev_items > h->plan_items_cap || dev_items * priv_chunk > h->plan_codes_cap) dev_lists = false;  // (k_plan has no room)
     } else if (a->flags & PASTA_DECODE_DEVICE_LISTS) {
       return PASTA_E_INVAL;
     }
@@ -1215,9 +1275,11 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         if (rb == kNoRoom) dev_lists = false;
         else if (rb != PASTA_OK) return rb;
       }
-      if (!dev_lists && (a->flags & PASTA_DECODE_DEVICE_LISTS)) return PASTA_E_CAPACITY;
+      const int fl = flush_lists(h);
+      if (fl != PASTA_OK) return fl;
       if (dev_lists) h->lists_in_use = true;
     }
+    if (!dev_lists && (a->flags & PASTA_DECODE_DEVICE_LISTS)) return PASTA_E_CAPACITY;
     // private items
     std::vector<DevStream>& streams = pb.streams;
     std::vector<DevRange>& ranges = pb.ranges;
@@ -1239,6 +1301,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       ds.pos = rope_q ? a->position[i] : 0;
       ds.mask_base = mask_base[i];
       ds.pc = q.pc;
+      ds.pend0 = INT32_MAX;
       if (dev_lists) {
         const StreamState& ss = sstate(h, a->request_id[i], a->stream_id[i]);
         const int64_t extra = (int64_t)lv[i].prefix_len - q.pc, T = ss.range_tokens;
@@ -1261,7 +1324,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         gather_total += (int64_t)q.pc + extra + T;
         continue;
       }
-      ds.range_begin = (int32_t)ranges.size();
+      const int32_t range_begin = (int32_t)ranges.size();
       int32_t cum = 0;
       if (lv[i].prefix_len > q.pc) {
         ranges.push_back({q.pc, lv[i].prefix_len - q.pc, 1, 0});
@@ -1272,18 +1335,18 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         ranges.push_back({g.start, g.count, g.stride, cum});
         cum += g.count;
       }
-      ds.range_end = (int32_t)ranges.size();
+      const int32_t range_end = (int32_t)ranges.size();
       ds.item_begin = (int32_t)items.size();
-      int32_t rcur = ds.range_begin;
+      int32_t rcur = range_begin;
       for (int32_t t = 0; t < cum; t += (int32_t)priv_chunk) {
-        while (rcur + 1 < ds.range_end && ranges[rcur + 1].cum <= t) rcur++;
+        while (rcur + 1 < range_end && ranges[rcur + 1].cum <= t) rcur++;
         DevItem it{};
         it.stream = i;
         it.tok_begin = t;
         it.tok_count = std::min<int32_t>((int32_t)priv_chunk, cum - t);
         it.range_first = rcur;
         int32_t rlast = rcur;
-        while (rlast + 1 < ds.range_end && ranges[rlast + 1].cum < t + it.tok_count) rlast++;
+        while (rlast + 1 < range_end && ranges[rlast + 1].cum < t + it.tok_count) rlast++;
         it.n_ranges = rlast - rcur + 1;
         it.gather_pos = (int32_t)(gather_total + q.pc + t);
         it.slot0 = ranges[rcur].start + (t - ranges[rcur].cum) * ranges[rcur].stride;
@@ -1352,6 +1415,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     p.off_ranges = put(ranges.data(), ranges.size() * sizeof(DevRange));
     p.off_items = put(items.data(), items.size() * sizeof(DevItem));
     if (blob.size() * 4 > h->meta_bytes) return PASTA_E_CAPACITY;
+    const size_t plan_size = blob.size();  // the words the attention and merge launches read
 
     if (a->dbg_plan) {
       int64_t tiles = 0;
@@ -1388,8 +1452,10 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         p.pend_rope = 1;
         std::memcpy(p.pend_pos, pd.pos, sizeof(p.pend_pos));
       }
-      // the blob was built before these fields were known: patch the table in place
+      for (auto& ds : streams) { ds.pend0 = pd.req_pend0[ds.req]; ds.pend_src0 = pd.req_src0[ds.req]; }
+      // the blob was built before these fields were known: patch the tables in place
       std::memcpy(blob.data() + p.off_reqs, reqs.data(), reqs.size() * sizeof(DevReq));
+      std::memcpy(blob.data() + p.off_streams, streams.data(), streams.size() * sizeof(DevStream));
     }
     if (dense) {  // the masks travel like the paper's mask tensors: host -> device, every step
       if (!h->mask_pinned) {
@@ -1408,37 +1474,94 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       h->mask_ev_used = true;
       p.dense_mask = dev_mask;
     }
-    if (blob.size() <= (size_t)kInlineMetaWords) {  // small plan: rides in the kernel arguments
+    p.page_table = (const int32_t*)((const char*)c.workspace + h->off_page_table);
+    p.lay = h->lay;
+    p.n_streams = n;
+    p.n_items = (int)n_items_total;
+    p.priv_chunk = (int)priv_chunk;
+    if (!dev_lists && blob.size() <= (size_t)kInlineMetaWords) {  // small plan: rides in the kernel arguments
       p.meta = nullptr;
       std::memcpy(p.inline_meta, blob.data(), blob.size() * 4);
     } else {
-      // large plan: it stays in pinned host memory and the kernels read it in place -- each
-      // work-group touches a few dozen bytes of it, and a copy-engine transfer ahead of the
-      // attention launch costs tens of microseconds on the stream (config 4: 97 -> 61 us per
-      // step).  The slot is reused only after the launches that read it have completed.
-      if (blob.size() * 4 > h->meta_bytes) return PASTA_E_CAPACITY;
-      if (blob.size() <= (size_t)kRelayMaxWords) {
-        // ... unless it is only a few KB (device-resident lists: one record per stream): then it travels to a
-        // device staging slot inside the kernel arguments of one or two tiny launches
-        const int sl = h->relay_next;
-        h->relay_next = (sl + 1) % kRing;
-        int32_t* dev = (int32_t*)((char*)c.workspace + h->off_meta + (size_t)sl * h->meta_bytes);
-        for (size_t lo = 0; lo < blob.size(); lo += kRelayWords) {
-          RelayParams rp;
-          rp.dst = dev + lo;
-          rp.n_words = (int)std::min<size_t>(kRelayWords, blob.size() - lo);
-          std::memcpy(rp.words, blob.data() + lo, (size_t)rp.n_words * 4);
-          k_meta_relay<<<dim3(1), 256, 0, st>>>(rp);
-        }
-        p.meta = dev;
-      } else {
-        meta_slot = h->ring_next;
-        h->ring_next = (meta_slot + 1) % kRing;
-        if (h->ring_used[meta_slot] && hipEventSynchronize(h->ring_ev[meta_slot]) != hipSuccess) return PASTA_E_DEVICE;
-        char* host = h->pinned + (size_t)meta_slot * h->meta_bytes;
-        std::memcpy(host, blob.data(), blob.size() * 4);
-        p.meta = (const int32_t*)host;
+      // A larger plan is put on the device once and used by every call that makes the same one -- all layers of
+      // a token step do (k_plan).  "The same" is decided by its words; for device-resident lists, whose ranges
+      // are not among them, the words end with the count of changes the lists have seen.  A captured call
+      // writes a place of its own every time it is replayed: what it leaves says nothing about later calls.
+      const bool keep = n_items_total <= h->plan_items_cap && n_items_total * priv_chunk <= h->plan_codes_cap;
+      if (dev_lists) {
+        if (!room(blob, blob.size() + (size_t)n_items_total + 4)) return PASTA_E_CAPACITY;
+        for (int i = 0; i < n; ++i) blob.insert(blob.end(), (size_t)(streams[i].item_end - streams[i].item_begin), i);
+        p.off_items = (int)plan_size;
+        blob.push_back((int32_t)(h->lists_epoch & 0xffffffffu));
+        blob.push_back((int32_t)(h->lists_epoch >> 32));
       }
+      blob.push_back((int32_t)priv_chunk);
+      if (blob.size() * 4 > h->meta_bytes) return PASTA_E_CAPACITY;
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+      const bool capturing = cap != hipStreamCaptureStatusNone;
+      const int at = capturing ? 1 : 0;
+      int32_t* dev = (int32_t*)((char*)c.workspace + h->off_plan[at]);
+      DevItem* d_items = (DevItem*)((char*)c.workspace + h->off_plan_items[at]);
+      int32_t* d_codes = (int32_t*)((char*)c.workspace + h->off_plan_codes[at]);
+      if (!keep || capturing || blob != h->plan_words) {
+        if (keep && !capturing) h->plan_words.clear();  // (what is there is about to be overwritten)
+        PlanParams pp{};
+        if (keep && blob.size() <= (size_t)kPlanWords) {
+          std::memcpy(pp.words, blob.data(), blob.size() * 4);
+        } else if (capturing && blob.size() <= (size_t)kRelayMaxWords) {  // inside the kernel arguments of one or two tiny launches
+          const int sl = h->relay_next;
+          h->relay_next = (sl + 1) % kRing;
+          int32_t* staged = (int32_t*)((char*)c.workspace + h->off_meta + (size_t)sl * h->meta_bytes);
+          for (size_t lo = 0; lo < blob.size(); lo += kRelayWords) {
+            RelayParams rp;
+            rp.dst = staged + lo;
+            rp.n_words = (int)std::min<size_t>(kRelayWords, blob.size() - lo);
+            std::memcpy(rp.words, blob.data() + lo, (size_t)rp.n_words * 4);
+            k_meta_relay<<<dim3(1), 256, 0, st>>>(rp);
+          }
+          p.meta = pp.src = staged;
+        } else {  // through pinned memory; the slot is reused only after the launches that read it have completed
+          char* host = nullptr;
+          rc = ring_take(h, &meta_slot, &host);
+          if (rc != PASTA_OK) return rc;
+          std::memcpy(host, blob.data(), blob.size() * 4);
+          p.meta = pp.src = (const int32_t*)host;
+        }
+        if (keep) {
+          pp.dst = dev;
+          pp.items = d_items;
+          pp.codes = d_codes;
+          pp.page_table = p.page_table;
+          pp.arena = (const DevRange*)((const char*)c.workspace + h->off_arena);
+          pp.cidx = (const int32_t*)((const char*)c.workspace + h->off_cidx);
+          pp.lay = h->lay;
+          pp.n_words = (int)plan_size;
+          pp.n_items = (int)n_items_total;
+          pp.priv_chunk = (int)priv_chunk;
+          pp.dev_tables = dev_lists ? 1 : 0;
+          pp.off_streams = p.off_streams;
+          pp.off_ranges = p.off_ranges;
+          pp.off_items = p.off_items;
+          const size_t wgs = std::max<size_t>((size_t)n_items_total, (plan_size + 255) / 256);
+          k_plan<<<dim3((unsigned)wgs), 256, 0, st>>>(pp);
+          if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
+          if (meta_slot >= 0) {
+            rc = ring_give(h, meta_slot);
+            if (rc != PASTA_OK) return rc;
+            meta_slot = -1;
+          }
+          if (!capturing) {
+            if (!room(h->plan_words, blob.size())) return PASTA_E_CAPACITY;
+            h->plan_words.assign(blob.begin(), blob.end());
+          }
+        }
+      }
+      if (keep) {
+        p.meta = dev;
+        p.items = d_items;
+        p.codes = d_codes;
+      }  // (else: a plan of millions of private tokens is read where it lies)
     }
     p.k = (const char*)c.k_pool + (size_t)a->layer * h->layer_elems * h->elem;
     p.v = (const char*)c.v_pool + (size_t)a->layer * h->layer_elems * h->elem;
@@ -1446,18 +1569,10 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     p.out = a->out;
     p.lse = a->out_lse;
     p.dbg_rows = a->dbg_gather_rows;
-    p.page_table = (const int32_t*)((const char*)c.workspace + h->off_page_table);
     p.part_acc = part_acc;
     p.part_ml = part_ml;
-    p.lay = h->lay;
-    p.n_streams = n;
     p.n_reqs = (int)reqs.size();
-    p.n_items = (int)n_items_total;
     p.n_mfma_items = matrix ? (int)n_items_total : 0;
-    p.arena = (const DevRange*)((const char*)c.workspace + h->off_arena);
-    p.cidx = (const int32_t*)((const char*)c.workspace + h->off_cidx);
-    p.dev_tables = dev_lists ? 1 : 0;
-    p.priv_chunk = (int)priv_chunk;
     p.n_prefix_wgs = (int)n_prefix_wgs;
     p.priv_part_base = (int)prefix_rows;
     p.Hq = c.n_q_heads;
@@ -1516,25 +1631,27 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
           else { if (rope) launch(k_direct<uint16_t, 128, true>); else launch(k_direct<uint16_t, 128, false>); }
         }
       } else if (dense) {  // the variant that carries the dense-mask mode
-        if (h->lay.paged) launch(k_attn<true, true>);
-        else launch(k_attn<false, true>);
+        if (p.codes) { if (h->lay.paged) launch(k_attn<true, true, true>); else launch(k_attn<true, false, true>); }
+        else { if (h->lay.paged) launch(k_attn<false, true, true>); else launch(k_attn<false, false, true>); }
       } else {
         // prefix chunks of more than two 32-token blocks per wave: the variant whose loop has the
         // cheap addressing of plain blocks
         const bool long_items = n_prefix_wgs > 0 && chunk_tokens > 2 * 4 * 32;
-        if (probe && !wide) {
-          if (h->lay.paged) { if (long_items) launch(k_attn<true, false, true, true>); else launch(k_attn<true, false, false, true>); }
-          else { if (long_items) launch(k_attn<false, false, true, true>); else launch(k_attn<false, false, false, true>); }
-        } else if (!wide) {
-          if (h->lay.paged) { if (long_items) launch(k_attn<true, false, true>); else launch(k_attn<true, false>); }
-          else { if (long_items) launch(k_attn<false, false, true>); else launch(k_attn<false, false>); }
-        } else if (probe) {
-          if (h->lay.paged) launch(k_attn<true, false, false, true, true>);
-          else launch(k_attn<false, false, false, true, true>);
-        } else {
-          if (h->lay.paged) launch(k_attn<true, false, false, false, true>);
-          else launch(k_attn<false, false, false, false, true>);
-        }
+        auto by_form = [&](auto kept, auto paged, auto prb) {
+          if (wide) launch(k_attn<kept.value, paged.value, false, false, prb.value, true>);
+          else if (long_items) launch(k_attn<kept.value, paged.value, false, true, prb.value>);
+          else launch(k_attn<kept.value, paged.value, false, false, prb.value>);
+        };
+        auto by_probe = [&](auto kept, auto paged) {
+          if (probe) by_form(kept, paged, std::true_type{});
+          else by_form(kept, paged, std::false_type{});
+        };
+        auto by_pool = [&](auto kept) {
+          if (h->lay.paged) by_probe(kept, std::true_type{});
+          else by_probe(kept, std::false_type{});
+        };
+        if (p.codes) by_pool(std::true_type{});
+        else by_pool(std::false_type{});
       }
       if (take_pending) h->pending.active = false;
     } else if (n_items_total > 0) {
@@ -1551,8 +1668,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       if (rc != PASTA_OK) return rc;
     }
     if (meta_slot >= 0) {
-      if (hipEventRecord(h->ring_ev[meta_slot], st) != hipSuccess) return PASTA_E_DEVICE;
-      h->ring_used[meta_slot] = true;
+      rc = ring_give(h, meta_slot);
+      if (rc != PASTA_OK) return rc;
     }
     if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
     return PASTA_OK;

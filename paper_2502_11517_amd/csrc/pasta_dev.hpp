@@ -46,8 +46,8 @@ struct DevStream {      // one per decoding stream, call order
   int32_t req_idx;      // index into DevReq[]
   int32_t local;        // rank among the request's streams in this call: stacked-Q row block
   int32_t pc;           // tokens of the list handled by the shared-prefix kernel
-  int32_t range_begin;  // private list = ranges [range_begin, range_end)
-  int32_t range_end;
+  int32_t pend0;        // deferred append: the request's slots from here on are rows pend_src0 .. of it (INT32_MAX: none)
+  int32_t pend_src0;
   int32_t item_begin;   // private work items [item_begin, item_end)
   int32_t item_end;
   int32_t gather_base;  // first entry of this stream in dbg_gather_rows
@@ -57,8 +57,8 @@ struct DevStream {      // one per decoding stream, call order
   int32_t m_pre0;       // part_base + local * G: first shared-prefix partial row of the stream (kv head 0, chunk 0, head 0)
   int32_t m_n_pre;      // split-K chunks of the request's common prefix
   int32_t m_R;          // stacked rows of the request: shared-prefix part i of kv head g is row m_pre0 + (g * m_n_pre + i) * m_R + gi
-  // ---- device-resident lists (DecodeParams::dev_tables): the stream's ranges are not in the blob but in the
-  // arena that the appends keep up to date, and its private work items are derived by the kernels
+  // ---- device-resident lists: the stream's ranges are not in the blob but in the arena that the appends keep
+  // up to date, and its private work items are derived on the device (k_plan)
   int32_t extra;        // prefix_len - pc: visible head beyond the common prefix (private, contiguous slots pc ..)
   int32_t n_ranges;     // ranges of the list: k < n_ranges - 1 at arena[seg_off + k], the newest one in `last`
   int32_t seg_off;
@@ -105,7 +105,8 @@ struct DecodeParams {
   float* part_acc;      // [rows][D]
   float2* part_ml;      // [rows] (m in log2 units, l)
   Layout lay;
-  int off_streams, off_reqs, off_req_streams, off_ranges, off_items;
+  int off_streams, off_reqs, off_req_streams, off_ranges;
+  int off_items;
   int n_streams, n_reqs, n_items, n_prefix_wgs;
   int n_mfma_items;     // private items taken by the matrix-core kernel (all or none)
   int priv_part_base;   // private partial row = priv_part_base + ((item*Hkv + g)*G + i)
@@ -128,9 +129,8 @@ struct DecodeParams {
   int32_t s_items[32];  // single_req with <= 16 streams: stream i's private items are
                         //   [s_items[2i], s_items[2i] + s_items[2i+1]) -- spares the merge a table look-up
   const uint8_t* dense_mask;  // comparison mode: 0/1 per (stream, slot); null otherwise
-  const DevRange* arena;      // device-resident lists: range arena and range index (see DevStream)
-  const int32_t* cidx;
-  int dev_tables;             // 1: the blob holds no ranges and no items
+  const DevItem* items;       // a plan kept on the device (k_plan): the private work items and, priv_chunk entries per
+  const int32_t* codes;       // item, the row of every token (physical row, or -(1 + row) of a deferred append); else null
   int priv_chunk;             // tokens per private work item
   const double* rope_tab;  // theta^(-2f/D) / (2 pi), f < D/2 (device), for k_rope_prep
   int single_req;       // 1: the call holds one request; its DevReq is req0 and stream i of
@@ -185,30 +185,22 @@ __device__ __forceinline__ const int32_t* pend_pos_of(const DecodeParams& p) {
   return (const int32_t*)(ka + __builtin_offsetof(DecodeParams, pend_pos));
 }
 
-// ---- device-resident lists: the pieces the kernels share
-__device__ __forceinline__ DevRange dev_range_at(const DecodeParams& p, const DevStream& st, int k) {
+// ---- device-resident lists: what k_plan finds in them
+template <class P>
+__device__ __forceinline__ DevRange dev_range_at(const P& p, const DevStream& st, int k) {
   if (k >= st.n_ranges - 1) return DevRange{st.last[0], st.last[1], st.last[2], st.last[3]};
   return p.arena[st.seg_off + k];
 }
-__device__ __forceinline__ int dev_cidx_at(const DecodeParams& p, const DevStream& st, int j) {
+template <class P>
+__device__ __forceinline__ int dev_cidx_at(const P& p, const DevStream& st, int j) {
   return j < st.n_cidx ? p.cidx[st.cseg_off + j] : st.n_ranges - 1;
-}
-// The call's stream whose private items include work item `item` (item_begin is ascending over the
-// streams of a call; streams without items have item_begin == item_end).  Every lane searches.
-__device__ __forceinline__ int dev_stream_of_item(const DecodeParams& p, const int32_t* meta, int item) {
-  const DevStream* streams = reinterpret_cast<const DevStream*>(meta + p.off_streams);
-  int lo = 0, hi = p.n_streams - 1;  // last stream with item_begin <= item
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (streams[mid].item_begin <= item) lo = mid; else hi = mid - 1;
-  }
-  return lo;  // (a stream without items shares its item_begin with the NEXT stream, which the search prefers)
 }
 // Work item `item` of stream i, derived: first the pieces of the visible head beyond the common prefix
 // (contiguous slots), then the pieces of the range list, both in steps of priv_chunk tokens.  For a piece
 // of the range list only tok_begin / tok_count / gather_pos are filled in here (tok_begin in range tokens):
 // its ranges are looked up by the caller (dev_item_candidates).
-__device__ __forceinline__ DevItem dev_item(const DecodeParams& p, const DevStream& st, int i, int item, bool& in_ranges) {
+template <class P>
+__device__ __forceinline__ DevItem dev_item(const P& p, const DevStream& st, int i, int item, bool& in_ranges) {
   const int C = p.priv_chunk;
   const int ci = item - st.item_begin;
   const int n_extra = (st.extra + C - 1) / C;
@@ -235,7 +227,8 @@ __device__ __forceinline__ DevItem dev_item(const DecodeParams& p, const DevStre
 }
 // The ranges that can hold tokens [t0, t0 + n) of the stream's range list: all of them when they fit
 // `cap` entries, else the stretch that the range index points at.  Returns the first candidate's index.
-__device__ __forceinline__ int dev_item_candidates(const DecodeParams& p, const DevStream& st, int t0, int n, int cap, int& count) {
+template <class P>
+__device__ __forceinline__ int dev_item_candidates(const P& p, const DevStream& st, int t0, int n, int cap, int& count) {
   if (st.n_ranges <= cap) { count = st.n_ranges; return 0; }
   const int first = dev_cidx_at(p, st, t0 / kCidxTokens);
   const int j_hi = (t0 + n - 1) / kCidxTokens + 1;
