@@ -95,7 +95,8 @@ struct DirItem {
 
 // One item, once code_of(j) -- the address code of token j -- can be asked for.  GATHER: the rows are the G
 // heads of one stream; otherwise rows row0 .. of the request's stack.
-template <typename T, int D, int RT, int NW, bool GATHER, bool ROPE, class Lds, class CodeOf>
+// WHOLE: the item is all that its stream sees, and what is written is the result instead of a partial row.
+template <typename T, int D, int RT, int NW, bool GATHER, bool ROPE, bool WHOLE, class Lds, class CodeOf>
 __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, const int32_t* meta, const DirItem& it, CodeOf code_of) {
   typedef DirBlock<T, D> Blk;
   constexpr int kTok = Blk::kTok, kNT = Blk::kNT, kNP = Blk::kNP, kMT = D / 16;
@@ -327,9 +328,10 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   if constexpr (sizeof(T) == 2 && D == 128) { qq = pc >> 3; r = (pc >> 1) & 3; cg = pc & 1; }
   else { cg = pc >> 4; qq = (pc >> 2) & 3; r = pc & 3; }
 #pragma unroll
-  for (int pass = 0; pass < 16 * RT / kRows; ++pass) {
+  for (int pass = 0; pass < (16 * RT + kRows - 1) / kRows; ++pass) {
     if (pass * kRows >= R) break;
     const int rr = pass * kRows + tid / kPR;
+    if (kRows > 16 * RT && rr >= 16 * RT) break;
     const int slot = (((rr >> 4) * 4 + r) * (D / 64) + cg) * 65 + 16 * qq + (rr & 15);
     float mk[NW], ma = -INFINITY;
 #pragma unroll
@@ -347,7 +349,14 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         l = fmaf(lds.lw[k][rr], sc, l);
       }
     }
-    if (rr < R) {
+    if (rr >= R) continue;
+    if constexpr (WHOLE) {
+      const long long row = (long long)it.q_stream * p.Hq + g * G + rr;
+      const float o[4] = {acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l};
+      if constexpr (sizeof(T) == 4) reinterpret_cast<f32x4*>(p.out)[row * kPR + pc] = f32x4{o[0], o[1], o[2], o[3]};
+      else reinterpret_cast<u32x2*>(p.out)[row * kPR + pc] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+      if (p.lse && pc == 0) p.lse[row] = (ma + __log2f(l)) * kLn2;
+    } else {
       *reinterpret_cast<f32x4*>(p.part_acc + (it.part_row0 + rr) * D + 4 * pc) = acc;
       if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(ma, l);
     }
@@ -358,12 +367,12 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
 // that name them are served from k_pend / v_pend), spread thin over the work-groups' first 16 threads; fewer
 // work-groups than that take more each.  ROPE: K rows are turned on the way.
 template <typename T, int D, bool ROPE>
-__device__ __forceinline__ void direct_copy_pending(const DecodeParams& p) {
+__device__ __forceinline__ void direct_copy_pending(const DecodeParams& p, int wg, int n_wgs) {
   constexpr int kPieceRow = D * (int)sizeof(T) / 16;
   const int row_pieces = p.Hkv * kPieceRow, total = p.pend_n * row_pieces;
-  const bool thin = 2 * total <= (int)gridDim.x * 16;
-  const int step = thin ? 2 * total : (int)gridDim.x * (int)blockDim.x;
-  for (int t = thin ? (threadIdx.x < 16 ? (int)blockIdx.x * 16 + (int)threadIdx.x : 2 * total) : (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  const bool thin = 2 * total <= n_wgs * 16;
+  const int step = thin ? 2 * total : n_wgs * (int)blockDim.x;
+  for (int t = thin ? (threadIdx.x < 16 ? wg * 16 + (int)threadIdx.x : 2 * total) : wg * (int)blockDim.x + (int)threadIdx.x;
        t < 2 * total; t += step) {
     const bool is_v = t >= total;
     const int u = is_v ? t - total : t;
@@ -392,7 +401,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
   __shared__ DirLds<D, 2, 4> lds;
   const int32_t* meta = meta_of(p);
   const int tid = threadIdx.x;
-  if (p.pend_n > 0) direct_copy_pending<T, D, ROPE>(p);
+  if (p.pend_n > 0) direct_copy_pending<T, D, ROPE>(p, (int)blockIdx.x, (int)gridDim.x);
   const int n_prefix_wgs = (int)gridDim.x - p.n_mfma_items * p.Hkv;
   const int G = p.Hq / p.Hkv;
   DirItem it;
@@ -433,8 +442,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
           p.dbg_rows[streams[it.req_streams ? it.req_streams[k] : k].gather_base + slot0 + j] = phys;
       return code;
     };
-    if (it.R > 16) direct_rows<T, D, 2, 4, false, ROPE>(p, lds, meta, it, code_of);
-    else direct_rows<T, D, 1, 4, false, ROPE>(p, lds, meta, it, code_of);
+    if (it.R > 16) direct_rows<T, D, 2, 4, false, ROPE, false>(p, lds, meta, it, code_of);
+    else direct_rows<T, D, 1, 4, false, ROPE, false>(p, lds, meta, it, code_of);
     return;
   }
   // ---- a piece of one stream's private list
@@ -488,7 +497,57 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
     if (report) p.dbg_rows[di.gather_pos + j] = phys;
     return code;
   };
-  direct_rows<T, D, 1, 4, true, ROPE>(p, lds, meta, it, code_of);
+  direct_rows<T, D, 1, 4, true, ROPE, false>(p, lds, meta, it, code_of);
+}
+
+// A small step in ONE launch: a work-group takes everything that one stream sees of one kv head and writes the
+// result, so that neither partial rows nor a merge launch -- nor, with rotary embedding, the launch that turns Q and
+// the deferred rows ahead of k_attn -- stand on the step's path.  All dtypes and widths.
+// What bounds it: the rate at which one CU takes in the rows (eight waves with a block each in flight), which is why
+// it is for short lists only, and every stream reads the shared prefix by itself (from its XCD's L2: work-group mod
+// Hkv is the kv head).  The copy of a deferred append's rows has work-groups of its own behind the others.
+// Append and decode step, split form -> this one (us): bf16, 8 kv heads x 128, 128 + 3 x 20 .. 60 tokens 10.0 -> 6.3, with
+// rotary embedding 13.8 -> 11.9; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
+constexpr int kOneWaves = 8;
+template <typename T, int D, bool ROPE>
+__global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
+  __shared__ DirLds<D, 1, kOneWaves> lds;
+  const int tid = threadIdx.x;
+  const int n_rows_wgs = p.n_mfma_items * p.Hkv;  // (one item per stream)
+  if ((int)blockIdx.x >= n_rows_wgs) {
+    direct_copy_pending<T, D, ROPE>(p, (int)blockIdx.x - n_rows_wgs, (int)gridDim.x - n_rows_wgs);
+    return;
+  }
+  const int32_t* meta = meta_of(p);
+  const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x / p.Hkv);
+  const DevItem di = reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
+  const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream];
+  DirItem it;
+  it.req_streams = nullptr;
+  it.row0 = 0;
+  it.part_row0 = 0;
+  it.g = __builtin_amdgcn_readfirstlane((int)blockIdx.x % p.Hkv);
+  it.n_tok = __builtin_amdgcn_readfirstlane(di.tok_count);
+  it.R = p.Hq / p.Hkv;
+  it.q_stream = __builtin_amdgcn_readfirstlane(di.stream);
+  const int nr = __builtin_amdgcn_readfirstlane(di.n_ranges);
+  const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges) + di.range_first;
+  for (int k = tid; k < nr; k += kOneWaves * 64) lds.ranges[k] = ranges[k];
+  __syncthreads();
+  const bool report = p.dbg_rows && it.g == 0;
+  auto code_of = [&](int j) -> uint32_t {  // the last range with cum <= j
+    int lo = 0, hi = nr - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (lds.ranges[mid].cum <= j) lo = mid; else hi = mid - 1;
+    }
+    int phys;
+    const int slot = lds.ranges[lo].start + (j - lds.ranges[lo].cum) * lds.ranges[lo].stride;
+    const uint32_t code = direct_code<T, D>(p, st.req, slot, it.g, st.pend0, st.pend_src0, phys);
+    if (report) p.dbg_rows[di.gather_pos + j] = phys;
+    return code;
+  };
+  direct_rows<T, D, 1, kOneWaves, true, ROPE, true>(p, lds, meta, it, code_of);
 }
 
 }  // namespace pasta

@@ -30,6 +30,7 @@ constexpr uint32_t kMagic = 0x50415354u;  // "PAST"
 constexpr int kRing = 8;                  // metadata staging buffers in flight
 constexpr int kRelayMaxWords = 2 * kRelayWords;  // largest plan that travels to the device inside kernel arguments
 constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes)
+constexpr int kOneTokens = 1024;          // most tokens of a work-group of k_one (it holds their addresses at once)
 constexpr int kNumCUs = 256;              // MI355X; planning default until the device has been asked
 constexpr int kTargetPrefixWgs = 768;     // most shared-prefix work-groups budgeted for
 
@@ -1004,6 +1005,51 @@ constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 void* g_scratch_ptr[kMaxDevices] = {};
 
+// Steps that k_one takes: every stream sees few enough bytes of K and V per kv head that one CU reads them sooner than the
+// merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  The lines lie where both
+// sides measure the same, 16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream (us, split / one):
+//   bf16 x 128           1 stream: prefix 128 9.2 / 6.1, 300 8.2 / 7.6, 450 8.1 / 8.9;  8 streams: 450 12.2 / 9.6
+//   bf16 x 128, rotated  1 stream: 128 12.9 / 11.7, 300 12.7 / 13.0;  3 streams: 300 14.1 / 13.3, 450 14.0 / 14.9
+//   bf16 x 64            1 stream: 640 8.8 / 8.1, 900 8.9 / 9.4;  rotated 450 10.7 / 9.9, 640 10.8 / 11.0
+//   fp32 x 64            1 stream: 128 8.5 / 7.3, 300 8.6 / 9.5;  fp32 x 128: 32 9.0 / 7.0, 128 8.8 / 9.4
+// (fp32: 16-row tiles of four planes at a time, a quarter of them live: a work-group computes longer than it reads;
+// rotated: every work-group turns its Q rows itself).
+bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, size_t n_reqs) {
+  const pasta_attn_config& c = h->cfg;
+  const int n = a->n_streams;
+  // what asks for a certain form, its partials or its plan's pieces gets the split one
+  if ((a->flags & ~(uint32_t)(PASTA_DECODE_ROPE_Q)) || a->dbg_part_ml || a->dbg_plan) return false;
+  if (n * c.n_kv_heads > h->n_cus) return false;
+  const bool rope = (a->flags & PASTA_DECODE_ROPE_Q) || (h->pending.active && h->pending.rope);
+  int64_t most = c.dtype == PASTA_F32 ? (rope ? 96 : 112) : !rope || (n > 1 && c.head_dim == 128) ? 192 : 144;  // KiB
+  most = std::min<int64_t>(kOneTokens, (most << 10) / ((int64_t)c.head_dim * h->elem * 2));
+  int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)n_reqs * (sizeof(DevReq) / 4) + 16;  // of the split plan at least: it has to ride in the kernel arguments
+  for (int i = 0; i < n; ++i) {
+    const ListView& v = lv[i];
+    if (v.prefix_len > most || v.n_ranges >= kGatherMax) return false;
+    int64_t seen = v.prefix_len;
+    for (int k = 0; k < v.n_ranges; ++k) seen += v.at(k).count;
+    if (seen > most) return false;
+    words += ((int64_t)v.n_ranges + 1) * (sizeof(DevRange) / 4) + (seen + 127) / 128 * (sizeof(DevItem) / 4);
+  }
+  if (words > kInlineMetaWords) return false;
+  // results are written while other work-groups still read: only where they lie apart from what is read
+  // (Q itself excepted, whose rows a work-group has read before it writes the same rows), in whole pieces
+  const size_t out_bytes = (size_t)n * c.n_q_heads * c.head_dim * h->elem, lse_bytes = (size_t)n * c.n_q_heads * sizeof(float);
+  auto apart = [](const void* x, size_t nx, const void* y, size_t ny) {
+    return !x || !y || (uintptr_t)x + nx <= (uintptr_t)y || (uintptr_t)y + ny <= (uintptr_t)x;
+  };
+  if ((uintptr_t)a->out & 15) return false;
+  if (a->out != a->q && !apart(a->out, out_bytes, a->q, out_bytes)) return false;
+  if (!apart(a->out_lse, lse_bytes, a->q, out_bytes)) return false;
+  if (h->pending.active) {
+    const size_t pend_bytes = (size_t)h->pending.n_rows * c.n_kv_heads * c.head_dim * h->elem;
+    for (const void* src : {(const void*)h->pending.k_new, (const void*)h->pending.v_new})
+      if (!apart(a->out, out_bytes, src, pend_bytes) || !apart(a->out_lse, lse_bytes, src, pend_bytes)) return false;
+  }
+  return true;
+}
+
 // `no_alloc`: the partials go to the static scratch array instead of the workspace, and the call
 // must get by without any allocation, device or host (see pasta_attn_decode_step_noalloc).
 int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_alloc) {
@@ -1195,11 +1241,13 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // Everything else -- fp32, 64-wide heads, layers too large for 32-bit offsets -- goes through the kernel that
     // takes its operands straight from memory (its address codes count 16-byte pieces in 31 bits).  The vector-ALU
     // walker is left with NO_MFMA and what is larger still.
-    const bool direct = !mfma && !(a->flags & PASTA_DECODE_NO_MFMA) && h->layer_elems * h->elem < ((int64_t)1 << 35);
+    const bool fits_direct = !(a->flags & PASTA_DECODE_NO_MFMA) && h->layer_elems * h->elem < ((int64_t)1 << 35);
+    const bool one = fits_direct && small_step(h, a, lv, reqs.size());
+    const bool direct = fits_direct && (one || !mfma);
     const bool matrix = mfma || direct;
     int64_t pc_total = 0, pc_weighted = 0;  // the second counts a prefix once per work-group that reads it
     for (auto& q : reqs) {
-      if (!matrix || q.pc < kTile || no_share) q.pc = 0;
+      if (!matrix || q.pc < kTile || no_share || one) q.pc = 0;
       pc_total += q.pc;
     }
     // More than 32 stacked rows per request: the rows go in groups of 32.  When EVERY request with a
@@ -1239,7 +1287,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       chunk_tokens = std::max<int64_t>(kTile, pc_weighted * Hkv / h->n_cus / kTile * kTile);
       priv_chunk = wide ? 256 : 128;  // (beside the long wide work-groups the private items get one slot per CU: longer items keep more in flight there)
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
-      if (h->tune_priv_chunk >= 32) priv_chunk = std::min<int64_t>(h->tune_priv_chunk / 32 * 32, kGatherMax);  // whole 32-token blocks
+      if (one) priv_chunk = kOneTokens;  // a stream's whole list
+      else if (h->tune_priv_chunk >= 32) priv_chunk = std::min<int64_t>(h->tune_priv_chunk / 32 * 32, kGatherMax);  // whole 32-token blocks
     }
     // ---- where the lists come from.  Maintained lists have a copy on the device (range arena + range
     // index, kept up to date by the appends): a step may then send a fixed-size record per stream and let
@@ -1617,12 +1666,19 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     if (merge_only) {
       // (kernel-isolated test of the merge: the partial buffers are taken as they are)
     } else if (matrix) {
-      const unsigned grid = (unsigned)(n_items_total * Hkv + n_prefix_wgs);
-      auto launch = [&](auto kernel) {
-        if (ev_in_dispatch) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, st, ev0, ev1, 0, p);
-        else kernel<<<dim3(grid), kAttnThreads, 0, st>>>(p);
+      unsigned grid = (unsigned)(n_items_total * Hkv + n_prefix_wgs);
+      if (one) grid += (unsigned)((2ll * p.pend_n * Hkv * D * h->elem / 16 + kOneWaves * 64 - 1) / (kOneWaves * 64));  // the deferred rows' copy
+      auto launch = [&](auto kernel, int threads = kAttnThreads) {
+        if (ev_in_dispatch) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, ev0, ev1, 0, p);
+        else kernel<<<dim3(grid), threads, 0, st>>>(p);
       };
-      if (direct) {
+      if (one) {
+        auto by_rope = [&](auto turned) {
+          if (c.dtype == PASTA_F32) { if (D == 64) launch(k_one<float, 64, turned.value>, kOneWaves * 64); else launch(k_one<float, 128, turned.value>, kOneWaves * 64); }
+          else { if (D == 64) launch(k_one<uint16_t, 64, turned.value>, kOneWaves * 64); else launch(k_one<uint16_t, 128, turned.value>, kOneWaves * 64); }
+        };
+        if (rope) by_rope(std::true_type{}); else by_rope(std::false_type{});
+      } else if (direct) {
         if (c.dtype == PASTA_F32) {
           if (D == 64) { if (rope) launch(k_direct<float, 64, true>); else launch(k_direct<float, 64, false>); }
           else { if (rope) launch(k_direct<float, 128, true>); else launch(k_direct<float, 128, false>); }
@@ -1663,7 +1719,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     int64_t merge_parts = 0;  // every output row reads its request's prefix chunks and its stream's items
     for (int i = 0; i < n; ++i)
       merge_parts += (int64_t)(reqs[stream_req_idx[i]].n_chunks + streams[i].item_end - streams[i].item_begin) * c.n_q_heads;
-    if (!probe && !partials_only) {
+    if (!probe && !partials_only && !one) {
       rc = launch_merge(h, dim3((unsigned)Hkv, (unsigned)G, (unsigned)n), st, p, merge_parts);
       if (rc != PASTA_OK) return rc;
     }

@@ -1,0 +1,90 @@
+"""The one-launch form of small steps (k_one) against the fp64 oracle, around the edges of its rule and of its blocks: one
+token, blocks of 16 and 32 tokens less and plus one, a round of eight waves and the next, the longest lists that it takes
+and the first that it does not, rows of a deferred append, paged rows, rotary embedding, results in place of Q."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+from paper_2502_11517_amd import binding as B
+from paper_2502_11517_amd import workloads as W
+from test_gpu_parity import THETA, _check_pool, _check_rope_pool, _check_rope_step, _check_step, _out64, _session
+from util import OraclePool, check_close
+
+pytestmark = pytest.mark.gpu
+
+KINDS = [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)]
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("G,Hkv,prefix,lengths,layout", [
+    (1, 8, 1, [1], "head"), (2, 2, 14, [1, 2], "token"), (4, 1, 31, [16, 1, 33], "head"), (8, 1, 90, [30, 37, 5], "token"),
+    (4, 2, 120, [7] * 6, "head"), (8, 4, 64, [3] * 9, "token")])
+def test_edges_of_blocks_and_deferred_rows(dtype, D, G, Hkv, prefix, lengths, layout):
+    w = W.single_request("one", dtype, Hkv * G, Hkv, D, 1.0, 21, prefix, lengths, "random", steps=2, k_std=D ** -0.5)
+    head = layout == "head"
+    s, op = _session(w, kv_layout=B.HEAD_MAJOR if head else B.TOKEN_MAJOR), OraclePool(w, head_major=head)
+    s.append_events(w.n_prefill)
+    op.append_events(w.n_prefill)
+    keep = []
+    for step in range(2):
+        s.append_events(w.n_events(step), chunk=w.n, flags=B.APPEND_DEFER)
+        keep.append(s._keep_rows)
+        op.append_events(w.n_events(step))
+        _check_step(w, s, op, step, explicit=bool(step))
+    _check_pool(w, s, op)
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("short", [0, 1])
+def test_the_longest_lists_and_the_first_that_are_split(dtype, D, short):
+    """The rule's line, from both sides: a stream that sees exactly the most tokens, and one more."""
+    most = (192 << 10) // (4 * D) if dtype == "bf16" else (112 << 10) // (8 * D)
+    w = W.single_request("line", dtype, 8, 2, D, 1.0, 22, most - 9 - short, [5, 9], "round_robin", steps=2, k_std=D ** -0.5)
+    s, op = _session(w, kv_layout=B.HEAD_MAJOR), OraclePool(w, head_major=True)
+    s.append_events(w.n_prefill)
+    op.append_events(w.n_prefill)
+    for step in range(2):
+        s.append_events(w.n_events(step))
+        op.append_events(w.n_events(step))
+        _check_step(w, s, op, step)
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("page", [8, 32])
+def test_paged_requests_with_rotated_rows(dtype, D, page):
+    w = W.config4(n_requests=2, seed=91, pmin=10, pmax=60, page_tokens=page, hq=8, hkv=2)
+    w.dtype, w.D, w.k_std = dtype, D, D ** -0.5
+    pos = w.event_positions()
+    s, op = _session(w, rope_theta=THETA), OraclePool(w)
+    s.append_events(w.n_prefill - 3, flags=B.APPEND_ROPE, positions=pos)
+    s.append_events(w.n_prefill, flags=B.APPEND_ROPE | B.APPEND_DEFER, positions=pos)
+    op.append_events(w.n_prefill, positions=pos, theta=THETA)
+    _check_rope_step(w, s, op, 0, pos)
+    _check_rope_pool(w, s, op, w.n_prefill)
+    s.close()
+
+
+@pytest.mark.parametrize("shift", ["in place of q", "over part of q", "two elements off"])
+def test_results_that_lie_over_the_queries(shift):
+    """`out` on top of `q`, half over it, or not on a 16-byte boundary gives what separate buffers give (the last two in
+    the split form, which has read Q before anything is written)."""
+    w = W.single_request("alias", "bf16", 8, 2, 128, 1.0, 23, 100, [20, 33, 7], "random", k_std=128 ** -0.5)
+    s = _session(w)
+    s.append_events(w.n_prefill)
+    size = w.n * w.Hq * w.D
+    buf = torch.randn(2 * size, device=s.device, generator=torch.Generator(device=s.device).manual_seed(3)).to(torch.bfloat16)
+    q, ref = buf[:size].view(w.n, w.Hq, w.D), torch.empty(w.n, w.Hq, w.D, dtype=torch.bfloat16, device=s.device)
+    s.h.decode_step(0, w.dec_request, w.dec_stream, q, ref)
+    at = {"in place of q": 0, "over part of q": size // 2, "two elements off": size + 2}[shift]
+    n = min(size, 2 * size - at)
+    assert n == size or shift == "two elements off"
+    if n < size:
+        buf = torch.cat([buf, buf])
+        q = buf[:size].view(w.n, w.Hq, w.D)
+    out = buf[at:at + size].view(w.n, w.Hq, w.D)
+    s.h.decode_step(0, w.dec_request, w.dec_stream, q, out)
+    check_close(_out64(w, out), _out64(w, ref), w.dtype, shift)
+    s.close()
