@@ -59,6 +59,7 @@ template <int D, int RT, int NW> struct DirLds {
   float mw[NW][16 * RT], lw[NW][16 * RT];
   uint32_t off[kDirWin];
   DevRange ranges[kGatherMax];
+  float2 turn[D / 2];  // (k_one) the angles of the stream's new token
 };
 
 // Turns the planes of a row whose pieces 4 kk + q are spread over the quarters' lanes: piece kk and piece
@@ -81,6 +82,30 @@ __device__ __forceinline__ void rope_lane(u32x4 (&x)[NP], int q, int pos, const 
     }
     x[kk] = u32x4{lo[0], lo[1], lo[2], lo[3]};
     x[kk + NP / 2] = u32x4{hi[0], hi[1], hi[2], hi[3]};
+  }
+}
+
+// The same by angles already worked out: plane f turns by (cos, sin) = cs[f].
+template <typename T, int NP>
+__device__ __forceinline__ void rope_lane_by(u32x4 (&x)[NP], int q, const float2* cs) {
+#pragma unroll
+  for (int kk = 0; kk < NP / 2; ++kk) {
+    const int f0 = (4 * kk + q) * (16 / (int)sizeof(T));
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t a = x[kk][w], b = x[kk + NP / 2][w];
+      if constexpr (sizeof(T) == 4) {
+        const float2 t = cs[f0 + w];
+        const float u = __uint_as_float(a), v = __uint_as_float(b);
+        x[kk][w] = __float_as_uint(u * t.x - v * t.y);
+        x[kk + NP / 2][w] = __float_as_uint(v * t.x + u * t.y);
+      } else {
+        const float2 t0 = cs[f0 + 2 * w], t1 = cs[f0 + 2 * w + 1];
+        const float u0 = bf16_lo(a), u1 = bf16_hi(a), v0 = bf16_lo(b), v1 = bf16_hi(b);
+        x[kk][w] = (uint32_t)f32_to_bf16_rne(u0 * t0.x - v0 * t0.y) | ((uint32_t)f32_to_bf16_rne(u1 * t1.x - v1 * t1.y) << 16);
+        x[kk + NP / 2][w] = (uint32_t)f32_to_bf16_rne(v0 * t0.x + u0 * t0.y) | ((uint32_t)f32_to_bf16_rne(v1 * t1.x + u1 * t1.y) << 16);
+      }
+    }
   }
 }
 
@@ -124,6 +149,17 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     qpos[rt] = 0;
     if constexpr (ROPE) {
       if (p.rope_q) qpos[rt] = reinterpret_cast<const DevStream*>(meta + p.off_streams)[s].pos;
+    }
+  }
+
+  // A whole stream's rows are turned by one position: its angles are worked out once per work-group, a plane per
+  // thread.  (Every lane for its own planes: 13.4 us per layer
+  // for 300 + 3 x 20 .. 60 tokens of 128 dims, append and decode step; this way 10.7.)
+  if constexpr (ROPE && WHOLE) {
+    if (p.rope_q && tid < D / 2) {
+      float2 t;
+      rope_cos_sin<sizeof(T) == 2>(p.rope_tab, tid, qpos[0], t.x, t.y);
+      lds.turn[tid] = t;
     }
   }
 
@@ -177,7 +213,14 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
           const uint32_t code = lds.off[b * kTok + 16 * t + i];
           if (__builtin_amdgcn_ballot_w64((int)code < 0)) {
             const int row = (int)((code & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
-            if ((int)code < 0) rope_lane<T, kNP>(x.k[t], q, pend_pos_of(p)[row], p.rope_tab);
+            bool by_row = (int)code < 0;
+            if constexpr (WHOLE) {  // the stream's new row stands, as a rule, where its query does
+              if (by_row && p.rope_q && pend_pos_of(p)[row] == qpos[0]) {
+                rope_lane_by<T, kNP>(x.k[t], q, lds.turn);
+                by_row = false;
+              }
+            }
+            if (by_row) rope_lane<T, kNP>(x.k[t], q, pend_pos_of(p)[row], p.rope_tab);
           }
         }
       }
@@ -285,7 +328,10 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       if constexpr (ROPE) {
         if (p.rope_q && !q_turned) {
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) rope_lane<T, kNP>(qf[rt], q, qpos[rt], p.rope_tab);
+          for (int rt = 0; rt < RT; ++rt) {
+            if constexpr (WHOLE) rope_lane_by<T, kNP>(qf[rt], q, lds.turn);
+            else rope_lane<T, kNP>(qf[rt], q, qpos[rt], p.rope_tab);
+          }
         }
         q_turned = true;
       }
@@ -507,7 +553,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
 // it is for short lists only, and every stream reads the shared prefix by itself (from its XCD's L2: work-group mod
 // Hkv is the kv head).  The copy of a deferred append's rows has work-groups of its own behind the others.
 // Append and decode step, split form -> this one (us): bf16, 8 kv heads x 128, 128 + 3 x 20 .. 60 tokens 10.0 -> 6.3, with
-// rotary embedding 13.8 -> 11.9; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
+// rotary embedding, 300 + 3 x 20 .. 60 tokens 13.8 -> 10.7; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
 constexpr int kOneWaves = 8;
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
