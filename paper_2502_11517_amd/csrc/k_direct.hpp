@@ -12,7 +12,7 @@
 //     is the B operand of the next product for that token order;
 //   * O^T += V^T P^T.  The lanes of quarter q load exactly those tokens' V rows, whole rows per 16 lanes.
 //     fp32: a loaded element IS an A operand (one per token and M-tile).  bf16: the eight tokens of a lane
-//     are interleaved in registers, one byte-permute per operand register.  Element c of a lane's piece
+//     are interleaved in registers, one byte-permute per operand register, and a weight is three bf16 operands.  Element c of a lane's piece
 //     belongs to M-tile c, so M-tile c is the head dims { (D / 16) m + c } -- a free renaming, undone when
 //     the rows leave through LDS.
 // The rows' addresses are worked out once per item (one thread per token) and left in LDS as 32-bit codes,
@@ -283,22 +283,60 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       }
     }
   };
-  auto weigh = [&](const Blk& x, const f32x4 (&pr)[kNT][RT]) {  // O^T += V^T P^T
+  // O^T += V^T P^T.  The weights of a bf16 block go in as three bf16 terms, cut off one behind the other, which hold
+  // all their 24 bits (each product is exact in the fp32 accumulator).  A term of 0 must not meet an infinite or NaN
+  // element of V: its product with zeros tells whether there is one, and the lower terms then see 0 in its place.
+  // k_one over 128 dims takes the steps that k_attn would take otherwise and rounds the weights to bf16 once, as that
+  // kernel does.  (8 streams over 4096 tokens of 64 dims: 10.6 us per layer with weights of one term, 11.0 with three;
+  // k_one over 128 dims, 300 + 3 x 20 .. 60 tokens, rotated: 10.7 and 11.1.)
+  auto weigh = [&](const Blk& x, const f32x4 (&pr)[kNT][RT]) {
     if constexpr (sizeof(T) == 2) {
-      bf16x8 pb[RT];
+      constexpr int kTerms = WHOLE && D == 128 ? 1 : 3;
+      u32x4 pb[kTerms][RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
-        pb[rt] = __builtin_bit_cast(bf16x8, u32x4{pack_bf16x2(pr[0][rt][0], pr[0][rt][1]), pack_bf16x2(pr[0][rt][2], pr[0][rt][3]),
-                                                  pack_bf16x2(pr[1][rt][0], pr[1][rt][1]), pack_bf16x2(pr[1][rt][2], pr[1][rt][3])});
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float u = pr[e >> 1][rt][2 * (e & 1)], v = pr[e >> 1][rt][2 * (e & 1) + 1];
+          if constexpr (kTerms == 1) {
+            pb[0][rt][e] = pack_bf16x2(u, v);
+          } else {
+#pragma unroll
+            for (int n = 0; n < kTerms; ++n) {
+              const uint32_t iu = __float_as_uint(u), iv = __float_as_uint(v);
+              pb[n][rt][e] = __builtin_amdgcn_perm(iv, iu, 0x07060302u);
+              u -= __uint_as_float(iu & 0xffff0000u);
+              v -= __uint_as_float(iv & 0xffff0000u);
+            }
+          }
+        }
+      u32x4 a[kMT];
+      f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < kMT; ++c) {
-        u32x4 a;
 #pragma unroll
         for (int e = 0; e < 4; ++e)  // element c of tokens 2 e and 2 e + 1
-          a[e] = __builtin_amdgcn_perm(x.v[2 * e + 1][0][c / 2], x.v[2 * e][0][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+          a[c][e] = __builtin_amdgcn_perm(x.v[2 * e + 1][0][c / 2], x.v[2 * e][0][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+        if constexpr (kTerms > 1)
+          zero = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u}), zero, 0, 0, 0);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), pb[rt], O[rt][c], 0, 0, 0);
+        for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, pb[0][rt]), O[rt][c], 0, 0, 0);
       }
+      if (kTerms > 1 && !__all(zero[0] + zero[1] + zero[2] + zero[3] == 0.f)) {
+#pragma unroll
+        for (int c = 0; c < kMT; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if ((a[c][e] & 0x7f80u) == 0x7f80u) a[c][e] &= 0xffff0000u;
+            if ((a[c][e] & 0x7f800000u) == 0x7f800000u) a[c][e] &= 0xffffu;
+          }
+      }
+#pragma unroll
+      for (int n = 1; n < kTerms; ++n)
+#pragma unroll
+        for (int c = 0; c < kMT; ++c)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, pb[n][rt]), O[rt][c], 0, 0, 0);
     } else {
 #pragma unroll
       for (int t = 0; t < kNT; ++t)

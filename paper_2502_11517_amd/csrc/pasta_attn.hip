@@ -1243,7 +1243,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // takes its operands straight from memory (its address codes count 16-byte pieces in 31 bits).  The vector-ALU
     // walker is left with NO_MFMA and what is larger still.
     const bool fits_direct = !(a->flags & PASTA_DECODE_NO_MFMA) && h->layer_elems * h->elem < ((int64_t)1 << 35);
-    const bool one = fits_direct && small_step(h, a, lv, reqs.size());
+    // (k_one rounds the weights of bf16 x 128 as k_attn does; layers that k_attn does not address keep fp32's)
+    const bool one = fits_direct && (mfma || c.dtype == PASTA_F32 || D == 64) && small_step(h, a, lv, reqs.size());
     const bool direct = fits_direct && (one || !mfma);
     const bool matrix = mfma || direct;
     int64_t pc_total = 0, pc_weighted = 0;  // the second counts a prefix once per work-group that reads it

@@ -1,0 +1,67 @@
+"""The softmax weights of bf16 pools with 64-wide heads have fp32's bits (k_direct, k_one): an output element may differ
+from the exact result by its own rounding to bf16 and by fp32 noise of the sum, and infinite elements of V come
+through them."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2502_11517_amd import binding as B
+from paper_2502_11517_amd import workloads as W
+from paper_2502_11517_amd.harness import to_device
+from test_gpu_parity import _out64, _session
+
+pytestmark = pytest.mark.gpu
+
+INF = 0x7F80
+# (D, prefix, own tokens): short enough for one launch; split into a shared prefix and private lists
+FORMS = [(64, 200, [33, 20, 60]), (64, 31, [1, 2, 3]), (64, 2111, [127, 40, 300])]
+
+
+def _state(D, prefix, lengths, spoil=None):
+    w = W.single_request("weights", "bf16", 16, 4, D, 1.0, 31, prefix, lengths, "random", k_std=2 * D ** -0.5)
+    k, v = w.kv_rows(0, w.n_prefill)
+    v = v.copy()
+    if spoil is not None:
+        spoil(v)
+    s = _session(w, kv_layout=B.HEAD_MAJOR)
+    g = oracle.Geom(w.dtype, w.Hq, w.Hkv, D, pool_tokens=w.pool_tokens, head_major=True)
+    kp, vp, tail = g.new_pool(), g.new_pool(), np.zeros(1, np.int64)
+    oracle.append(g, kp, vp, w.ev_request, k, v, tail)
+    s.h.append_kv(0, w.ev_request, w.ev_stream, to_device(k, "bf16", s.device), to_device(v, "bf16", s.device), parent_stream=w.ev_parent)
+    out, _, _ = s.decode(0, explicit=False)
+    got = _out64(w, out)
+    s.close()
+
+    def exact(values):
+        return oracle.attention(g, kp, values, w.dec_request, *w.lists(0), w.q(0), w.scale)[0]
+
+    return got, exact(vp), exact(vp & 0x7FFF)
+
+
+def _check(got, ref, ref_abs):
+    """Up to 2^-8 of the element for its rounding to 8 significant bits (half a unit of 2^-7); 1e-5 of sum w |v| for a few hundred fp32 steps and exponents of a few units
+    (weights of 8 bits would be off by some 1e-3 of it over these lengths)."""
+    bound = np.abs(ref) * 2.0 ** -8 * 1.001 + 1e-5 * ref_abs
+    worst = float(np.max(np.abs(got - ref) / bound))
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("D,prefix,lengths", FORMS)
+def test_outputs_differ_by_their_own_rounding_alone(D, prefix, lengths):
+    _check(*_state(D, prefix, lengths))
+
+
+@pytest.mark.parametrize("D,prefix,lengths", FORMS)
+def test_infinite_values_come_through(D, prefix, lengths):
+    """+inf in one row of the prefix that every stream sees, -inf in another dim's: these elements are infinite,
+    all others as without them."""
+    def spoil(v):
+        v[7, 1, 5], v[3, 2, D - 1] = INF, INF | 0x8000
+    got, _, _ = _state(D, prefix, lengths, spoil)
+    _, ref, ref_abs = _state(D, prefix, lengths)
+    hit = np.zeros(ref.shape, bool)
+    hit[:, 4:8, 5], hit[:, 8:12, D - 1] = True, True
+    assert np.all(got[:, 4:8, 5] == np.inf) and np.all(got[:, 8:12, D - 1] == -np.inf)
+    _check(np.where(hit, ref, got), ref, ref_abs)
