@@ -194,10 +194,12 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   };
 
   f32x4 O[RT][kMT];
-  float m_run[RT], l_run[RT];  // row rt * 16 + i; l_run covers this lane's quarter of the tokens
+  // Row rt * 16 + i; l_run covers this lane's quarter of the tokens.  The maximum starts at the lowest finite value: a
+  // block whose scores are all -inf in log2 units then has weights of 0 (from -inf on, -inf - -inf would make them NaN).
+  float m_run[RT], l_run[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    m_run[rt] = -INFINITY;
+    m_run[rt] = -__FLT_MAX__;
     l_run[rt] = 0.f;
 #pragma unroll
     for (int c = 0; c < kMT; ++c) O[rt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -442,7 +444,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       if (p.lse && pc == 0) p.lse[row] = (ma + __log2f(l)) * kLn2;
     } else {
       *reinterpret_cast<f32x4*>(p.part_acc + (it.part_row0 + rr) * D + 4 * pc) = acc;
-      if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(ma, l);
+      if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(l > 0.f ? ma : -INFINITY, l);
     }
   }
 }
