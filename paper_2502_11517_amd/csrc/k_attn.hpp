@@ -1011,7 +1011,8 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
   }
 
   f32x16 O[4];  // O^T M-tile mt: d = 32 mt + 8 (i / 4) + 4 hh + i % 4, row l32
-  float m_run = -INFINITY, l_run = 0.f;
+  // (the maximum starts at the lowest finite value: a block whose scores are all -inf in log2 units has weights of 0)
+  float m_run = -__FLT_MAX__, l_run = 0.f;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -1054,7 +1055,7 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * p.scale_log2e;  // finite: every block holds at least one token
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * p.scale_log2e;
     const float mn = fmaxf(m_run, mx);
     const float corr = fast_exp2(m_run - mn);
     m_run = mn;
@@ -1135,7 +1136,7 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
         otile[l32 * 32 + (cc ^ l32)] = f32x4{O[mt][4 * b4], O[mt][4 * b4 + 1], O[mt][4 * b4 + 2], O[mt][4 * b4 + 3]};
       }
     const float l_all = l_run + __shfl_xor(l_run, 32, kWave);
-    if (hh == 0 && l32 < R) p.part_ml[part_row0 + l32] = make_float2(m_run, l_all);
+    if (hh == 0 && l32 < R) p.part_ml[part_row0 + l32] = make_float2(l_all > 0.f ? m_run : -INFINITY, l_all);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -46,3 +46,9 @@ def test_a_block_of_the_prefix(dtype, D, prefix, lo, hi):
 @pytest.mark.parametrize("prefix", [40, 1000])
 def test_all_rows_of_the_threads(dtype, D, prefix):
     _check(dtype, D, 8, 2, prefix, [40, 3], slice(prefix, None))
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 32), (32, 160), (1472, 1500)])
+def test_a_block_of_the_prefix_under_four_row_groups(lo, hi):
+    """5 streams x 8 heads per kv head = 40 stacked rows: the work-groups that serve four row groups each."""
+    _check("bf16", 128, 16, 2, 1500, [30, 7, 140, 20, 26], slice(lo, hi), flags=B.DECODE_FOUR_GROUPS)
