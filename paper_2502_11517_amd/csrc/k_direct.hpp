@@ -126,6 +126,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   typedef DirBlock<T, D> Blk;
   constexpr int kTok = Blk::kTok, kNT = Blk::kNT, kNP = Blk::kNP, kMT = D / 16;
   constexpr int kPieceRow = D * (int)sizeof(T) / 16;
+  constexpr bool kExact = sizeof(T) == 4 || D == 64 || !WHOLE;  // (otherwise k_attn's arithmetic, see weigh)
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = p.Hq / p.Hkv;
@@ -289,11 +290,11 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   // all their 24 bits (each product is exact in the fp32 accumulator).  A term of 0 must not meet an infinite or NaN
   // element of V: its product with zeros tells whether there is one, and the lower terms then see 0 in its place.
   // k_one over 128 dims takes the steps that k_attn would take otherwise and rounds the weights to bf16 once, as that
-  // kernel does.  (8 streams over 4096 tokens of 64 dims: 10.6 us per layer with weights of one term, 11.0 with three;
+  // kernel does (and, as there, places past a list's end repeat its last token whatever that holds).  (8 streams over 4096 tokens of 64 dims: 10.6 us per layer with weights of one term, 11.0 with three;
   // k_one over 128 dims, 300 + 3 x 20 .. 60 tokens, rotated: 10.7 and 11.1.)
   auto weigh = [&](const Blk& x, const f32x4 (&pr)[kNT][RT]) {
     if constexpr (sizeof(T) == 2) {
-      constexpr int kTerms = WHOLE && D == 128 ? 1 : 3;
+      constexpr int kTerms = kExact ? 3 : 1;
       u32x4 pb[kTerms][RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
@@ -386,6 +387,16 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       load_v(A, b + NW);
     }
     scores(A, last, n_here, pr);
+    if (kExact && (last + 1) * kTok > n_here) {  // places past the end hold the last token again: 0 x its infinities would be NaN
+      const int left = n_here - (last * kTok + 4 * q);
+#pragma unroll
+      for (int t = 0; t < kNT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int h = 0; h < Blk::kVP; ++h)
+            if (16 * t + r >= left) A.v[4 * t + r][h] = typename Blk::vec(0);
+    }
     weigh(A, pr);
   }
 

@@ -65,3 +65,21 @@ def test_infinite_values_come_through(D, prefix, lengths):
     hit[:, 4:8, 5], hit[:, 8:12, D - 1] = True, True
     assert np.all(got[:, 4:8, 5] == np.inf) and np.all(got[:, 8:12, D - 1] == -np.inf)
     _check(np.where(hit, ref, got), ref, ref_abs)
+
+
+@pytest.mark.parametrize("prefix,own,dtype,D", [
+    (p, n, *kind) for p, n in [(48, 16), (200, 16), (1100, 48), (1000, 8)] for kind in [("bf16", 64), ("f32", 64), ("f32", 128)]])
+def test_an_infinite_value_in_the_last_row(prefix, own, dtype, D):
+    """One thread whose list ends inside a block: the places past its end must not turn its last row's infinity into NaN."""
+    w = W.single_request("last", dtype, 8, 2, D, 1.0, 32, prefix, [own], "random", k_std=D ** -0.5)
+    k, v = w.kv_rows(0, w.n_prefill)
+    v = v.copy()
+    v[-1, 0, 3] = INF if dtype == "bf16" else np.inf
+    s = _session(w)
+    s.h.append_kv(0, w.ev_request, w.ev_stream, to_device(k, dtype, s.device), to_device(v, dtype, s.device), parent_stream=w.ev_parent)
+    out, _, _ = s.decode(0, explicit=False)
+    got = _out64(w, out)
+    s.close()
+    hit = np.zeros(got.shape, bool)
+    hit[:, :4, 3] = True
+    assert np.all(got[hit] == np.inf) and np.all(np.isfinite(got[~hit]))
