@@ -231,7 +231,8 @@ enum {
   PASTA_DECODE_DEVICE_LISTS = 256u, /* maintained mode: take the lists from their device-resident copy even when the
                                        step's plan would fit the kernel arguments (see "Maintained lists on the
                                        device" below); E_INVAL with explicit lists, causal_skip or DENSE_MASK,
-                                       E_CAPACITY when the copy has no room */
+                                       E_CAPACITY when the copy has no room, or is out of date in a call that may
+                                       not rebuild it (stream capture, the no-alloc entry point) */
   /* A request with more than 32 stacked query rows (streams x heads per kv head) is served in groups of 32 rows:
    * one group per work-group, or -- when every request of the step with a shared prefix is that wide -- four
    * groups per work-group.  The library picks by the step's shape; these two flags force either form (both:
@@ -258,7 +259,10 @@ enum {
  * per stream -- with the stream's newest range, which changes at every append, inline -- and the kernels find
  * ranges and derive the private work items themselves: the bytes a step sends do not grow with the lists, no
  * KV row and no list entry moves at a join (Section 3, "Efficiency").  Small plans ride in the kernel arguments
- * as before (no dependent loads on the way to the first K/V request).                                      */
+ * as before (no dependent loads on the way to the first K/V request).
+ * Stream capture: a captured call records every word its launches read, so it may be replayed whatever later calls
+ * do to the library's staging; lists that are out of date on the device are then sent whole.  A captured step that
+ * did read the copy on the device is to be replayed only while these lists have done no more than grow.    */
 typedef struct {
   uint32_t struct_size;
   uint32_t flags;               /* PASTA_DECODE_* */

@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256) void k_append(AppendParams p) {
   }
 }
 
-// Carries a piece of a decode step's plan to the device inside its own kernel arguments (two launches at
-// most): how a step under stream capture sends a plan that is too large for k_plan's arguments, since a
-// captured launch must not depend on what later calls leave in host memory.
+// Carries a piece of a decode step's plan, or of an append's list of rows, to the device inside its own kernel
+// arguments: how calls under stream capture send what is too large for the arguments of the launch that reads it,
+// since a captured launch must not depend on what later calls leave in host memory.
 constexpr int kRelayWords = 960;
 struct RelayParams {
   int32_t* dst;

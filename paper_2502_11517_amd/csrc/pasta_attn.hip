@@ -28,7 +28,6 @@ namespace {
 
 constexpr uint32_t kMagic = 0x50415354u;  // "PAST"
 constexpr int kRing = 8;                  // metadata staging buffers in flight
-constexpr int kRelayMaxWords = 2 * kRelayWords;  // largest plan that travels to the device inside kernel arguments
 constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes)
 constexpr int kOneTokens = 1024;          // most tokens of a work-group of k_one (it holds their addresses at once)
 constexpr int kNumCUs = 256;              // MI355X; planning default until the device has been asked
@@ -308,11 +307,37 @@ int ring_give(pasta_attn* h, int slot) {  // the work that reads the slot has be
   return PASTA_OK;
 }
 
-// Copies `bytes` of host metadata to the next device staging slot, asynchronously on the
+bool stream_capturing(const pasta_attn* h) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)h->cfg.hip_stream, &cap) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// Host words to the next device staging slot inside the arguments of as many small launches as it takes.
+int relay_words(pasta_attn* h, const int32_t* src, size_t n, const int32_t** dev_out) {
+  const int s = h->relay_next;
+  h->relay_next = (s + 1) % kRing;
+  int32_t* dev = (int32_t*)((char*)h->cfg.workspace + h->off_meta + (size_t)s * h->meta_bytes);
+  for (size_t lo = 0; lo < n; lo += kRelayWords) {
+    RelayParams rp;
+    rp.dst = dev + lo;
+    rp.n_words = (int)std::min<size_t>(kRelayWords, n - lo);
+    std::memcpy(rp.words, src + lo, (size_t)rp.n_words * 4);
+    k_meta_relay<<<dim3(1), 256, 0, (hipStream_t)h->cfg.hip_stream>>>(rp);
+    if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
+  }
+  *dev_out = dev;
+  return PASTA_OK;
+}
+
+// Copies n words of host metadata to the next device staging slot, asynchronously on the
 // caller's stream; returns the device address.  A slot is reused only after the copy that
-// last read its pinned half has completed.
-int upload_meta(pasta_attn* h, const void* src, size_t bytes, const int32_t** dev_out) {
+// last read its pinned half has completed.  (Under stream capture the words are recorded with the launches
+// that carry them: a replay finds a pinned slot as later calls have left it.)
+int upload_meta(pasta_attn* h, const int32_t* src, size_t n, const int32_t** dev_out) {
+  const size_t bytes = n * 4;
   if (bytes > h->meta_bytes) return PASTA_E_CAPACITY;
+  if (stream_capturing(h)) return relay_words(h, src, n, dev_out);
   int s;
   char* host;
   const int rc = ring_take(h, &s, &host);
@@ -325,7 +350,7 @@ int upload_meta(pasta_attn* h, const void* src, size_t bytes, const int32_t** de
   return ring_give(h, s);
 }
 
-// Sends the staged pieces of lists to their places in the workspace: one pinned slot, one launch.
+// Sends the staged pieces of lists to their places in the workspace: one pinned slot, one launch (never under capture).
 int flush_lists(pasta_attn* h) {
   std::vector<ListPiece>& ps = h->stage_pieces;
   std::vector<int32_t>& words = h->stage_words;
@@ -545,8 +570,8 @@ int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const
   const size_t per = std::min(h->meta_bytes / 4, most);
   for (size_t lo = 0; lo < (size_t)n_rows; lo += per) {
     const size_t n = std::min(per, (size_t)n_rows - lo);
-    int rc = upload_meta(h, dst.data() + lo, n * 4, &p.dst_rows);
-    if (rc == PASTA_OK && rope) rc = upload_meta(h, positions + lo, n * 4, &p.pos_rows);
+    int rc = upload_meta(h, dst.data() + lo, n, &p.dst_rows);
+    if (rc == PASTA_OK && rope) rc = upload_meta(h, positions + lo, n, &p.pos_rows);
     if (rc == PASTA_OK) rc = launch(lo, n);
     if (rc != PASTA_OK) return rc;
   }
@@ -1313,21 +1338,28 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       return PASTA_E_INVAL;
     }
     if (dev_lists && !plan_only) {  // the copies this step reads must be current (all but each list's newest range)
-      if (h->tables_reset) {        // the segments ran out earlier: start over
-        h->tables_reset = false;
-        h->arena_top = h->cidx_top = 0;
-        for (StreamState& ss : h->streams) { ss.seg_off = ss.cseg_off = -1; ss.seg_cap = ss.cseg_cap = 0; ss.dirty = true; }
+      auto stale = [](const StreamState& ss) { return ss.dirty || ss.dev_ranges < (int32_t)ss.ranges.size() - 1; };
+      bool rebuild = h->tables_reset;
+      for (int i = 0; i < n && !rebuild; ++i) rebuild = stale(sstate(h, a->request_id[i], a->stream_id[i]));
+      // No rebuild where nothing may be allocated (it stages through buffers that may have to grow), nor under stream
+      // capture: a replay would find the pinned slot as later calls left it, and put back lists of another time.
+      if (rebuild && (no_alloc || stream_capturing(h))) rebuild = dev_lists = false;
+      if (rebuild) {
+        if (h->tables_reset) {  // the segments ran out earlier: start over
+          h->tables_reset = false;
+          h->arena_top = h->cidx_top = 0;
+          for (StreamState& ss : h->streams) { ss.seg_off = ss.cseg_off = -1; ss.seg_cap = ss.cseg_cap = 0; ss.dirty = true; }
+        }
+        for (int i = 0; i < n && dev_lists; ++i) {
+          StreamState& ss = sstate(h, a->request_id[i], a->stream_id[i]);
+          if (!stale(ss)) continue;
+          const int rb = rebuild_tables(h, ss);
+          if (rb == kNoRoom) dev_lists = false;
+          else if (rb != PASTA_OK) return rb;
+        }
+        const int fl = flush_lists(h);
+        if (fl != PASTA_OK) return fl;
       }
-      for (int i = 0; i < n && dev_lists; ++i) {
-        StreamState& ss = sstate(h, a->request_id[i], a->stream_id[i]);
-        if (!ss.dirty && ss.dev_ranges >= (int32_t)ss.ranges.size() - 1) continue;
-        if (no_alloc) { dev_lists = false; break; }  // (a rebuild stages through buffers that may have to grow)
-        const int rb = rebuild_tables(h, ss);
-        if (rb == kNoRoom) dev_lists = false;
-        else if (rb != PASTA_OK) return rb;
-      }
-      const int fl = flush_lists(h);
-      if (fl != PASTA_OK) return fl;
       if (dev_lists) h->lists_in_use = true;
     }
     if (!dev_lists && (a->flags & PASTA_DECODE_DEVICE_LISTS)) return PASTA_E_CAPACITY;
@@ -1548,9 +1580,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       }
       blob.push_back((int32_t)priv_chunk);
       if (blob.size() * 4 > h->meta_bytes) return PASTA_E_CAPACITY;
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
-      const bool capturing = cap != hipStreamCaptureStatusNone;
+      const bool capturing = stream_capturing(h);
       const int at = capturing ? 1 : 0;
       int32_t* dev = (int32_t*)((char*)c.workspace + h->off_plan[at]);
       DevItem* d_items = (DevItem*)((char*)c.workspace + h->off_plan_items[at]);
@@ -1560,18 +1590,10 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         PlanParams pp{};
         if (keep && blob.size() <= (size_t)kPlanWords) {
           std::memcpy(pp.words, blob.data(), blob.size() * 4);
-        } else if (capturing && blob.size() <= (size_t)kRelayMaxWords) {  // inside the kernel arguments of one or two tiny launches
-          const int sl = h->relay_next;
-          h->relay_next = (sl + 1) % kRing;
-          int32_t* staged = (int32_t*)((char*)c.workspace + h->off_meta + (size_t)sl * h->meta_bytes);
-          for (size_t lo = 0; lo < blob.size(); lo += kRelayWords) {
-            RelayParams rp;
-            rp.dst = staged + lo;
-            rp.n_words = (int)std::min<size_t>(kRelayWords, blob.size() - lo);
-            std::memcpy(rp.words, blob.data() + lo, (size_t)rp.n_words * 4);
-            k_meta_relay<<<dim3(1), 256, 0, st>>>(rp);
-          }
-          p.meta = pp.src = staged;
+        } else if (capturing) {
+          rc = relay_words(h, blob.data(), blob.size(), &pp.src);
+          if (rc != PASTA_OK) return rc;
+          p.meta = pp.src;
         } else {  // through pinned memory; the slot is reused only after the launches that read it have completed
           char* host = nullptr;
           rc = ring_take(h, &meta_slot, &host);
