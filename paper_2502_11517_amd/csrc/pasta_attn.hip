@@ -21,6 +21,7 @@
 #include "k_direct.hpp"
 #include "k_merge.hpp"
 #include "k_private.hpp"
+#include "staging_ring.hpp"
 
 using namespace pasta;
 
@@ -141,8 +142,8 @@ struct pasta_attn {
   hipEvent_t ring_ev[2]{};               // one per half of the ring
   int ring_ev_made = 0;                  // events created so far (both once the device is ready)
   int device = 0, n_cus = kNumCUs;       // the device current at first use and its compute-unit count
-  bool ring_used[2]{};
-  int ring_next = 0, relay_next = 0;
+  StagingRing<kRing> ring;
+  int relay_next = 0;
 };
 
 namespace {
@@ -289,22 +290,14 @@ int ensure_device(pasta_attn* h) {
   return PASTA_OK;
 }
 
-// The pinned staging slots go round; one is written again only after the work that reads it has completed.
-// That is recorded once per half of the ring, behind its last slot: an event is a packet on the stream.
 int ring_take(pasta_attn* h, int* slot, char** host) {
-  const int s = h->ring_next, half = s / (kRing / 2);
-  if (s % (kRing / 2) == 0 && h->ring_used[half] && hipEventSynchronize(h->ring_ev[half]) != hipSuccess) return PASTA_E_DEVICE;
-  h->ring_next = (s + 1) % kRing;
-  *slot = s;
-  *host = h->pinned + (size_t)s * h->meta_bytes;
+  if (!h->ring.take(slot, [&](int half) { return hipEventSynchronize(h->ring_ev[half]) == hipSuccess; },
+                    [&] { return hipStreamSynchronize((hipStream_t)h->cfg.hip_stream) == hipSuccess; })) return PASTA_E_DEVICE;
+  *host = h->pinned + (size_t)*slot * h->meta_bytes;
   return PASTA_OK;
 }
-int ring_give(pasta_attn* h, int slot) {  // the work that reads the slot has been enqueued
-  const int half = slot / (kRing / 2);
-  if (slot % (kRing / 2) != kRing / 2 - 1) return PASTA_OK;
-  if (hipEventRecord(h->ring_ev[half], (hipStream_t)h->cfg.hip_stream) != hipSuccess) return PASTA_E_DEVICE;
-  h->ring_used[half] = true;
-  return PASTA_OK;
+int ring_give(pasta_attn* h) {  // the work that reads the slot has been enqueued
+  return h->ring.give([&](int half) { return hipEventRecord(h->ring_ev[half], (hipStream_t)h->cfg.hip_stream) == hipSuccess; }) ? PASTA_OK : PASTA_E_DEVICE;
 }
 
 bool stream_capturing(const pasta_attn* h) {
@@ -347,7 +340,7 @@ int upload_meta(pasta_attn* h, const int32_t* src, size_t n, const int32_t** dev
   hipStream_t st = (hipStream_t)h->cfg.hip_stream;
   if (hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st) != hipSuccess) return PASTA_E_DEVICE;
   *dev_out = (const int32_t*)dev;
-  return ring_give(h, s);
+  return ring_give(h);
 }
 
 // Sends the staged pieces of lists to their places in the workspace: one pinned slot, one launch (never under capture).
@@ -366,7 +359,7 @@ int flush_lists(pasta_attn* h) {
   if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
   ps.clear();
   words.clear();
-  return ring_give(h, sl);
+  return ring_give(h);
 }
 
 // Stages n words for place `off` (bytes, a multiple of 4) of the workspace, in pieces of a few KB each.
@@ -386,7 +379,7 @@ int stage_list(pasta_attn* h, size_t off, const int32_t* src, size_t n) {
 
 constexpr int kNoRoom = 1;  // rebuild_tables: the segments ran out (not an error: the call plans from the host lists)
 
-// Rebuilds the device copy of one stream's range list and range index from the mirror; flush_lists sends it.
+// Stages the device copy of one stream's range list and range index, from the mirror; flush_lists sends it.
 int rebuild_tables(pasta_attn* h, StreamState& st) {
   const int64_t n = (int64_t)st.ranges.size();
   const int64_t n_c = (st.range_tokens + kCidxTokens - 1) / kCidxTokens;
@@ -421,7 +414,7 @@ int rebuild_tables(pasta_attn* h, StreamState& st) {
   if (rc != PASTA_OK) return rc;
   st.dev_ranges = (int32_t)n;
   st.dev_cidx = (int32_t)n_c;
-  st.dirty = false;
+  st.dirty = true;  // until the pieces have been sent
   return PASTA_OK;
 }
 
@@ -1345,6 +1338,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       // capture: a replay would find the pinned slot as later calls left it, and put back lists of another time.
       if (rebuild && (no_alloc || stream_capturing(h))) rebuild = dev_lists = false;
       if (rebuild) {
+        h->stage_pieces.clear();  // (what a failed call may have left)
+        h->stage_words.clear();
         if (h->tables_reset) {  // the segments ran out earlier: start over
           h->tables_reset = false;
           h->arena_top = h->cidx_top = 0;
@@ -1359,6 +1354,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         }
         const int fl = flush_lists(h);
         if (fl != PASTA_OK) return fl;
+        for (int i = 0; i < n && dev_lists; ++i) sstate(h, a->request_id[i], a->stream_id[i]).dirty = false;  // (kNoRoom: staged again next time)
       }
       if (dev_lists) h->lists_in_use = true;
     }
@@ -1620,7 +1616,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
           k_plan<<<dim3((unsigned)wgs), 256, 0, st>>>(pp);
           if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
           if (meta_slot >= 0) {
-            rc = ring_give(h, meta_slot);
+            rc = ring_give(h);
             if (rc != PASTA_OK) return rc;
             meta_slot = -1;
           }
@@ -1748,7 +1744,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       if (rc != PASTA_OK) return rc;
     }
     if (meta_slot >= 0) {
-      rc = ring_give(h, meta_slot);
+      rc = ring_give(h);
       if (rc != PASTA_OK) return rc;
     }
     if (hipGetLastError() != hipSuccess) return PASTA_E_DEVICE;
