@@ -672,8 +672,8 @@ extern "C" int32_t pasta_attn_create(pasta_attn_config* cfg, pasta_attn** out) {
     pb.req_idx_of.reserve(cfg->max_requests); pb.reqs.reserve(cfg->max_requests);
     pb.ranges.reserve(std::min<size_t>((size_t)cfg->max_ranges + nsc, kInlineMetaWords));
     pb.items.reserve(kInlineMetaWords / (sizeof(DevItem) / 4));
-    pb.blob.reserve(kInlineMetaWords + 16 + (size_t)kInlineMetaWords);  // (and an entry per private item: device-resident lists)
-    h->plan_words.reserve(2 * kInlineMetaWords + 16);
+    pb.blob.reserve(kInlineMetaWords + 16 + (size_t)h->plan_items_cap);  // (and an entry per private item: device-resident lists)
+    h->plan_words.reserve(kInlineMetaWords + 16 + (size_t)h->plan_items_cap);
   } catch (...) { return fail(PASTA_E_NOMEM); }
 #if defined(PASTA_TUNING) && PASTA_TUNING >= 2
   std::fprintf(stderr, "PASTA_CLOCKS byte offset in workspace: %zu\n", h->off_ml + (size_t)(h->part_rows_cap - 16 * PASTA_CLK_WGS) * 8);

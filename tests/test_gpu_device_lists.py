@@ -188,3 +188,19 @@ def test_device_lists_refusals_and_no_alloc():
     ref, _ = op.attention(0)
     check_close(_out64(w, out2), ref, w.dtype, "no-alloc, device lists")
     s.close()
+
+
+def test_no_alloc_over_more_private_items_than_a_small_plan_has_words():
+    """24 streams of 6000 own tokens: 1128 private items in a plan of 24 records.  The copies on the device are brought
+    up to date a few streams at a time, so that nothing but the set-up has sized the handle's buffers."""
+    from paper_2502_11517_amd.harness import to_device
+    w = W.single_request("items", "bf16", 2, 1, 128, 1.0, 24, 64, [6000] * 24, "round_robin", k_std=128 ** -0.5)
+    s = _session(w)
+    s.append_events(w.n_prefill)
+    qd = to_device(w.q(0), w.dtype, s.device)
+    out, part = torch.empty_like(qd), torch.empty_like(qd)
+    for lo in range(0, w.n, 4):
+        s.h.decode_step(0, w.dec_request[lo:lo + 4], w.dec_stream[lo:lo + 4], qd[lo:lo + 4], part[lo:lo + 4], flags=DEV)
+    s.h.decode_step_noalloc(0, w.dec_request, w.dec_stream, qd, out, flags=DEV)
+    check_close(_out64(w, out), _out64(w, part), w.dtype, "no-alloc, 1128 private items")  # (chunks of the prefix differ)
+    s.close()
