@@ -232,7 +232,9 @@ enum {
                                        step's plan would fit the kernel arguments (see "Maintained lists on the
                                        device" below); E_INVAL with explicit lists, causal_skip or DENSE_MASK,
                                        E_CAPACITY when the copy has no room, or is out of date in a call that may
-                                       not rebuild it (stream capture, the no-alloc entry point) */
+                                       not rebuild it (stream capture, the no-alloc entry point); a step whose streams
+                                       have more than 4M tokens beyond the common prefixes is planned from the host's
+                                       lists all the same (the entry point below needs a small plan then) */
   /* A request with more than 32 stacked query rows (streams x heads per kv head) is served in groups of 32 rows:
    * one group per work-group, or -- when every request of the step with a shared prefix is that wide -- four
    * groups per work-group.  The library picks by the step's shape; these two flags force either form (both:

@@ -29,7 +29,8 @@ namespace {
 
 constexpr uint32_t kMagic = 0x50415354u;  // "PAST"
 constexpr int kRing = 8;                  // metadata staging buffers in flight
-constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes)
+constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes;
+                                                     // more where the streams of a no-alloc call can have more between them)
 constexpr int kOneTokens = 1024;          // most tokens of a work-group of k_one (it holds their addresses at once)
 constexpr int kNumCUs = 256;              // MI355X; planning default until the device has been asked
 constexpr int kTargetPrefixWgs = 768;     // most shared-prefix work-groups budgeted for
@@ -223,10 +224,11 @@ void carve(pasta_attn* h) {
     h->off_cidx = off;
     off += align_up((size_t)h->cidx_cap * 4, 256);
   }
-  {  // the plan kept on the device; a plan with more private tokens is derived by the attention launch itself
+  {  // the plan kept on the device; one with more private tokens is made from the host's lists and read where it lies
     const int64_t ns = (int64_t)c.max_requests * c.max_streams;
     const int64_t cap_tokens = c.page_tokens ? (int64_t)c.pages_per_request * c.page_tokens : c.pool_tokens;
-    h->plan_codes_cap = std::min<int64_t>(ns * (cap_tokens + 2 * kGatherMax), kPlanCodesMax);
+    const int64_t per_stream = cap_tokens + 2 * kGatherMax;
+    h->plan_codes_cap = std::min<int64_t>(ns * per_stream, std::max<int64_t>(kPlanCodesMax, kInlineMetaWords / (sizeof(DevStream) / 4) * per_stream));
     h->plan_items_cap = h->plan_codes_cap / kPrivChunk;
     for (int at = 0; at < 2; ++at) {
       h->off_plan[at] = off;
@@ -1315,7 +1317,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // the kernels derive the private work items, instead of sending every range and item.  A plan small
     // enough to ride in the kernel arguments is sent whole all the same -- its items then cost the
     // kernels no dependent loads -- unless the caller asks for the device lists.
-    bool dev_lists = false;
+    bool dev_lists = false, plan_fits = true;
     if (!explicit_mode && !a->causal_skip && !dense) {
       int64_t dev_items = 0;
       int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (sizeof(DevReq) / 4) + 8;
@@ -1326,7 +1328,8 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         dev_items += (priv + priv_chunk - 1) / priv_chunk + 1;
       }
       dev_lists = (a->flags & PASTA_DECODE_DEVICE_LISTS) || words > kInlineMetaWords;
-      if (dev_items > h->plan_items_cap || dev_items * priv_chunk > h->plan_codes_cap) dev_lists = false;  // (k_plan has no room)
+      plan_fits = dev_items <= h->plan_items_cap && dev_items * priv_chunk <= h->plan_codes_cap;
+      if (!plan_fits) dev_lists = false;  // (k_plan has no room)
     } else if (a->flags & PASTA_DECODE_DEVICE_LISTS) {
       return PASTA_E_INVAL;
     }
@@ -1358,7 +1361,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       }
       if (dev_lists) h->lists_in_use = true;
     }
-    if (!dev_lists && (a->flags & PASTA_DECODE_DEVICE_LISTS)) return PASTA_E_CAPACITY;
+    if (!dev_lists && plan_fits && (a->flags & PASTA_DECODE_DEVICE_LISTS)) return PASTA_E_CAPACITY;
     // private items
     std::vector<DevStream>& streams = pb.streams;
     std::vector<DevRange>& ranges = pb.ranges;

@@ -204,3 +204,13 @@ def test_no_alloc_over_more_private_items_than_a_small_plan_has_words():
     s.h.decode_step_noalloc(0, w.dec_request, w.dec_stream, qd, out, flags=DEV)
     check_close(_out64(w, out), _out64(w, part), w.dtype, "no-alloc, 1128 private items")  # (chunks of the prefix differ)
     s.close()
+
+
+def test_more_private_tokens_than_a_kept_plan_holds():
+    """40 streams that read a prefix of 110k tokens each by themselves: 4.4M private tokens in one step."""
+    w = W.single_request("4M", "bf16", 1, 1, 64, 1.0, 25, 110_000, [3] * 40, "round_robin", k_std=64 ** -0.5)
+    s = _session(w)
+    op = OraclePool(w).append_events(w.n_prefill)
+    s.append_events(w.n_prefill)
+    _check_step(w, s, op, explicit=False, flags=DEV | B.DECODE_NO_SHARE, streams=[0, 17, 39], what="4.4M private tokens")
+    s.close()
