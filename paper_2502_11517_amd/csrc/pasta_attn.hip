@@ -761,7 +761,8 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       while (end < a->n_rows && a->request_id[end] == r && a->stream_id[end] == s && (!a->parent_stream || a->parent_stream[end] == -1)) end++;
       const int n_g = end - i;
       const int64_t slot = t2[r];
-      if (slot + n_g > (c.page_tokens ? (int64_t)h->req_pages[r] << h->page_shift : h->req_capacity)) return fail(PASTA_E_CAPACITY);
+      const int64_t room = c.page_tokens ? (int64_t)h->req_pages[r] << h->page_shift : h->req_capacity;
+      if (slot >= room) return fail(PASTA_E_CAPACITY);  // (the errors are those of the first row that cannot be taken)
       t2[r] = slot + n_g;
       // the copy's runs: one as long as the request stays the same (and the position ids go on by one)
       for (int k = i; k < end;) {
@@ -772,7 +773,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
         k = ke;
       }
       if (!commit) {  // replay: same slots as the layer-0 call, lists untouched
-        if (slot + n_g > h->tail[r]) return fail(PASTA_E_STATE);
+        if (slot + n_g > h->tail[r]) return fail(h->tail[r] >= room ? PASTA_E_CAPACITY : PASTA_E_STATE);
         continue;
       }
       StreamState& st = touch(r, s);
@@ -800,6 +801,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
         st.dirty = true;  // the device copy is rebuilt from the mirror when a decode step wants it
         st.dev_ranges = st.dev_cidx = 0;
       }
+      if (slot + n_g > room) return fail(PASTA_E_CAPACITY);
       add_slots(st, (int32_t)slot, n_g);
       if ((int64_t)st.ranges.size() > c.max_ranges) return fail(PASTA_E_CAPACITY);
     }

@@ -497,3 +497,23 @@ def test_device_list_plans_have_a_fixed_size_and_failed_appends_leave_the_lists_
         assert b[0] == a_[0] and all(np.array_equal(x, y) for x, y in zip(b[1:], a_[1:]))
     assert _plan(h, [0, 0], [1, 2], flags=B.DECODE_DEVICE_LISTS)[1][2] == sizes[1][2]   # same item count: token counts restored
     h.destroy()
+
+
+def test_append_errors_are_those_of_the_first_row_that_cannot_be_taken():
+    """Rows that one stream appends one behind the other: a layer-1 call that leaves the layer-0 rows behind long before
+    the pool is full, and one that meets both at once; a row that opens a stream wrongly ahead of rows without room."""
+    h = _handle(n_layers=2, pool_tokens=64, max_streams=4)
+    _reserve(h, [0] * 10, [0] * 10)
+    for rows, par, layer, code in [(100, None, 1, B.E_STATE), (11, None, 1, B.E_STATE), (100, [2] + [-1] * 99, 0, B.E_INVAL),
+                                   (100, [0] + [-1] * 99, 0, B.E_CAPACITY)]:
+        with pytest.raises(B.PastaError) as e:
+            _reserve(h, [0] * rows, [0 if par is None else 1] * rows, par=par, layer=layer)
+        assert e.value.code == code, (rows, par, layer)
+    assert _reserve(h, [0] * 54, [0] * 54).tolist() == list(range(10, 64))
+    with pytest.raises(B.PastaError) as e:
+        _reserve(h, [0] * 55, [0] * 55, layer=1)
+    assert e.value.code == B.E_CAPACITY
+    with pytest.raises(B.PastaError) as e:  # no room for the first row: that comes first
+        _reserve(h, [0], [1], par=[2])
+    assert e.value.code == B.E_CAPACITY
+    h.destroy()
