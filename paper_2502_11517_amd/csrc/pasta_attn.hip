@@ -512,6 +512,15 @@ struct ListPatches {  // entries of the device-resident lists that an append bri
   int32_t c_val[kPatchMax];
 };
 
+// Most rows of one K1 launch: the kernel numbers its pieces in 32 bits.
+size_t append_rows_max(const pasta_attn* h, bool rope) {
+  return (size_t)(((int64_t)1 << 30) / ((int64_t)h->cfg.n_kv_heads * h->cfg.head_dim * h->elem / 16 / (rope ? 2 : 1)));
+}
+// Whether an append sends its destination rows as a list: more runs than travel in the kernel arguments, or more rows than one launch takes.
+bool append_as_list(const pasta_attn* h, size_t n_runs, int n_rows, bool rope) {
+  return n_runs > (size_t)kAppendRuns || (size_t)n_rows > append_rows_max(h, rope);
+}
+
 // Launches K1 for n_rows rows that form the given runs.  positions: rotate K by them.
 int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const void* v_new, const std::vector<AppendRun>& runs,
                   const int32_t* positions = nullptr, const ListPatches* patches = nullptr) {
@@ -541,8 +550,7 @@ int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const
     else k_append<false><<<grid, 256, 0, st>>>(p);
     return hipGetLastError() == hipSuccess ? PASTA_OK : PASTA_E_DEVICE;
   };
-  const size_t most = (size_t)(((int64_t)1 << 30) / units_per_row);  // 32-bit piece numbers in the kernel
-  if (runs.size() <= (size_t)kAppendRuns && (size_t)n_rows <= most) {
+  if (!append_as_list(h, runs.size(), n_rows, rope)) {
     p.n_runs = (int)runs.size();
     std::memcpy(p.runs, runs.data(), runs.size() * sizeof(AppendRun));
     if (patches) {
@@ -555,14 +563,14 @@ int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const
     }
     return launch(0, (size_t)n_rows);
   }
-  // more runs than travel in the kernel arguments: the destination rows as a list, in pieces of one staging slot
-  std::vector<int32_t>& dst = h->dst_rows;
+  // the destination rows as a list, in pieces of one staging slot
+  std::vector<int32_t>& dst = h->dst_rows;  // (append_kv has reserved it)
   dst.resize((size_t)n_rows);
   for (size_t k = 0; k < runs.size(); ++k) {
     const int32_t end = k + 1 < runs.size() ? runs[k + 1].row0 : n_rows;
     for (int32_t i = runs[k].row0; i < end; ++i) dst[(size_t)i] = (int32_t)host_phys(h, runs[k].req, runs[k].slot0 + (i - runs[k].row0));
   }
-  const size_t per = std::min(h->meta_bytes / 4, most);
+  const size_t per = std::min(h->meta_bytes / 4, append_rows_max(h, rope));
   for (size_t lo = 0; lo < (size_t)n_rows; lo += per) {
     const size_t n = std::min(per, (size_t)n_rows - lo);
     int rc = upload_meta(h, dst.data() + lo, n, &p.dst_rows);
@@ -665,6 +673,7 @@ extern "C" int32_t pasta_attn_create(pasta_attn_config* cfg, pasta_attn** out) {
     h->tail.assign(cfg->max_requests, 0);
     h->tail_before.assign(cfg->max_requests, 0);
     h->streams.resize((size_t)cfg->max_requests * cfg->max_streams);
+    for (auto* v : {&h->pending.req_pend0, &h->pending.req_src0, &h->pending.stage_p0, &h->pending.stage_s0, &h->pending.stage_last}) v->reserve(cfg->max_requests);
     // plan buffers: what a plan that rides in the kernel arguments can need (larger plans grow them on demand)
     const size_t ns = (size_t)cfg->max_requests * cfg->max_streams, nsc = std::min<size_t>(ns, 65535);
     PlanBuf& pb = h->pb;
@@ -805,6 +814,7 @@ extern "C" int32_t pasta_attn_append_kv(pasta_attn* h, const pasta_append_args* 
       add_slots(st, (int32_t)slot, n_g);
       if ((int64_t)st.ranges.size() > c.max_ranges) return fail(PASTA_E_CAPACITY);
     }
+    if (!reserve_only && append_as_list(h, runs.size(), a->n_rows, rope)) h->dst_rows.reserve((size_t)a->n_rows);  // (the launch below must not throw)
   } catch (...) { roll_back(); return PASTA_E_NOMEM; }
 
   // ---- what the call changes in the device-resident lists.  A stream whose ranges only GREW needs
