@@ -8,8 +8,8 @@
 // destination rows had to be written, pinned and copied to the device ahead of the launch, in two launches for
 // 8192 rows: 44 us per layer for a prompt of 8192 rows, 8 heads x 128 bf16, of which the kernels took 22; with
 // runs 14.)  A call with more runs than fit the kernel arguments still sends the list.
-// What bounds it: memory, for a prompt.  A thread moves four pieces of K and four of V, all requested before the
-// first is stored.
+// What bounds it: memory, for a prompt: a thread moves four pieces of K and four of V, all requested before the first is
+// stored.  Smaller calls are a chain of latencies on a chip that is not full, and a thread moves one piece of each.
 #pragma once
 #include "k_rope.hpp"
 #include "mfma_util.hpp"
@@ -52,11 +52,15 @@ static_assert(sizeof(AppendParams) <= 4096, "kernel arguments are limited to 4 K
 
 // ROPE: a thread takes both pieces of a pair of partner pieces (D / 2 elements apart), so that a plane's
 // angle is worked out once.
-constexpr int append_units(bool rope) { return rope ? 2 : 4; }  // pieces (pairs of pieces) per thread
+constexpr int append_units(bool rope) { return rope ? 2 : 4; }  // pieces (pairs of pieces) per thread, beyond ...
+// ... this many pieces (pairs) per call; up to it one per thread.  Launches in a graph, 8 heads x 128, many / one per thread (us):
+//   bf16          8 rows 2.6 / 1.9, 512 3.0 / 2.2, 4096 (2^19 pieces) 6.4 / 5.9;  fp32 2048 (2^19) 6.4 / 5.7, 4096 9.0 / 9.5
+//   bf16, rotated 8 rows 4.2 / 2.8, 512 4.6 / 3.3, 4096 8.2 / 7.8;  fp32, rotated 8 rows 3.1 / 2.4, 4096 (2^19 pairs) 10.0 / 9.8
+constexpr long long kAppendThin = 1ll << 19;
 
-template <bool ROPE>
+template <bool ROPE, int UNR>
 __global__ __launch_bounds__(256) void k_append(AppendParams p) {
-  constexpr int UNR = append_units(ROPE), PART = ROPE ? 2 : 1;
+  constexpr int PART = ROPE ? 2 : 1;
   const uint32_t t = blockIdx.x * 256u + threadIdx.x;
   if (t < (uint32_t)p.n_rpatch) p.arena[p.rp_idx[t]] = p.rp_val[t];
   else if (t < (uint32_t)(p.n_rpatch + p.n_cpatch)) p.cidx[p.cp_idx[t - p.n_rpatch]] = p.cp_val[t - p.n_rpatch];
@@ -82,11 +86,30 @@ __global__ __launch_bounds__(256) void k_append(AppendParams p) {
     row[n] = (int)((min(unit(n), total - 1) >> unit_log2) / (uint32_t)p.Hkv);
     run[n] = p.runs[0];
   }
-  for (int k = 1; k < p.n_runs; ++k) {  // (the same run for every lane: scalar loads)
-    const AppendRun rk = p.runs[k];
+  if constexpr (UNR > 1) {  // (the chip is full: other waves cover the reads)
+    for (int k = 1; k < p.n_runs; ++k) {  // (the same run for every lane: scalar loads)
+      const AppendRun rk = p.runs[k];
 #pragma unroll
-    for (int n = 0; n < UNR; ++n)
-      if (row[n] >= rk.row0) run[n] = rk;
+      for (int n = 0; n < UNR; ++n)
+        if (row[n] >= rk.row0) run[n] = rk;
+    }
+  } else if (p.n_runs > 1) {
+    // Lane k has run k.  A wave's rows go up with its lanes, so it looks at the runs of its first to its last row only,
+    // one as a rule.  (All runs in turn, one dependent read each: 32 rotated rows of as many threads, 8 heads x 128
+    // bf16, an append after the other, 7.6 us; this way 4.6, which is the host's call.  The rows of sixteen requests,
+    // append and decode step: 64 -> 60.5 us.)
+    const int lane = threadIdx.x & 63;
+    const AppendRun mine = p.runs[min(lane, p.n_runs - 1)];
+    const int begins = lane < p.n_runs ? mine.row0 : INT32_MAX;
+    auto run_of = [&](int k) { return AppendRun{__builtin_amdgcn_readlane(mine.row0, k), __builtin_amdgcn_readlane(mine.req, k),
+                                                __builtin_amdgcn_readlane(mine.slot0, k), __builtin_amdgcn_readlane(mine.pos0, k)}; };
+    const int first = __popcll(__ballot(begins <= __builtin_amdgcn_readlane(row[0], 0))) - 1;  // (run 0 begins at row 0)
+    const int last = __popcll(__ballot(begins <= __builtin_amdgcn_readlane(row[0], 63))) - 1;
+    run[0] = run_of(first);
+    for (int k = first + 1; k <= last; ++k) {
+      const AppendRun rk = run_of(k);
+      if (row[0] >= rk.row0) run[0] = rk;
+    }
   }
 #pragma unroll
   for (int n = 0; n < UNR; ++n) {

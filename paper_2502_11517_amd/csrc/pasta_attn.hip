@@ -544,10 +544,11 @@ int launch_append(pasta_attn* h, int layer, int n_rows, const void* k_new, const
     p.n_rows = (int)n;
     p.k_new = (const u32x4*)((const char*)k_new + lo * row_bytes);
     p.v_new = (const u32x4*)((const char*)v_new + lo * row_bytes);
-    const long long threads = ((long long)n * units_per_row + append_units(rope) - 1) / append_units(rope);
-    const dim3 grid((unsigned)((threads + 255) / 256));
-    if (rope) k_append<true><<<grid, 256, 0, st>>>(p);
-    else k_append<false><<<grid, 256, 0, st>>>(p);
+    const long long units = (long long)n * units_per_row;
+    const int per = units <= kAppendThin ? 1 : append_units(rope);
+    const dim3 grid((unsigned)((units + 256 * per - 1) / (256 * per)));
+    if (rope) { if (per == 1) k_append<true, 1><<<grid, 256, 0, st>>>(p); else k_append<true, append_units(true)><<<grid, 256, 0, st>>>(p); }
+    else { if (per == 1) k_append<false, 1><<<grid, 256, 0, st>>>(p); else k_append<false, append_units(false)><<<grid, 256, 0, st>>>(p); }
     return hipGetLastError() == hipSuccess ? PASTA_OK : PASTA_E_DEVICE;
   };
   if (!append_as_list(h, runs.size(), n_rows, rope)) {

@@ -44,3 +44,22 @@ def test_rows_land_where_the_runs_say(kind, dtype, Hkv, D, page, rope):
     else:
         _check_pool(w, s, op)
     s.close()
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("more", [0, 1])
+def test_one_piece_per_thread_and_several(rope, more):
+    """The line between them, 2^19 pieces (pairs of pieces, rotated): fp32, 8 heads x 128, 2048 (4096) rows and one more."""
+    n = (4096 if rope else 2048) + more
+    w = W.Workload(name="thin", dtype="f32", Hq=8, Hkv=8, D=128, scale=1.0, seed=9, max_requests=1, pool_tokens=4160, max_streams=2)
+    w.ev_request, w.ev_stream, w.ev_parent, w.n_prefill = np.zeros(n, np.int32), np.zeros(n, np.int32), np.full(n, -1, np.int32), n
+    w.ev_request[100:300], w.max_requests = 1, 2
+    pos = np.arange(n, dtype=np.int32) + np.arange(n, dtype=np.int32) // 301  # (three runs, a dozen and more with the ids' jumps)
+    s, op = _session(w, rope_theta=THETA if rope else 0.0), OraclePool(w)
+    s.append_events(n, flags=B.APPEND_ROPE if rope else 0, positions=pos if rope else None)
+    op.append_events(n, positions=pos if rope else None, theta=THETA)
+    if rope:
+        _check_rope_pool(w, s, op, n)
+    else:
+        _check_pool(w, s, op)
+    s.close()
