@@ -299,7 +299,11 @@ typedef struct {
                                    prefix work-groups, private items, partial rows,
                                    tokens per prefix chunk, common-prefix tokens
                                    summed over requests, metadata bytes, first private
-                                   partial row} */
+                                   partial row}.  Of the form that the call takes: a small
+                                   step whose streams are read whole by one launch each has
+                                   one item per stream and no partial rows.  With any flag
+                                   but ROPE_Q, PLAN_ONLY among them, or with dbg_part_*, a
+                                   step is split and merged. */
   float *dbg_part_ml;           /* DEVICE [rows][2] fp32 or NULL (both or neither) */
   float *dbg_part_acc;          /* DEVICE [rows][head_dim] fp32 or NULL: when given, the step's split partials live
                                    here instead of in the workspace; rows = dbg_plan[3] of the same call planned with

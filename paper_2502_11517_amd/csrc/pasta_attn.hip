@@ -1051,8 +1051,8 @@ void* g_scratch_ptr[kMaxDevices] = {};
 bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, size_t n_reqs) {
   const pasta_attn_config& c = h->cfg;
   const int n = a->n_streams;
-  // what asks for a certain form, its partials or its plan's pieces gets the split one
-  if ((a->flags & ~(uint32_t)(PASTA_DECODE_ROPE_Q)) || a->dbg_part_ml || a->dbg_plan) return false;
+  // what asks for a certain form, its partials or a plan alone gets the split one
+  if ((a->flags & ~(uint32_t)(PASTA_DECODE_ROPE_Q)) || a->dbg_part_ml) return false;
   if (n * c.n_kv_heads > h->n_cus) return false;
   const bool rope = (a->flags & PASTA_DECODE_ROPE_Q) || (h->pending.active && h->pending.rope);
   int64_t most = c.dtype == PASTA_F32 ? (rope ? 96 : 112) : !rope || (n > 1 && c.head_dim == 128) ? 192 : 144;  // KiB
@@ -1518,7 +1518,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       a->dbg_plan[0] = tiles;
       a->dbg_plan[1] = n_prefix_wgs;
       a->dbg_plan[2] = n_items_total;
-      a->dbg_plan[3] = prefix_rows + priv_rows;
+      a->dbg_plan[3] = one ? 0 : prefix_rows + priv_rows;
       a->dbg_plan[4] = pc_total ? chunk_tokens : 0;
       a->dbg_plan[5] = pc_total;
       a->dbg_plan[6] = (int64_t)blob.size() * 4;

@@ -3,17 +3,38 @@ token, blocks of 16 and 32 tokens less and plus one, a round of eight waves and 
 and the first that it does not, rows of a deferred append, paged rows, rotary embedding, results in place of Q."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2502_11517_amd import binding as B
 from paper_2502_11517_amd import workloads as W
+from paper_2502_11517_amd.harness import to_device
 from test_gpu_parity import THETA, _check_pool, _check_rope_pool, _check_rope_step, _check_step, _out64, _session
 from util import OraclePool, check_close
 
 pytestmark = pytest.mark.gpu
 
 KINDS = [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)]
+
+
+def _most(dtype, D):
+    """Tokens of the longest list that one launch takes: 192 KiB of K and V per kv head in bf16, 112 in fp32."""
+    return (192 << 10) // (4 * D) if dtype == "bf16" else (112 << 10) // (8 * D)
+
+
+def _one_launch(w, s, step, lists=None, flags=0, position=None):
+    """Whether this step is taken by one launch: it then has no partial rows.  The plan is that of a real call, whose results
+    are those of the call without it, bit for bit."""
+    q = to_device(w.q(step), w.dtype, s.device)
+    out, again = torch.empty_like(q), torch.empty_like(q)
+    plan = np.zeros(8, np.int64)
+    s.h.decode_step(0, w.dec_request, w.dec_stream, q, out, lists=lists, flags=flags, position=position)
+    s.h.decode_step(0, w.dec_request, w.dec_stream, q, again, lists=lists, flags=flags, position=position, dbg_plan=plan)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.uint8), again.view(torch.uint8))
+    assert plan[3] or (plan[1] == 0 and plan[2] == w.n)
+    return plan[3] == 0
 
 
 @pytest.mark.parametrize("dtype,D", KINDS)
@@ -32,6 +53,7 @@ def test_edges_of_blocks_and_deferred_rows(dtype, D, G, Hkv, prefix, lengths, la
         keep.append(s._keep_rows)
         op.append_events(w.n_events(step))
         _check_step(w, s, op, step, explicit=bool(step))
+        assert _one_launch(w, s, step, lists=w.lists(step) if step else None) == (prefix + max(lengths) + step + 1 <= _most(dtype, D))
     _check_pool(w, s, op)
     s.close()
 
@@ -39,8 +61,8 @@ def test_edges_of_blocks_and_deferred_rows(dtype, D, G, Hkv, prefix, lengths, la
 @pytest.mark.parametrize("dtype,D", KINDS)
 @pytest.mark.parametrize("short", [0, 1])
 def test_the_longest_lists_and_the_first_that_are_split(dtype, D, short):
-    """The rule's line, from both sides: a stream that sees exactly the most tokens, and one more."""
-    most = (192 << 10) // (4 * D) if dtype == "bf16" else (112 << 10) // (8 * D)
+    """The rule's line, from both sides: a stream that sees exactly the most tokens, one more and two more."""
+    most = _most(dtype, D)
     w = W.single_request("line", dtype, 8, 2, D, 1.0, 22, most - 9 - short, [5, 9], "round_robin", steps=2, k_std=D ** -0.5)
     s, op = _session(w, kv_layout=B.HEAD_MAJOR), OraclePool(w, head_major=True)
     s.append_events(w.n_prefill)
@@ -49,21 +71,48 @@ def test_the_longest_lists_and_the_first_that_are_split(dtype, D, short):
         s.append_events(w.n_events(step))
         op.append_events(w.n_events(step))
         _check_step(w, s, op, step)
+        assert _one_launch(w, s, step) == (step < short)
     s.close()
 
 
+def _two_requests(dtype, D, page):
+    """Prefixes of 20 and 37 rows, three and two short threads; the newest three rows are two of one thread and one of another."""
+    w = W.Workload(name="small batch", dtype=dtype, Hq=8, Hkv=2, D=D, scale=1.0, seed=91, max_requests=2, max_streams=4, k_std=D ** -0.5)
+    w.dec_request, w.dec_stream = np.array([0, 0, 0, 1, 1], np.int32), np.array([1, 2, 3, 1, 2], np.int32)
+    rng = np.random.default_rng(91)
+    ev = []
+    for r, (prefix, lengths) in enumerate([(20, [5, 20, 11]), (37, [7, 16])]):
+        order = np.repeat(np.arange(len(lengths)), lengths)
+        rng.shuffle(order)
+        order = np.concatenate([order, [0, 0, 1]])
+        ev += [(r, 0, -1)] * prefix
+        ev += [(r, 1 + i, -1 if i in order[:k] else 0) for k, i in enumerate(order)]
+        w.anc_slots += [list(range(prefix)) for _ in lengths]
+    w.ev_request, w.ev_stream, w.ev_parent = (np.array(x, np.int32) for x in zip(*ev))
+    w.n_prefill = len(ev)
+    if page:
+        w.page_tokens, w.pages_per_request = page, 128 // page
+        w.n_phys_pages = 2 * w.pages_per_request + 3
+        w.page_table = rng.permutation(w.n_phys_pages)[:2 * w.pages_per_request].astype(np.int32).reshape(2, -1)
+    else:
+        w.pool_tokens = 128
+    return w
+
+
 @pytest.mark.parametrize("dtype,D", KINDS)
-@pytest.mark.parametrize("page", [8, 32])
-def test_paged_requests_with_rotated_rows(dtype, D, page):
-    w = W.config4(n_requests=2, seed=91, pmin=10, pmax=60, page_tokens=page, hq=8, hkv=2)
-    w.dtype, w.D, w.k_std = dtype, D, D ** -0.5
+@pytest.mark.parametrize("page", [0, 8, 32])
+@pytest.mark.parametrize("defer", [False, True])
+def test_requests_with_rotated_rows(dtype, D, page, defer):
+    """Deferred, the newest rows are turned inside the launch: one where its query stands, one a position ahead of it."""
+    w = _two_requests(dtype, D, page)
     pos = w.event_positions()
     s, op = _session(w, rope_theta=THETA), OraclePool(w)
     s.append_events(w.n_prefill - 3, flags=B.APPEND_ROPE, positions=pos)
-    s.append_events(w.n_prefill, flags=B.APPEND_ROPE | B.APPEND_DEFER, positions=pos)
+    s.append_events(w.n_prefill, flags=B.APPEND_ROPE | (B.APPEND_DEFER if defer else 0), positions=pos)
     op.append_events(w.n_prefill, positions=pos, theta=THETA)
     _check_rope_step(w, s, op, 0, pos)
     _check_rope_pool(w, s, op, w.n_prefill)
+    assert _one_launch(w, s, 0, flags=B.DECODE_ROPE_Q, position=w.q_positions(0))
     s.close()
 
 
