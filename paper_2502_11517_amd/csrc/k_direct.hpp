@@ -298,60 +298,44 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       }
     }
   };
-  // O^T += V^T P^T.  The weights of a bf16 block go in as three bf16 terms, cut off one behind the other, which hold
-  // all their 24 bits (each product is exact in the fp32 accumulator).  A term of 0 must not meet an infinite or NaN
-  // element of V: its product with zeros tells whether there is one, and the lower terms then see 0 in its place.
-  // k_one over 128 dims takes the steps that k_attn would take otherwise and rounds the weights to bf16 once, as that
-  // kernel does (and, as there, places past a list's end repeat its last token whatever that holds).  (8 streams over 4096 tokens of 64 dims: 10.6 us per layer with weights of one term, 11.0 with three;
-  // k_one over 128 dims, 300 + 3 x 20 .. 60 tokens, rotated: 10.7 and 11.1.)
+  // O^T += V^T P^T.  The weights of a bf16 block go in as bf16 terms, cut off one behind the other (each product is exact in
+  // the fp32 accumulator): three hold all their 24 bits, where the vector-ALU walker had fp32 weights.  Where k_attn would
+  // round them to bf16 it takes two: one alone left the results 0.4 % further off than k_attn's, since a weight's rounding
+  // depends on how far the maximum reaches (here 32 tokens of one wave).  Lower terms are 2^-126 at least: a term of 0
+  // would make NaN of an infinite element of V.
+  // (Per layer, 8 streams over 4096 tokens of 64 dims: one term 10.6 us, three 10.9; k_one over 128 dims, 300 + 3 x 20 .. 60
+  // tokens, rotated: one 10.7, two 10.8.)
   auto weigh = [&](const Blk& x, const f32x4 (&pr)[kNT][RT]) {
     if constexpr (sizeof(T) == 2) {
-      constexpr int kTerms = kExact ? 3 : 1;
+      constexpr int kTerms = kExact ? 3 : 2;
+      typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
       u32x4 pb[kTerms][RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float u = pr[e >> 1][rt][2 * (e & 1)], v = pr[e >> 1][rt][2 * (e & 1) + 1];
-          if constexpr (kTerms == 1) {
-            pb[0][rt][e] = pack_bf16x2(u, v);
-          } else {
 #pragma unroll
-            for (int n = 0; n < kTerms; ++n) {
-              const uint32_t iu = __float_as_uint(u), iv = __float_as_uint(v);
-              pb[n][rt][e] = __builtin_amdgcn_perm(iv, iu, 0x07060302u);
-              u -= __uint_as_float(iu & 0xffff0000u);
-              v -= __uint_as_float(iv & 0xffff0000u);
-            }
+          for (int n = 0; n < kTerms; ++n) {
+            const uint32_t iu = __float_as_uint(u), iv = __float_as_uint(v);
+            uint32_t term = __builtin_amdgcn_perm(iv, iu, 0x07060302u);
+            if (n > 0) term = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, term), u16x2{0x0080, 0x0080}));
+            pb[n][rt][e] = term;
+            u -= __uint_as_float(iu & 0xffff0000u);
+            v -= __uint_as_float(iv & 0xffff0000u);
           }
         }
-      u32x4 a[kMT];
-      f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < kMT; ++c) {
+        u32x4 a;
 #pragma unroll
         for (int e = 0; e < 4; ++e)  // element c of tokens 2 e and 2 e + 1
-          a[c][e] = __builtin_amdgcn_perm(x.v[2 * e + 1][0][c / 2], x.v[2 * e][0][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
-        if constexpr (kTerms > 1)
-          zero = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u}), zero, 0, 0, 0);
+          a[e] = __builtin_amdgcn_perm(x.v[2 * e + 1][0][c / 2], x.v[2 * e][0][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, pb[0][rt]), O[rt][c], 0, 0, 0);
+        for (int n = 0; n < kTerms; ++n)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb[n][rt]), O[rt][c], 0, 0, 0);
       }
-      if (kTerms > 1 && !__all(zero[0] + zero[1] + zero[2] + zero[3] == 0.f)) {
-#pragma unroll
-        for (int c = 0; c < kMT; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if ((a[c][e] & 0x7f80u) == 0x7f80u) a[c][e] &= 0xffff0000u;
-            if ((a[c][e] & 0x7f800000u) == 0x7f800000u) a[c][e] &= 0xffffu;
-          }
-      }
-#pragma unroll
-      for (int n = 1; n < kTerms; ++n)
-#pragma unroll
-        for (int c = 0; c < kMT; ++c)
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt) O[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[c]), __builtin_bit_cast(bf16x8, pb[n][rt]), O[rt][c], 0, 0, 0);
     } else {
 #pragma unroll
       for (int c = 0; c < kMT; ++c)
@@ -464,6 +448,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     if (rr >= R) continue;
     if constexpr (WHOLE) {
       const long long row = (long long)it.q_stream * p.Hq + g * G + rr;
+      if (l == 0.f) acc = f32x4{0.f, 0.f, 0.f, 0.f};  // (nothing weighed anything: 0 / 0, as behind the merge)
       const float o[4] = {acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l};
       if constexpr (sizeof(T) == 4) reinterpret_cast<f32x4*>(p.out)[row * kPR + pc] = f32x4{o[0], o[1], o[2], o[3]};
       else reinterpret_cast<u32x2*>(p.out)[row * kPR + pc] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
