@@ -131,7 +131,8 @@ typedef struct {
 
 /* Creates a handle.  With out == NULL ("query mode") only validates cfg and
  * writes the required size into cfg->workspace_bytes; pointers in cfg may be
- * NULL then.  Otherwise cfg->workspace_bytes must be at least that size.
+ * NULL then.  Otherwise cfg->workspace_bytes must be at least that size (it is
+ * the library's to change from build to build: query it).
  * Makes no HIP call that needs a device except one synchronous copy of the
  * page table into the workspace (paged mode).
  * Errors: E_INVAL (shape / NULL / misaligned / bad page table), E_CAPACITY
@@ -164,8 +165,7 @@ enum {
   PASTA_APPEND_ROPE = 4u         /* rotate every K row by position[i] on its way into the
                                     pool (needs position != NULL and rope_theta > 0; not
                                     with RESERVE_ONLY).  Combines with DEFER: the rows are then
-                                    turned by the small launch that a decode_step with
-                                    rotations puts ahead of its attention launch. */
+                                    turned by the decode_step that takes them along. */
 };
 
 typedef struct {
@@ -256,10 +256,10 @@ enum {
 /* Maintained lists on the device.  The lists that append_kv keeps per (request, stream) have a copy in the
  * workspace: every range with the running token count, and an index from token number to range.  Appends of up
  * to 32 rows bring the entries they change up to date in their own K1 launch; larger appends, forks and joins
- * mark a stream's copy for a rebuild, done (one stream-ordered copy) by the next decode step that reads it.  A
+ * mark a stream's copy for a rebuild, done (one stream-ordered launch) by the next decode step that reads it.  A
  * decode step in maintained mode whose plan would not fit the kernel arguments then sends one fixed-size record
- * per stream -- with the stream's newest range, which changes at every append, inline -- and the kernels find
- * ranges and derive the private work items themselves: the bytes a step sends do not grow with the lists, no
+ * per stream -- with the stream's newest range, which changes at every append, inline -- and a small launch finds
+ * the ranges and derives the private work items, once for all layers: the bytes a step sends do not grow with the lists, no
  * KV row and no list entry moves at a join (Section 3, "Efficiency").  Small plans ride in the kernel arguments
  * as before (no dependent loads on the way to the first K/V request).
  * Stream capture: a captured call records every word its launches read, so it may be replayed whatever later calls
@@ -289,7 +289,9 @@ typedef struct {
   const int32_t *range_stride;
   const void *q;                /* DEVICE [n][Hq][D], pool dtype */
   void *out;                    /* DEVICE [n][Hq][D], pool dtype (BF16: round to
-                                   nearest even from fp32 accumulators) */
+                                   nearest even from fp32 accumulators; the softmax
+                                   weights have fp32's bits, but over 128-wide BF16 heads
+                                   those of bf16, in small steps 16) */
   float *out_lse;               /* DEVICE [n][Hq] or NULL: natural-log sum-exp */
   int64_t *dbg_gather_offsets;  /* HOST [n+1] or NULL: out, CSR over the visited rows */
   int32_t *dbg_gather_rows;     /* DEVICE [sum |Vis(s)|] or NULL: out, the PHYSICAL

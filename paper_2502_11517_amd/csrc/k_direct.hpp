@@ -22,10 +22,11 @@
 // walker (k_private), whose cost was a chain of lane shuffles per row, which read a shared prefix once per
 // stream and could not take a deferred append along.  Append and decode step, walker -> this kernel (us):
 //   fp32, 4 query heads on 1 x 64, 256 + 2 x 16 tokens           28.7 ->  9.1
-//   fp32, 32 heads on 8 x 128, 1024 tokens + 4 x 32 .. 256       46.0 -> 12.8
-//   bf16, 32 heads on 8 x 64, 4096 tokens + 8 x 64 .. 512        27.9 -> 11.0
-// One block per wave in registers: a second one spilled (fp32 rows with 32 stacked queries need 256 registers
-// without it), and chunks are short enough here that most waves have only one.
+//   fp32, 32 heads on 8 x 128, 1024 tokens + 4 x 32 .. 256       45.8 -> 11.4
+//   bf16, 32 heads on 8 x 64, 4096 tokens + 8 x 64 .. 512        27.9 -> 10.9
+// One block per wave in registers: with 32 stacked queries fp32 rows need 254 of the 256 registers without a second
+// one, and chunks are short enough here that most waves have only one.  (The rotated forms over 128 dims, which work
+// out angles between the loads, do not fit: 26 registers spilled in bf16, 33 in fp32.)
 #pragma once
 #include "k_plan.hpp"
 #include "k_rope.hpp"
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
 // it is for short lists only, and every stream reads the shared prefix by itself (from its XCD's L2: work-group mod
 // Hkv is the kv head).  The copy of a deferred append's rows has work-groups of its own behind the others.
 // Append and decode step, split form -> this one (us): bf16, 8 kv heads x 128, 128 + 3 x 20 .. 60 tokens 10.0 -> 6.3, with
-// rotary embedding, 300 + 3 x 20 .. 60 tokens 13.8 -> 10.7; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
+// rotary embedding, 300 + 3 x 20 .. 60 tokens 13.8 -> 10.8; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
 constexpr int kOneWaves = 8;
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {

@@ -2,8 +2,8 @@
 // gets an estimated position id, because the asynchronous block before it has only a predicted
 // length (arxiv 2502.11517, Section 4, "Training a PASTA-SFT model"; appendix "Positional
 // Embedding"); the ids are the caller's, the rotation is the base model's.  It is applied to K
-// on its way into the pool (K1) and, ahead of a decode step's attention launch, to Q and to the
-// K rows of a deferred append (k_rope_prep).  Half-split planes over the whole head dim: plane
+// on its way into the pool (K1) and, in a decode step, to Q and to the K rows of a deferred append: in a small launch
+// ahead of k_attn (k_rope_prep), as they are loaded in k_direct and k_one.  Half-split planes over the whole head dim: plane
 // f = (x[f], x[f + D/2]) turns by position * theta^(-2f/D).
 //
 // Precision: position * frequency reaches tens of thousands of radians, so the product is

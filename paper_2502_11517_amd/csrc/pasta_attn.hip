@@ -1040,14 +1040,18 @@ void* g_scratch_ptr[kMaxDevices] = {};
 
 // Steps that k_one takes: every stream sees few enough bytes of K and V per kv head that one CU reads them sooner than the
 // merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  The lines lie where both
-// sides measure the same, 16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream (us, split / one):
+// sides measure the same for ONE stream, 16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream
+// (us, split / one).  With more streams the split form takes longer and one launch would be the shorter one beyond the line
+// too (8 streams, 450); the rule follows their number in one place only:
 //   bf16 x 128           1 stream: prefix 128 9.2 / 6.1, 300 8.2 / 7.6, 450 8.1 / 8.9;  8 streams: 450 12.2 / 9.6
 //   bf16 x 128, rotated  1 stream: 128 12.9 / 11.7, 300 12.7 / 13.0;  3 streams: 300 14.1 / 13.3, 450 14.0 / 14.9
+//                        (hence 144 KiB for one stream and 192 for more, over 128 dims)
 //   bf16 x 64            1 stream: 640 8.8 / 8.1, 900 8.9 / 9.4;  rotated 450 10.7 / 9.9, 640 10.8 / 11.0
 //   fp32 x 64            1 stream: 128 8.5 / 7.3, 300 8.6 / 9.5;  fp32 x 128: 32 9.0 / 7.0, 128 8.8 / 9.4
 // (fp32: 16-row tiles of four planes at a time, a quarter of them live: a work-group computes longer than it reads;
 // rotated: measured while every lane worked out its own planes' angles; with one table per work-group the one-launch
-// side takes 2.7 us less at 128 dims, so these lines lie on the safe side).
+// side takes 2.7 us less at 128 dims, so these lines lie on the safe side.  All before the weights of bf16 and the
+// sums of fp32 got back their bits, which takes 0.1 us of k_one's side and 0.2 to 0.3 of k_direct's.)
 bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, size_t n_reqs) {
   const pasta_attn_config& c = h->cfg;
   const int n = a->n_streams;
@@ -1543,7 +1547,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       p.v_pend = pd.v_new;
       p.pend_n = pd.n_rows;
       std::memcpy(p.pend_dst, pd.dst_rows, sizeof(p.pend_dst));
-      if (pd.rope) {  // turned by the small launch below, before the attention launch reads them
+      if (pd.rope) {  // turned by the small launch ahead of k_attn (below), or by k_direct / k_one as they load them
         p.pend_rope = 1;
         std::memcpy(p.pend_pos, pd.pos, sizeof(p.pend_pos));
       }

@@ -122,8 +122,8 @@ struct DecodeParams {
   int pend_n;           // rows of the deferred append (0: none)
   int32_t pend_dst[32]; // their physical rows
   int32_t pend_pos[32]; // their position ids, when pend_rope
-  // Rotary embedding: both flags are for the small launch ahead of the attention launch (k_rope_prep),
-  // which writes rotated copies; the attention launch then gets q / k_pend pointing at those.
+  // Rotary embedding.  Ahead of k_attn a small launch (k_rope_prep) writes rotated copies and the attention launch gets
+  // q / k_pend pointing at those; k_direct and k_one go by both flags themselves, as they load the rows.
   int rope_q;           // 1: Q rows are to be turned by their streams' position ids
   int pend_rope;        // 1: the deferred K rows are still unrotated (PASTA_APPEND_ROPE), to be turned by pend_pos
   int32_t s_items[32];  // single_req with <= 16 streams: stream i's private items are
@@ -132,7 +132,7 @@ struct DecodeParams {
   const DevItem* items;       // a plan kept on the device (k_plan): the private work items and, priv_chunk entries per
   const int32_t* codes;       // item, the row of every token (physical row, or -(1 + row) of a deferred append); else null
   int priv_chunk;             // tokens per private work item
-  const double* rope_tab;  // theta^(-2f/D) / (2 pi), f < D/2 (device), for k_rope_prep
+  const double* rope_tab;  // theta^(-2f/D) / (2 pi), f < D/2 (device), for whoever turns rows
   int single_req;       // 1: the call holds one request; its DevReq is req0 and stream i of
   DevReq req0;          //    the call is stacked-row block i (no table look-ups on the way
                         //    to the first K/V load)

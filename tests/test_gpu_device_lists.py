@@ -27,8 +27,8 @@ def _plan(s, w, flags=0):
 @pytest.mark.parametrize("cfg", ["config1", "config2", "config4", "config5"])
 def test_single_step_configs_from_the_device_lists(cfg):
     """Lists rebuilt from the mirror after the prefill (bulk), then read by the kernels: the matrix-core
-    kernel (configs 2, 4, 5: strided, scattered and nested-fork lists, contiguous and paged pools) and
-    the vector-ALU kernel (config 1, fp32)."""
+    kernel (configs 2, 4, 5: strided, scattered and nested-fork lists, contiguous and paged pools), the one
+    that takes its operands straight from memory (config 1, fp32) and the vector-ALU walker."""
     w = getattr(W, cfg)()
     s = _session(w, kv_layout=B.HEAD_MAJOR)
     op = OraclePool(w, head_major=True).append_events(w.n_prefill)

@@ -750,7 +750,7 @@ def test_rope_at_append_and_on_queries_config3_loop(layout):
                                                    ("bf16", 8, 2, 64, 0), ("bf16", 16, 4, 128, B.DECODE_NO_MFMA),
                                                    ("bf16", 64, 8, 128, 0)])
 def test_rope_on_the_other_paths(dtype, Hq, Hkv, D, flags):
-    """fp32 pools, D = 64 and the vector-ALU walker take Q from a rotated copy (k_rope_q); G = 8 on
+    """fp32 pools and D = 64 turn Q as they load it, the vector-ALU walker takes it from a rotated copy (k_rope_prep); G = 8 on
     the matrix-core path; random interleave, so many short ranges."""
     w = W.single_request("rope", dtype, Hq, Hkv, D, D ** -0.5, 77, 300, [40, 3, 129, 77], "random")
     pos = w.event_positions()
