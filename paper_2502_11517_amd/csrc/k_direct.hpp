@@ -299,6 +299,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       }
     }
   };
+
   // O^T += V^T P^T.  The weights of a bf16 block go in as bf16 terms, cut off one behind the other (each product is exact in
   // the fp32 accumulator): three hold all their 24 bits, where the vector-ALU walker had fp32 weights.  Where k_attn would
   // round them to bf16 it takes two: one alone left the results 0.4 % further off than k_attn's, since a weight's rounding
