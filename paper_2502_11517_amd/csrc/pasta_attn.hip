@@ -32,6 +32,7 @@ constexpr int kRing = 8;                  // metadata staging buffers in flight
 constexpr int64_t kPlanCodesMax = (int64_t)1 << 22;  // most private tokens of a plan that is kept on the device (16 MiB of row codes;
                                                      // more where the streams of a no-alloc call can have more between them)
 constexpr int kOneTokens = 1024;          // most tokens of a work-group of k_one (it holds their addresses at once)
+constexpr int kManyChunk = 512;           // tokens: chunks of several requests' prefixes are not cut down below this
 constexpr int kNumCUs = 256;              // MI355X; planning default until the device has been asked
 constexpr int kTargetPrefixWgs = 768;     // most shared-prefix work-groups budgeted for
 
@@ -1324,6 +1325,10 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     int64_t priv_chunk = kPrivChunk, chunk_tokens = kTile;
     if (matrix) {
       chunk_tokens = std::max<int64_t>(kTile, pc_weighted * Hkv / h->n_cus / kTile * kTile);
+      // Several requests: their prefixes do not end with a chunk, and a launch ends with its longest items, so two thirds of that
+      // (16 requests of 256 .. 4096 tokens, 1 .. 8 streams, pages of 16, append and decode step: chunks of 1024 tokens 60.3 us,
+      // 768 56.1, 512 57.1, 384 59.6, 256 64.3; one request of 8192: 256 17.3, 128 20.8).
+      if (!wide && reqs.size() > 1 && chunk_tokens >= kManyChunk) chunk_tokens = std::max<int64_t>(kManyChunk, chunk_tokens * 2 / 3 / kTile * kTile);
       priv_chunk = wide ? 256 : 128;  // (beside the long wide work-groups the private items get one slot per CU: longer items keep more in flight there)
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
       if (one) priv_chunk = kOneTokens;  // a stream's whole list
