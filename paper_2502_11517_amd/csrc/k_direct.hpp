@@ -60,7 +60,14 @@ template <int D, int RT, int NW> struct DirLds {
   float mw[NW][16 * RT], lw[NW][16 * RT];
   uint32_t off[kDirWin];
   DevRange ranges[kGatherMax];
-  float2 turn[D / 2];  // (k_one) the angles of the stream's new token
+};
+// ... and of k_one: the rows that are turned once per work-group (a stream's query rows; behind them its own deferred row)
+// and, per wave, one more deferred row.
+constexpr int kMostHeads = 8;  // query heads per kv head
+template <typename T, int D, int NW, bool ROPE> struct OneLds : DirLds<D, 1, NW> {};
+template <typename T, int D, int NW> struct OneLds<T, D, NW, true> : DirLds<D, 1, NW> {
+  static constexpr int kPieces = D * (int)sizeof(T) / 16;
+  u32x4 turned[kMostHeads + 1][kPieces + 1], other[NW][kPieces];
 };
 
 // Turns the planes of a row whose pieces 4 kk + q are spread over the quarters' lanes: piece kk and piece
@@ -86,27 +93,23 @@ __device__ __forceinline__ void rope_lane(u32x4 (&x)[NP], int q, int pos, const 
   }
 }
 
-// The same by angles already worked out: plane f turns by (cos, sin) = cs[f].
-template <typename T, int NP>
-__device__ __forceinline__ void rope_lane_by(u32x4 (&x)[NP], int q, const float2* cs) {
-#pragma unroll
-  for (int kk = 0; kk < NP / 2; ++kk) {
-    const int f0 = (4 * kk + q) * (16 / (int)sizeof(T));
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t a = x[kk][w], b = x[kk + NP / 2][w];
-      if constexpr (sizeof(T) == 4) {
-        const float2 t = cs[f0 + w];
-        const float u = __uint_as_float(a), v = __uint_as_float(b);
-        x[kk][w] = __float_as_uint(u * t.x - v * t.y);
-        x[kk + NP / 2][w] = __float_as_uint(v * t.x + u * t.y);
-      } else {
-        const float2 t0 = cs[f0 + 2 * w], t1 = cs[f0 + 2 * w + 1];
-        const float u0 = bf16_lo(a), u1 = bf16_hi(a), v0 = bf16_lo(b), v1 = bf16_hi(b);
-        x[kk][w] = (uint32_t)f32_to_bf16_rne(u0 * t0.x - v0 * t0.y) | ((uint32_t)f32_to_bf16_rne(u1 * t1.x - v1 * t1.y) << 16);
-        x[kk + NP / 2][w] = (uint32_t)f32_to_bf16_rne(v0 * t0.x + u0 * t0.y) | ((uint32_t)f32_to_bf16_rne(v1 * t1.x + u1 * t1.y) << 16);
-      }
-    }
+// Plane f of a row, turned by (c, sn), on its way from `src` to LDS: lane f < D / 2 of a wave.
+template <typename T> struct Plane { T a, b; };
+template <typename T, int D>
+__device__ __forceinline__ Plane<T> plane_load(const char* src, int f) {
+  return {reinterpret_cast<const T*>(src)[f], reinterpret_cast<const T*>(src)[f + D / 2]};
+}
+template <typename T, int D>
+__device__ __forceinline__ void plane_store(u32x4* dst, int f, const Plane<T>& x, float c, float sn) {
+  typedef T __attribute__((may_alias)) elem;
+  elem* const out = reinterpret_cast<elem*>(dst);
+  if constexpr (sizeof(T) == 4) {
+    out[f] = x.a * c - x.b * sn;
+    out[f + D / 2] = x.b * c + x.a * sn;
+  } else {
+    const float u = __uint_as_float((uint32_t)x.a << 16), v = __uint_as_float((uint32_t)x.b << 16);
+    out[f] = f32_to_bf16_rne(u * c - v * sn);
+    out[f + D / 2] = f32_to_bf16_rne(v * c + u * sn);
   }
 }
 
@@ -117,6 +120,8 @@ struct DirItem {
   const int32_t* req_streams;  // shared-prefix item: the request's streams (null: stack block s is stream s)
   int row0;                    // ... its first stacked row
   int q_stream;                // private item: its stream
+  int q_pos;                   // (WHOLE) its query's position id,
+  int own_row, own_pos;        // the row of its newest token in a deferred append that is to be turned (-1: none), that one's id
 };
 
 // One item, once code_of(j) -- the address code of token j -- can be asked for.  GATHER: the rows are the G
@@ -150,18 +155,31 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     for (int kk = 0; kk < kNP; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4*>(src + kk * 64);
     qpos[rt] = 0;
     if constexpr (ROPE) {
-      if (p.rope_q) qpos[rt] = reinterpret_cast<const DevStream*>(meta + p.off_streams)[s].pos;
+      if (!WHOLE && p.rope_q) qpos[rt] = reinterpret_cast<const DevStream*>(meta + p.off_streams)[s].pos;
     }
   }
 
-  // A whole stream's rows are turned by one position: its angles are worked out once per work-group, a plane per
-  // thread.  (Every lane for its own planes: 13.4 us per layer
-  // for 300 + 3 x 20 .. 60 tokens of 128 dims, append and decode step; this way 10.7.)
+  // A whole stream's rows are turned once per work-group, a plane per lane, and go to the waves through LDS: the last wave
+  // turns the stream's newest row, the others the query rows.  Requested here, turned behind the requests for the rows.
+  // A launch this short runs its code once, so what the turning costs is code to fetch as much as arithmetic: with every
+  // lane turning the planes of its operand registers in place, by a table of angles and, for deferred rows, by angles of
+  // its own, 300 + 3 x 20 .. 60 tokens, 16 layers of append and decode step, took 172.8 us; this way 139.2.
+  // (For the same reason a second copy of the block's code, with two blocks requested together, lost: 189.)
+  constexpr int kUnits = ROPE && WHOLE ? (kMostHeads + NW - 2) / (NW - 1) : 1;
+  const int plane = lane & (D / 2 - 1);
+  Plane<T> unit[kUnits];
+  double per_pos = 0.0;
+  const bool own = ROPE && WHOLE && it.own_row >= 0;
+  const uint32_t own_code = kPendBit | (uint32_t)((it.own_row * p.Hkv + g) * kPieceRow);
   if constexpr (ROPE && WHOLE) {
-    if (p.rope_q && tid < D / 2) {
-      float2 t;
-      rope_cos_sin<sizeof(T) == 2>(p.rope_tab, tid, qpos[0], t.x, t.y);
-      lds.turn[tid] = t;
+    per_pos = p.rope_tab[plane];
+    if (w == NW - 1) {
+      if (own) unit[0] = plane_load<T, D>(reinterpret_cast<const char*>(p.k_pend) + (long long)(it.own_row * p.Hkv + g) * (D * sizeof(T)), plane);
+    } else if (p.rope_q) {
+#pragma unroll
+      for (int n = 0; n < kUnits; ++n)
+        if (w + n * (NW - 1) < R)
+          unit[n] = plane_load<T, D>(reinterpret_cast<const char*>(p.q) + (long long)(it.q_stream * p.Hq + g * G + w + n * (NW - 1)) * (D * sizeof(T)), plane);
     }
   }
 
@@ -216,15 +234,32 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         for (int t = 0; t < kNT; ++t) {
           const uint32_t code = lds.off[b * kTok + 16 * t + i];
           if (__builtin_amdgcn_ballot_w64((int)code < 0)) {
-            const int row = (int)((code & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
-            bool by_row = (int)code < 0;
-            if constexpr (WHOLE) {  // the stream's new row stands, as a rule, where its query does
-              if (by_row && p.rope_q && pend_pos_of(p)[row] == qpos[0]) {
-                rope_lane_by<T, kNP>(x.k[t], q, lds.turn);
-                by_row = false;
+            if constexpr (WHOLE) {
+              if (own && code == own_code) {  // it stands in LDS by now
+#pragma unroll
+                for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = lds.turned[kMostHeads][4 * kk + q];
               }
+              // rows that others have just appended, one at a time
+              for (uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64((int)code < 0 && !(own && code == own_code)) & 0xffffu; m; m &= m - 1) {
+                const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)code, __builtin_ctz(m));
+                const int row = (int)((one & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
+                const Plane<T> y = plane_load<T, D>(kpend + ((unsigned long long)(one & ~kPendBit) << 4), plane);
+                float c, sn;
+                rope_cos_sin_by<sizeof(T) == 2>(per_pos, pend_pos_of(p)[row], c, sn);
+                if (lane < D / 2) plane_store<T, D>(lds.other[w], plane, y, c, sn);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (code == one) {
+#pragma unroll
+                  for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = lds.other[w][4 * kk + q];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+              }
+            } else {
+              const int row = (int)((code & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
+              if ((int)code < 0) rope_lane<T, kNP>(x.k[t], q, pend_pos_of(p)[row], p.rope_tab);
             }
-            if (by_row) rope_lane<T, kNP>(x.k[t], q, pend_pos_of(p)[row], p.rope_tab);
           }
         }
       }
@@ -362,22 +397,39 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     if (w0) lds_barrier();  // everybody is done with the last window's codes
     for (int j = tid; j < nb * kTok; j += NW * 64) lds.off[j] = code_of(w0 + min(j, n_here - 1));  // past the end: the last token again
     lds_barrier();
-    if (w >= nb) continue;
-    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
-    Blk A;
-    f32x4 pr[kNT][RT];
     auto turn_q = [&]() {
-      if constexpr (ROPE) {
+      if constexpr (ROPE && WHOLE) {  // (by all waves, with a block or without, once)
+        float c, sn;
+        rope_cos_sin_by<sizeof(T) == 2>(per_pos, w == NW - 1 ? it.own_pos : it.q_pos, c, sn);
+        if (lane < D / 2) {
+          if (w == NW - 1) {
+            if (own) plane_store<T, D>(lds.turned[kMostHeads], plane, unit[0], c, sn);
+          } else if (p.rope_q) {
+#pragma unroll
+            for (int n = 0; n < kUnits; ++n)
+              if (w + n * (NW - 1) < R) plane_store<T, D>(lds.turned[w + n * (NW - 1)], plane, unit[n], c, sn);
+          }
+        }
+        lds_barrier();
+        if (p.rope_q) {
+#pragma unroll
+          for (int kk = 0; kk < kNP; ++kk) qf[0][kk] = lds.turned[i < R ? i : 0][4 * kk + q];
+        }
+      } else if constexpr (ROPE) {
         if (p.rope_q && !q_turned) {
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) {
-            if constexpr (WHOLE) rope_lane_by<T, kNP>(qf[rt], q, lds.turn);
-            else rope_lane<T, kNP>(qf[rt], q, qpos[rt], p.rope_tab);
-          }
+          for (int rt = 0; rt < RT; ++rt) rope_lane<T, kNP>(qf[rt], q, qpos[rt], p.rope_tab);
         }
         q_turned = true;
       }
     };
+    if (w >= nb) {
+      if constexpr (WHOLE) turn_q();
+      continue;
+    }
+    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
+    Blk A;
+    f32x4 pr[kNT][RT];
     load_k(A, w);
     load_v(A, w);
     turn_q();
@@ -605,33 +657,51 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
 // What bounds it: the rate at which one CU takes in the rows (eight waves with a block each in flight), which is why
 // it is for short lists only, and every stream reads the shared prefix by itself (from its XCD's L2: work-group mod
 // Hkv is the kv head).  The copy of a deferred append's rows has work-groups of its own behind the others.
-// Append and decode step, split form -> this one (us): bf16, 8 kv heads x 128, 128 + 3 x 20 .. 60 tokens 10.0 -> 6.3, with
-// rotary embedding, 300 + 3 x 20 .. 60 tokens 13.8 -> 10.8; 8 streams over 300 tokens 11.7 -> 8.2; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
+// Append and decode step, split form -> this one (us): bf16, 8 kv heads x 128, 128 + 3 x 20 .. 60 tokens 10.0 -> 6.4, with
+// rotary embedding, 300 + 3 x 20 .. 60 tokens 13.8 -> 8.6; 8 streams over 300 tokens 11.7 -> 8.0; bf16 x 64, 3 streams over 300 tokens 8.9 -> 6.4.
 constexpr int kOneWaves = 8;
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
-  __shared__ DirLds<D, 1, kOneWaves> lds;
+  __shared__ OneLds<T, D, kOneWaves, ROPE> lds;
   const int tid = threadIdx.x;
   const int n_rows_wgs = p.n_mfma_items * p.Hkv;  // (one item per stream)
   if ((int)blockIdx.x >= n_rows_wgs) {
     direct_copy_pending<T, D, ROPE>(p, (int)blockIdx.x - n_rows_wgs, (int)gridDim.x - n_rows_wgs);
     return;
   }
-  const int32_t* meta = meta_of(p);
+  // The plan always rides in the kernel arguments here (small_step): its records are read with scalar loads
+  // (8 kv heads x 128, 128 .. 300 + 1 .. 8 x 20 .. 60 tokens: 0.3 us of 6.4 .. 8.4).
+  typedef const int32_t __attribute__((address_space(4))) * words;
+  typedef const char __attribute__((address_space(4))) * kernarg_ptr;
+  const words meta = (words)((kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr() + __builtin_offsetof(DecodeParams, inline_meta));
   const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x / p.Hkv);
-  const DevItem di = reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
-  const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream];
+  const words di = meta + p.off_items + item * (int)(sizeof(DevItem) / 4);
+  auto item_word = [&](size_t byte) { return di[byte / 4]; };
+  const int stream = item_word(offsetof(DevItem, stream)), gather_pos = item_word(offsetof(DevItem, gather_pos));
+  const words ds = meta + p.off_streams + stream * (int)(sizeof(DevStream) / 4);
+  const int req = ds[offsetof(DevStream, req) / 4], pend0 = ds[offsetof(DevStream, pend0) / 4], pend_src0 = ds[offsetof(DevStream, pend_src0) / 4];
   DirItem it;
   it.req_streams = nullptr;
   it.row0 = 0;
   it.part_row0 = 0;
   it.g = __builtin_amdgcn_readfirstlane((int)blockIdx.x % p.Hkv);
-  it.n_tok = __builtin_amdgcn_readfirstlane(di.tok_count);
+  it.n_tok = item_word(offsetof(DevItem, tok_count));
   it.R = p.Hq / p.Hkv;
-  it.q_stream = __builtin_amdgcn_readfirstlane(di.stream);
-  const int nr = __builtin_amdgcn_readfirstlane(di.n_ranges);
-  const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges) + di.range_first;
-  for (int k = tid; k < nr; k += kOneWaves * 64) lds.ranges[k] = ranges[k];
+  it.q_stream = stream;
+  it.q_pos = ds[offsetof(DevStream, pos) / 4];
+  const int nr = item_word(offsetof(DevItem, n_ranges));
+  const words ranges = meta + p.off_ranges + item_word(offsetof(DevItem, range_first)) * (int)(sizeof(DevRange) / 4);
+  it.own_row = -1;
+  it.own_pos = 0;
+  if (ROPE && p.pend_rope) {
+    const words newest = ranges + 4 * (nr - 1);
+    const int slot = newest[0] + (it.n_tok - 1 - newest[3]) * newest[2];
+    if (slot >= pend0) {
+      it.own_row = pend_src0 + (slot - pend0);
+      it.own_pos = pend_pos_of(p)[it.own_row];
+    }
+  }
+  for (int k = tid; k < nr; k += kOneWaves * 64) lds.ranges[k] = DevRange{ranges[4 * k], ranges[4 * k + 1], ranges[4 * k + 2], ranges[4 * k + 3]};
   __syncthreads();
   const bool report = p.dbg_rows && it.g == 0;
   auto code_of = [&](int j) -> uint32_t {  // the last range with cum <= j
@@ -642,11 +712,11 @@ __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
     }
     int phys;
     const int slot = lds.ranges[lo].start + (j - lds.ranges[lo].cum) * lds.ranges[lo].stride;
-    const uint32_t code = direct_code<T, D>(p, st.req, slot, it.g, st.pend0, st.pend_src0, phys);
-    if (report) p.dbg_rows[di.gather_pos + j] = phys;
+    const uint32_t code = direct_code<T, D>(p, req, slot, it.g, pend0, pend_src0, phys);
+    if (report) p.dbg_rows[gather_pos + j] = phys;
     return code;
   };
-  direct_rows<T, D, 1, kOneWaves, true, ROPE, true>(p, lds, meta, it, code_of);
+  direct_rows<T, D, 1, kOneWaves, true, ROPE, true>(p, lds, nullptr, it, code_of);
 }
 
 }  // namespace pasta

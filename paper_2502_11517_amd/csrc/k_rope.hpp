@@ -18,8 +18,8 @@ namespace pasta {
 // FAST: the hardware's v_cos_f32 / v_sin_f32 (argument in revolutions), good to about 1e-6
 // absolute -- ample under a bf16 rounding.  Otherwise the library's sincospi (about 1 ulp).
 template <bool FAST>
-__device__ __forceinline__ void rope_cos_sin(const double* tab, int f, int pos, float& c, float& s) {
-  const double rev = (double)pos * tab[f];
+__device__ __forceinline__ void rope_cos_sin_by(double per_pos, int pos, float& c, float& s) {  // per_pos: revolutions per position
+  const double rev = (double)pos * per_pos;
   const float fr = (float)(rev - __builtin_floor(rev));
   if constexpr (FAST) {
     c = __builtin_amdgcn_cosf(fr);
@@ -27,6 +27,10 @@ __device__ __forceinline__ void rope_cos_sin(const double* tab, int f, int pos, 
   } else {
     sincospif(2.f * fr, &s, &c);
   }
+}
+template <bool FAST>
+__device__ __forceinline__ void rope_cos_sin(const double* tab, int f, int pos, float& c, float& s) {
+  rope_cos_sin_by<FAST>(tab[f], pos, c, s);
 }
 
 // One 16-byte piece of a bf16 head row (8 elements, first plane index f0), `par` the piece D/2

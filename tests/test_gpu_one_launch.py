@@ -116,6 +116,25 @@ def test_requests_with_rotated_rows(dtype, D, page, defer):
     s.close()
 
 
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("G", [1, 2, 8])
+@pytest.mark.parametrize("deferred", [0, 1, 9])
+def test_rotated_rows_of_narrow_and_wide_groups(dtype, D, G, deferred):
+    """Query rows for some of the waves, for each, and for more than there are; a stream's newest rows deferred, nine of them."""
+    w = _two_requests(dtype, D, 0)
+    w.Hq = w.Hkv * G
+    pos = w.event_positions()
+    s, op = _session(w, rope_theta=THETA), OraclePool(w)
+    s.append_events(w.n_prefill - deferred, flags=B.APPEND_ROPE, positions=pos)
+    if deferred:
+        s.append_events(w.n_prefill, flags=B.APPEND_ROPE | B.APPEND_DEFER, positions=pos)
+    op.append_events(w.n_prefill, positions=pos, theta=THETA)
+    _check_rope_step(w, s, op, 0, pos)
+    _check_rope_pool(w, s, op, w.n_prefill)
+    assert _one_launch(w, s, 0, flags=B.DECODE_ROPE_Q, position=w.q_positions(0))
+    s.close()
+
+
 @pytest.mark.parametrize("shift", ["in place of q", "over part of q", "two elements off"])
 def test_results_that_lie_over_the_queries(shift):
     """`out` on top of `q`, half over it, or not on a 16-byte boundary gives what separate buffers give (the last two in
