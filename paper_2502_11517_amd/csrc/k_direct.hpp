@@ -93,26 +93,6 @@ __device__ __forceinline__ void rope_lane(u32x4 (&x)[NP], int q, int pos, const 
   }
 }
 
-// Plane f of a row, turned by (c, sn), on its way from `src` to LDS: lane f < D / 2 of a wave.
-template <typename T> struct Plane { T a, b; };
-template <typename T, int D>
-__device__ __forceinline__ Plane<T> plane_load(const char* src, int f) {
-  return {reinterpret_cast<const T*>(src)[f], reinterpret_cast<const T*>(src)[f + D / 2]};
-}
-template <typename T, int D>
-__device__ __forceinline__ void plane_store(u32x4* dst, int f, const Plane<T>& x, float c, float sn) {
-  typedef T __attribute__((may_alias)) elem;
-  elem* const out = reinterpret_cast<elem*>(dst);
-  if constexpr (sizeof(T) == 4) {
-    out[f] = x.a * c - x.b * sn;
-    out[f + D / 2] = x.b * c + x.a * sn;
-  } else {
-    const float u = __uint_as_float((uint32_t)x.a << 16), v = __uint_as_float((uint32_t)x.b << 16);
-    out[f] = f32_to_bf16_rne(u * c - v * sn);
-    out[f + D / 2] = f32_to_bf16_rne(v * c + u * sn);
-  }
-}
-
 // What an item's rows are made of.
 struct DirItem {
   int n_tok, R, g;
@@ -174,12 +154,12 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   if constexpr (ROPE && WHOLE) {
     per_pos = p.rope_tab[plane];
     if (w == NW - 1) {
-      if (own) unit[0] = plane_load<T, D>(reinterpret_cast<const char*>(p.k_pend) + (long long)(it.own_row * p.Hkv + g) * (D * sizeof(T)), plane);
+      if (own) unit[0] = plane_load<T>(reinterpret_cast<const char*>(p.k_pend) + (long long)(it.own_row * p.Hkv + g) * (D * sizeof(T)), plane, D / 2);
     } else if (p.rope_q) {
 #pragma unroll
       for (int n = 0; n < kUnits; ++n)
         if (w + n * (NW - 1) < R)
-          unit[n] = plane_load<T, D>(reinterpret_cast<const char*>(p.q) + (long long)(it.q_stream * p.Hq + g * G + w + n * (NW - 1)) * (D * sizeof(T)), plane);
+          unit[n] = plane_load<T>(reinterpret_cast<const char*>(p.q) + (long long)(it.q_stream * p.Hq + g * G + w + n * (NW - 1)) * (D * sizeof(T)), plane, D / 2);
     }
   }
 
@@ -243,10 +223,10 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
               for (uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64((int)code < 0 && !(own && code == own_code)) & 0xffffu; m; m &= m - 1) {
                 const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)code, __builtin_ctz(m));
                 const int row = (int)((one & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
-                const Plane<T> y = plane_load<T, D>(kpend + ((unsigned long long)(one & ~kPendBit) << 4), plane);
+                const Plane<T> y = plane_load<T>(kpend + ((unsigned long long)(one & ~kPendBit) << 4), plane, D / 2);
                 float c, sn;
                 rope_cos_sin_by<sizeof(T) == 2>(per_pos, pend_pos_of(p)[row], c, sn);
-                if (lane < D / 2) plane_store<T, D>(lds.other[w], plane, y, c, sn);
+                if (lane < D / 2) plane_store<T>(lds.other[w], plane, D / 2, y, c, sn);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 if (code == one) {
@@ -403,11 +383,11 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         rope_cos_sin_by<sizeof(T) == 2>(per_pos, w == NW - 1 ? it.own_pos : it.q_pos, c, sn);
         if (lane < D / 2) {
           if (w == NW - 1) {
-            if (own) plane_store<T, D>(lds.turned[kMostHeads], plane, unit[0], c, sn);
+            if (own) plane_store<T>(lds.turned[kMostHeads], plane, D / 2, unit[0], c, sn);
           } else if (p.rope_q) {
 #pragma unroll
             for (int n = 0; n < kUnits; ++n)
-              if (w + n * (NW - 1) < R) plane_store<T, D>(lds.turned[w + n * (NW - 1)], plane, unit[n], c, sn);
+              if (w + n * (NW - 1) < R) plane_store<T>(lds.turned[w + n * (NW - 1)], plane, D / 2, unit[n], c, sn);
           }
         }
         lds_barrier();

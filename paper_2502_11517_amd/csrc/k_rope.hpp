@@ -82,33 +82,51 @@ __device__ __forceinline__ uint4 rope_row_piece(const uint4* src, int piece, int
   return make_uint4(out[0], out[1], out[2], out[3]);
 }
 
+// Plane f of a row of 2 * half elements, turned by (c, sn) on its way from `src` to `dst`: a lane per plane.
+template <typename T> struct Plane { T a, b; };
+template <typename T>
+__device__ __forceinline__ Plane<T> plane_load(const void* src, int f, int half) {
+  return {static_cast<const T*>(src)[f], static_cast<const T*>(src)[f + half]};
+}
+template <typename T>
+__device__ __forceinline__ void plane_store(void* dst, int f, int half, const Plane<T>& x, float c, float sn) {
+  typedef T __attribute__((may_alias)) elem;
+  elem* const out = static_cast<elem*>(dst);
+  if constexpr (sizeof(T) == 4) {
+    out[f] = x.a * c - x.b * sn;
+    out[f + half] = x.b * c + x.a * sn;
+  } else {
+    const float u = __uint_as_float((uint32_t)x.a << 16), v = __uint_as_float((uint32_t)x.b << 16);
+    out[f] = f32_to_bf16_rne(u * c - v * sn);
+    out[f + half] = f32_to_bf16_rne(v * c + u * sn);
+  }
+}
+
 // What a decode step with a k_attn launch has to turn before it, in one small launch: the Q rows
 // (into q_rot, [n][Hq][D]) and the K rows of a deferred rotating append (into k_rot,
 // [pend_n][Hkv][D]; the attention launch then reads and copies those instead of the caller's
-// unrotated rows).  One thread per 16-byte piece; pieces [0, n_q_pieces) are Q's.  Rotating
+// unrotated rows).  A lane per plane, rows [0, n_q_rows) are Q's: the launch is a chain of a position, a row and a store, and
+// runs its code once, so little code and many lanes (a lane per 16-byte piece, eight angles each: 8 streams over 4096 tokens, append and decode step, 17.4 us; this way 16.1;
+// 3 over 1024 15.8 and 15.4, 8 over 8192 19.8 and 18.9).  Rotating
 // inside the attention kernel was tried first and costs more than this launch: with loads that
 // go straight into LDS in flight the compiler makes every other wait a wait for all of them.
-// DecodeParams comes first (the metadata may ride inside it).
-__global__ __launch_bounds__(256) void k_rope_prep(DecodeParams p, uint4* q_rot, uint4* k_rot, int pieces_per_head,
-                                                  int is_f32, long long n_q_pieces) {
-  const long long n_k_pieces = p.pend_rope ? (long long)p.pend_n * p.Hkv * pieces_per_head : 0;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_q_pieces + n_k_pieces) return;
-  if (t < n_q_pieces) {
-    const int piece = (int)(t % pieces_per_head);
-    const long long row = t / pieces_per_head;  // (stream, query head)
-    const int s = (int)(row / p.Hq);
-    const DevStream* streams = reinterpret_cast<const DevStream*>(meta_of(p) + p.off_streams);
-    const uint4* src = reinterpret_cast<const uint4*>(p.q) + row * pieces_per_head;
-    q_rot[t] = rope_row_piece(src, piece, pieces_per_head, is_f32 != 0, streams[s].pos, p.rope_tab);
-  } else {
-    const long long u = t - n_q_pieces;
-    const int piece = (int)(u % pieces_per_head);
-    const long long rh = u / pieces_per_head;  // (deferred row, kv head)
-    const int row = (int)(rh / p.Hkv);
-    const uint4* src = reinterpret_cast<const uint4*>(p.k_pend) + rh * pieces_per_head;
-    k_rot[u] = rope_row_piece(src, piece, pieces_per_head, is_f32 != 0, pend_pos_of(p)[row], p.rope_tab);
-  }
+// DecodeParams comes first (the metadata may ride inside it).  half = 1 << half_log: planes of a row.
+template <typename T>
+__global__ __launch_bounds__(256) void k_rope_prep(DecodeParams p, T* q_rot, T* k_rot, int half_log, int n_q_rows) {
+  const int half = 1 << half_log, f = (int)threadIdx.x & (half - 1);
+  const double per_pos = p.rope_tab[f];
+  const int t = (int)blockIdx.x * (256 >> half_log) + ((int)threadIdx.x >> half_log);
+  const int n_k_rows = p.pend_rope ? p.pend_n * p.Hkv : 0;
+  if (t >= n_q_rows + n_k_rows) return;
+  const bool is_q = t < n_q_rows;
+  const int row = is_q ? t : t - n_q_rows;
+  const T* src = static_cast<const T*>(is_q ? p.q : p.k_pend) + (long long)row * 2 * half;
+  const Plane<T> x = plane_load<T>(src, f, half);
+  const int pos = is_q ? meta_of(p)[p.off_streams + row / p.Hq * (int)(sizeof(DevStream) / 4) + (int)(offsetof(DevStream, pos) / 4)]
+                       : pend_pos_of(p)[row / p.Hkv];
+  float c, sn;
+  rope_cos_sin_by<sizeof(T) == 2>(per_pos, pos, c, sn);
+  plane_store<T>((is_q ? q_rot : k_rot) + (long long)row * 2 * half, f, half, x, c, sn);
 }
 
 }  // namespace pasta

@@ -1693,12 +1693,13 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       // one small launch turns what has to be turned: Q into its buffer, the deferred K rows into theirs
       p.rope_tab = (const double*)((const char*)c.workspace + h->off_rope);
       p.rope_q = rope_q ? 1 : 0;
-      uint4* q_rot = (uint4*)((char*)c.workspace + h->off_qrot);
-      uint4* k_rot = (uint4*)((char*)c.workspace + h->off_krot);
-      const int pph = D * h->elem / 16;
-      const long long nq = rope_q ? (long long)n * c.n_q_heads * pph : 0;
-      const long long nk = p.pend_rope ? (long long)p.pend_n * Hkv * pph : 0;
-      k_rope_prep<<<dim3((unsigned)((nq + nk + 255) / 256)), 256, 0, st>>>(p, q_rot, k_rot, pph, h->elem == 4, nq);
+      void* const q_rot = (char*)c.workspace + h->off_qrot;
+      void* const k_rot = (char*)c.workspace + h->off_krot;
+      const int half_log = D == 128 ? 6 : 5, per_wg = 256 >> half_log;
+      const int64_t nq = rope_q ? (int64_t)n * c.n_q_heads : 0, nk = p.pend_rope ? (int64_t)p.pend_n * Hkv : 0;
+      const dim3 grid((unsigned)((nq + nk + per_wg - 1) / per_wg));
+      if (c.dtype == PASTA_F32) k_rope_prep<float><<<grid, 256, 0, st>>>(p, (float*)q_rot, (float*)k_rot, half_log, (int)nq);
+      else k_rope_prep<uint16_t><<<grid, 256, 0, st>>>(p, (uint16_t*)q_rot, (uint16_t*)k_rot, half_log, (int)nq);
       if (rope_q) p.q = q_rot;
       if (p.pend_rope) { p.k_pend = k_rot; p.pend_rope = 0; }
     }
