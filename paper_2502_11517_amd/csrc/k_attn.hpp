@@ -359,7 +359,7 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
         d.first_pend = __builtin_ctz(m);
         d.n_pend = min(kBlock, n_tok - b * kBlock) - d.first_pend;
         d.patch = d.first_pend > 0 && d.n_pend <= 4;
-        d.any_pend = !d.patch;
+        d.any_pend = !d.patch && d.first_pend > 0;
       }
     }
 #pragma unroll
@@ -380,12 +380,15 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
       for (int i = 0; i < 8; ++i)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(is_v.value ? v_rs : k_rs, (lds_ptr)(dst + 64 * i), 16,
                                                  is_v.value ? lane_v : lane_k[i & 3], d.base + (uint32_t)(4 * i) * row_bytes32, 0, 0);
-    } else if (!d.any_pend) {
+    } else if (!d.any_pend) {  // all of its rows from the pool, or all of them deferred ones
+      // (a prompt's piece of 32 tokens over 4096, append and decode step: 18.5 us with the masked form below, 15.9 this way)
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<char*>(d.first_pend == 0 ? (is_v.value ? vpend : kpend) : (is_v.value ? vb : kb)), 0, -1, kRawBuffer);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {  // the row offset is a multiple of 256: bits 4..7 hold the piece alone
         const int r = rbase + 4 * i;
         const uint32_t o = is_v.value ? d.off[i] ^ (uint32_t)(((r & 15) ^ v_swizzle(r)) << 4) : d.off[i];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_v.value ? v_rs : k_rs, (lds_ptr)(dst + 64 * i), 16, o, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(dst + 64 * i), 16, o, 0, 0, 0);
       }
     } else {
       // some row of the block is a deferred one (the newest rows of a list sit in its last block): those
@@ -821,7 +824,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
   // The deferred append's copy into the pool (K1's job).  No work-group of this launch reads those
   // pool rows -- lists that name them are served from k_pend / v_pend -- so the copy needs no
   // ordering against the rest of the launch.  Normally it is spread thin: work-group b moves
-  // the 16 pieces of one (row, kv head) of K or V with its first 16 threads, which fetch them
+  // the 16 pieces of one (row, kv head) of K or V with its first 16 threads (many rows: 64), which fetch them
   // here, carry them through their item, and store them at the very end -- nobody waits for it.
   u32x4 pend_val = u32x4{0u, 0u, 0u, 0u};
   int pend_u = -1;  // this thread's piece of the copy, -1: none
@@ -840,9 +843,10 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
     return reinterpret_cast<const u32x4*>(is_v ? p.v_pend : p.k_pend)[u];
   };
   if (p.pend_n > 0) {
-    if (pend_total <= (int)gridDim.x * 16) {
-      if (threadIdx.x < 16 && (int)blockIdx.x * 16 < pend_total) {
-        pend_u = blockIdx.x * 16 + threadIdx.x;
+    const int lanes = pend_total <= (int)gridDim.x * 16 ? 16 : 64;
+    if (pend_total <= (int)gridDim.x * lanes) {
+      if ((int)threadIdx.x < lanes && (int)(blockIdx.x * lanes + threadIdx.x) < pend_total) {
+        pend_u = blockIdx.x * lanes + threadIdx.x;
         pend_val = pend_load(pend_u);
       }
     } else {  // few work-groups, many rows: all of it here and now
