@@ -1040,19 +1040,26 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 void* g_scratch_ptr[kMaxDevices] = {};
 
 // Steps that k_one takes: every stream sees few enough bytes of K and V per kv head that one CU reads them sooner than the
-// merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  The lines lie where both
-// sides measure the same for ONE stream, 16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream
-// (us, split / one).  With more streams the split form takes longer and one launch would be the shorter one beyond the line
-// too (8 streams, 450); the rule follows their number in one place only:
-//   bf16 x 128           1 stream: prefix 128 9.2 / 6.1, 300 8.2 / 7.6, 450 8.1 / 8.9;  8 streams: 450 12.2 / 9.6
-//   bf16 x 128, rotated  1 stream: 128 12.9 / 11.7, 300 12.7 / 13.0;  3 streams: 300 14.1 / 13.3, 450 14.0 / 14.9
-//                        (hence 144 KiB for one stream and 192 for more, over 128 dims)
-//   bf16 x 64            1 stream: 640 8.8 / 8.1, 900 8.9 / 9.4;  rotated 450 10.7 / 9.9, 640 10.8 / 11.0
-//   fp32 x 64            1 stream: 128 8.5 / 7.3, 300 8.6 / 9.5;  fp32 x 128: 32 9.0 / 7.0, 128 8.8 / 9.4
-// (fp32: 16-row tiles of four planes at a time, a quarter of them live: a work-group computes longer than it reads;
-// rotated: measured while every lane worked out its own planes' angles; with one table per work-group the one-launch
-// side takes 2.7 us less at 128 dims, so these lines lie on the safe side.  All before the weights of bf16 and the
-// sums of fp32 got back their bits, which takes 0.1 us of k_one's side and 0.2 to 0.3 of k_direct's.)
+// merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  One launch takes longer with
+// the list, hardly with the number of streams; the split form takes longer with the number of (stream, kv head) pairs, whose
+// partial rows it writes and reads.  Hence a line per kind and range of pairs, a twentieth and more inside of where both
+// sides measure the same.  16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream (us, split / one):
+//                        1 stream                           3 streams                          8 streams
+//   bf16 x 128           450 tokens 8.7 / 8.8               450 10.3 / 9.0, 640 10.4 / 10.8    640 12.5 / 11.1
+//   bf16 x 128, rotated  450 11.8 / 10.1, 640 12.1 / 12.1  450 13.6 / 10.2, 640 13.6 / 12.2   640 14.0 / 12.3
+//   bf16 x 64            640 8.7 / 8.2, 900 8.6 / 9.6       640 9.1 / 8.4, 900 9.3 / 9.8       640 9.7 / 8.5
+//   bf16 x 64, rotated   640 11.5 / 8.9, 900 11.5 / 10.5    900 12.1 / 10.9                    640 12.7 / 9.5
+//   fp32 x 64            250 9.4 / 8.8, 400 9.4 / 10.7      250 9.9 / 9.0, 400 10.0 / 11.1     400 11.8 / 11.2
+//   fp32 x 64, rotated   250 12.0 / 10.4, 400 11.3 / 11.8   400 12.8 / 12.3                    400 14.5 / 12.4
+//   fp32 x 128           128 9.4 / 8.9, 250 9.8 / 11.9      128 10.3 / 9.2, 250 10.4 / 12.1    250 13.3 / 12.4
+//   fp32 x 128, rotated  128 12.7 / 10.2, 250 12.7 / 13.8   250 13.7 / 14.0                    250 19.1 / 14.4
+// (not rotated and few pairs: fewer kv heads make the split form no slower, and the lines stay well inside.)
+constexpr int kOneKiB[4][2][3] = {  // [bf16 x 128, bf16 x 64, fp32 x 128, fp32 x 64][rotated][pairs < 24, < 64, more]
+    {{192, 300, 400}, {300, 400, 512}},
+    {{192, 208, 224}, {224, 256, 256}},
+    {{112, 204, 300}, {232, 264, 400}},
+    {{112, 172, 232}, {180, 228, 280}},
+};
 bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, size_t n_reqs) {
   const pasta_attn_config& c = h->cfg;
   const int n = a->n_streams;
@@ -1060,7 +1067,8 @@ bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vect
   if ((a->flags & ~(uint32_t)(PASTA_DECODE_ROPE_Q)) || a->dbg_part_ml) return false;
   if (n * c.n_kv_heads > h->n_cus) return false;
   const bool rope = (a->flags & PASTA_DECODE_ROPE_Q) || (h->pending.active && h->pending.rope);
-  int64_t most = c.dtype == PASTA_F32 ? (rope ? 96 : 112) : !rope || (n > 1 && c.head_dim == 128) ? 192 : 144;  // KiB
+  const int pairs = n * c.n_kv_heads;
+  int64_t most = kOneKiB[(c.dtype == PASTA_F32 ? 2 : 0) + (c.head_dim == 64 ? 1 : 0)][rope ? 1 : 0][pairs < 24 ? 0 : pairs < 64 ? 1 : 2];
   most = std::min<int64_t>(kOneTokens, (most << 10) / ((int64_t)c.head_dim * h->elem * 2));
   int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)n_reqs * (sizeof(DevReq) / 4) + 16;  // of the split plan at least: it has to ride in the kernel arguments
   for (int i = 0; i < n; ++i) {

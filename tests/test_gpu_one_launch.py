@@ -116,6 +116,33 @@ def test_requests_with_rotated_rows(dtype, D, page, defer):
     s.close()
 
 
+# KiB of K and V per kv head up to which steps of 24 .. 63 and of 64 and more (stream, kv head) pairs take one launch
+LINES = {("bf16", 128): [(300, 400), (400, 512)], ("bf16", 64): [(208, 224), (256, 256)],
+         ("f32", 128): [(204, 300), (264, 400)], ("f32", 64): [(172, 232), (228, 280)]}
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("n,Hkv", [(6, 4), (3, 8), (4, 16)])
+def test_the_longest_lists_of_many_pairs(dtype, D, rope, n, Hkv):
+    """The line by the number of pairs, from both sides: the longest list sees exactly the most tokens, then one more."""
+    most = min(1024, (LINES[dtype, D][rope][n * Hkv >= 64] << 10) // (2 * D * (2 if dtype == "bf16" else 4)))
+    w = W.single_request("pairs", dtype, Hkv, Hkv, D, 1.0, 24, most - 4, [3] + [2] * (n - 1), "round_robin", steps=2, k_std=D ** -0.5)
+    pos = w.event_positions() if rope else None
+    s, op = _session(w, rope_theta=THETA if rope else 0.0), OraclePool(w)
+    af, df = (B.APPEND_ROPE, B.DECODE_ROPE_Q) if rope else (0, 0)
+    s.append_events(w.n_prefill, flags=af, positions=pos)
+    for step in range(2):
+        s.append_events(w.n_events(step), flags=af | B.APPEND_DEFER, positions=pos)
+        op.append_events(w.n_events(step), **(dict(positions=pos, theta=THETA) if rope else {}))
+        if rope:
+            _check_rope_step(w, s, op, step, pos)
+        else:
+            _check_step(w, s, op, step)
+        assert _one_launch(w, s, step, flags=df, position=w.q_positions(step) if rope else None) == (step == 0)
+    s.close()
+
+
 @pytest.mark.parametrize("dtype,D", KINDS)
 @pytest.mark.parametrize("G", [1, 2, 8])
 @pytest.mark.parametrize("deferred", [0, 1, 9])
