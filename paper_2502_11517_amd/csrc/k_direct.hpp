@@ -61,13 +61,14 @@ template <int D, int RT, int NW> struct DirLds {
   uint32_t off[kDirWin];
   DevRange ranges[kGatherMax];
 };
-// ... and of k_one: the rows that are turned once per work-group (a stream's query rows; behind them its own deferred row)
-// and, per wave, one more deferred row.
+// ... and of k_one: the rows that are turned once per work-group (a stream's query rows; behind them its newest row where that
+// is a deferred one).
 constexpr int kMostHeads = 8;  // query heads per kv head
+constexpr int kMostDeferred = (int)(sizeof(DecodeParams::pend_pos) / sizeof(int32_t));
 template <typename T, int D, int NW, bool ROPE> struct OneLds : DirLds<D, 1, NW> {};
 template <typename T, int D, int NW> struct OneLds<T, D, NW, true> : DirLds<D, 1, NW> {
   static constexpr int kPieces = D * (int)sizeof(T) / 16;
-  u32x4 turned[kMostHeads + 1][kPieces + 1], other[NW][kPieces];
+  u32x4 turned[kMostHeads + 1][kPieces + 1];
 };
 
 // Turns the planes of a row whose pieces 4 kk + q are spread over the quarters' lanes: piece kk and piece
@@ -101,7 +102,8 @@ struct DirItem {
   int row0;                    // ... its first stacked row
   int q_stream;                // private item: its stream
   int q_pos;                   // (WHOLE) its query's position id,
-  int own_row, own_pos;        // the row of its newest token in a deferred append that is to be turned (-1: none), that one's id
+  int own_row, own_pos;        // ... the row of its newest token in a deferred append that is to be turned (-1: none), that one's id,
+  bool more_deferred;          // ... and whether the token before that may be such a row, too
 };
 
 // One item, once code_of(j) -- the address code of token j -- can be asked for.  GATHER: the rows are the G
@@ -145,16 +147,22 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   // lane turning the planes of its operand registers in place, by a table of angles and, for deferred rows, by angles of
   // its own, 300 + 3 x 20 .. 60 tokens, 16 layers of append and decode step, took 172.8 us; this way 139.2.
   // (For the same reason a second copy of the block's code, with two blocks requested together, lost: 189.)
+  // More deferred rows than that -- the newest slots of their request, so the list's last -- are spread over the waves and go
+  // to the place of the waves' O, free until they meet.  (One at a time, by the wave whose block holds them, they took 0.2 us
+  // each: 16 tokens of one stream over 64, 8 kv heads, append and decode step, fp32 x 64 9.9 us, bf16 x 64 8.3; this way 7.3
+  // and 6.1.  32 rows and one query: 14.2 and 12.1, 7.6 and 6.6.  Steps of one such row per list measure the same.)
   constexpr int kUnits = ROPE && WHOLE ? (kMostHeads + NW - 2) / (NW - 1) : 1;
+  constexpr int kTurnedRow = kPieceRow + 1;
+  static_assert(!(ROPE && WHOLE) || sizeof(lds.o) >= sizeof(u32x4) * kMostDeferred * kTurnedRow, "more deferred rows than the waves' O hold");
+  u32x4* const more_rows = reinterpret_cast<u32x4*>(&lds.o[0][0]);  // deferred row k >= 1, counted from the list's end: row k - 1
   const int plane = lane & (D / 2 - 1);
   Plane<T> unit[kUnits];
   double per_pos = 0.0;
-  const bool own = ROPE && WHOLE && it.own_row >= 0;
-  const uint32_t own_code = kPendBit | (uint32_t)((it.own_row * p.Hkv + g) * kPieceRow);
+  int n_def = 0;  // deferred rows of the list that are to be turned, where they are more than the newest
   if constexpr (ROPE && WHOLE) {
     per_pos = p.rope_tab[plane];
     if (w == NW - 1) {
-      if (own) unit[0] = plane_load<T>(reinterpret_cast<const char*>(p.k_pend) + (long long)(it.own_row * p.Hkv + g) * (D * sizeof(T)), plane, D / 2);
+      if (it.own_row >= 0) unit[0] = plane_load<T>(reinterpret_cast<const char*>(p.k_pend) + (long long)(it.own_row * p.Hkv + g) * (D * sizeof(T)), plane, D / 2);
     } else if (p.rope_q) {
 #pragma unroll
       for (int n = 0; n < kUnits; ++n)
@@ -214,27 +222,12 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         for (int t = 0; t < kNT; ++t) {
           const uint32_t code = lds.off[b * kTok + 16 * t + i];
           if (__builtin_amdgcn_ballot_w64((int)code < 0)) {
-            if constexpr (WHOLE) {
-              if (own && code == own_code) {  // it stands in LDS by now
+            if constexpr (WHOLE) {  // they stand in LDS by now
+              if ((int)code < 0) {
+                const int k = max(n_here - 1 - (b * kTok + 16 * t + i), 0);
+                const u32x4* src = (k == 0 ? lds.turned[kMostHeads] : more_rows + (k - 1) * kTurnedRow) + q;
 #pragma unroll
-                for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = lds.turned[kMostHeads][4 * kk + q];
-              }
-              // rows that others have just appended, one at a time
-              for (uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64((int)code < 0 && !(own && code == own_code)) & 0xffffu; m; m &= m - 1) {
-                const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)code, __builtin_ctz(m));
-                const int row = (int)((one & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
-                const Plane<T> y = plane_load<T>(kpend + ((unsigned long long)(one & ~kPendBit) << 4), plane, D / 2);
-                float c, sn;
-                rope_cos_sin_by<sizeof(T) == 2>(per_pos, pend_pos_of(p)[row], c, sn);
-                if (lane < D / 2) plane_store<T>(lds.other[w], plane, D / 2, y, c, sn);
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                if (code == one) {
-#pragma unroll
-                  for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = lds.other[w][4 * kk + q];
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+                for (int kk = 0; kk < kNP; ++kk) x.k[t][kk] = src[4 * kk];
               }
             } else {
               const int row = (int)((code & ~kPendBit) / (uint32_t)(p.Hkv * kPieceRow));
@@ -383,11 +376,20 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         rope_cos_sin_by<sizeof(T) == 2>(per_pos, w == NW - 1 ? it.own_pos : it.q_pos, c, sn);
         if (lane < D / 2) {
           if (w == NW - 1) {
-            if (own) plane_store<T>(lds.turned[kMostHeads], plane, D / 2, unit[0], c, sn);
+            if (it.own_row >= 0) plane_store<T>(lds.turned[kMostHeads], plane, D / 2, unit[0], c, sn);
           } else if (p.rope_q) {
 #pragma unroll
             for (int n = 0; n < kUnits; ++n)
               if (w + n * (NW - 1) < R) plane_store<T>(lds.turned[w + n * (NW - 1)], plane, D / 2, unit[n], c, sn);
+          }
+        }
+        if (__builtin_expect(it.more_deferred, 0)) {
+          n_def = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < min(n_here, kMostDeferred) && (int)lds.off[max(n_here - 1 - lane, 0)] < 0));
+          for (int k = 1 + w; k < n_def; k += NW) {
+            const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds.off[n_here - 1 - k]) & ~kPendBit;
+            const Plane<T> x = plane_load<T>(kpend + ((unsigned long long)at << 4), plane, D / 2);
+            rope_cos_sin_by<sizeof(T) == 2>(per_pos, pend_pos_of(p)[at / (uint32_t)(p.Hkv * kPieceRow)], c, sn);
+            plane_store<T>(more_rows + (k - 1) * kTurnedRow, plane, D / 2, x, c, sn);
           }
         }
         lds_barrier();
@@ -403,16 +405,16 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         q_turned = true;
       }
     };
-    if (w >= nb) {
-      if constexpr (WHOLE) turn_q();
-      continue;
-    }
-    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
+    if (!WHOLE && w >= nb) continue;
     Blk A;
     f32x4 pr[kNT][RT];
-    load_k(A, w);
-    load_v(A, w);
+    if (!WHOLE || w < nb) {
+      load_k(A, w);
+      load_v(A, w);
+    }
     turn_q();
+    if (WHOLE && w >= nb) continue;
+    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
     for (int b = w; b < last; b += NW) {  // the next block is requested half by half, as this one's places fall free
       scores(A, b, n_here, pr);
       load_k(A, b + NW);
@@ -433,6 +435,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     weigh(A, pr);
   }
 
+  if (ROPE && WHOLE && __builtin_expect(it.more_deferred, 0)) lds_barrier();  // every wave is done with the rows that stand in the place of O
   // ---- the waves meet once.  Group (rt, r, cg) of a lane: head dims of M-tiles 4 cg .. 4 cg + 3 at m = 4 q + r.
   const int n_act = min(NW, (min(kDirWin, n_tok) + kTok - 1) / kTok);  // waves that had a block
   if (w < n_act) {
@@ -643,6 +646,7 @@ constexpr int kOneWaves = 8;
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
   __shared__ OneLds<T, D, kOneWaves, ROPE> lds;
+  static_assert(2 * sizeof(lds) <= 160 * 1024, "two work-groups per CU: the copy's stand beside the streams'");
   const int tid = threadIdx.x;
   const int n_rows_wgs = p.n_mfma_items * p.Hkv;  // (one item per stream)
   if ((int)blockIdx.x >= n_rows_wgs) {
@@ -673,12 +677,14 @@ __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
   const words ranges = meta + p.off_ranges + item_word(offsetof(DevItem, range_first)) * (int)(sizeof(DevRange) / 4);
   it.own_row = -1;
   it.own_pos = 0;
+  it.more_deferred = false;
   if (ROPE && p.pend_rope) {
     const words newest = ranges + 4 * (nr - 1);
-    const int slot = newest[0] + (it.n_tok - 1 - newest[3]) * newest[2];
+    const int left = it.n_tok - 1 - newest[3], slot = newest[0] + left * newest[2];
     if (slot >= pend0) {
       it.own_row = pend_src0 + (slot - pend0);
       it.own_pos = pend_pos_of(p)[it.own_row];
+      it.more_deferred = it.n_tok > 1 && slot - (left > 0 ? newest[2] : 1) >= pend0;
     }
   }
   for (int k = tid; k < nr; k += kOneWaves * 64) lds.ranges[k] = DevRange{ranges[4 * k], ranges[4 * k + 1], ranges[4 * k + 2], ranges[4 * k + 3]};

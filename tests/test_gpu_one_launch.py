@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2502_11517_amd import binding as B
 from paper_2502_11517_amd import workloads as W
 from paper_2502_11517_amd.harness import to_device
@@ -159,6 +160,52 @@ def test_rotated_rows_of_narrow_and_wide_groups(dtype, D, G, deferred):
     _check_rope_step(w, s, op, 0, pos)
     _check_rope_pool(w, s, op, w.n_prefill)
     assert _one_launch(w, s, 0, flags=B.DECODE_ROPE_Q, position=w.q_positions(0))
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("page", [0, 8])
+@pytest.mark.parametrize("deferred", [2, 17, 32])
+def test_many_deferred_rotated_rows(dtype, D, page, deferred):
+    """Two deferred rows, more of them than one round of waves turns, and the most that a step takes along; lists that hold one of
+    them, several (with other threads' rows between them) and, in the other request, none."""
+    w = _two_requests(dtype, D, page)
+    pos = w.event_positions()
+    s, op = _session(w, rope_theta=THETA), OraclePool(w)
+    s.append_events(w.n_prefill - deferred, flags=B.APPEND_ROPE, positions=pos)
+    s.append_events(w.n_prefill, flags=B.APPEND_ROPE | B.APPEND_DEFER, positions=pos)
+    op.append_events(w.n_prefill, positions=pos, theta=THETA)
+    _check_rope_step(w, s, op, 0, pos)
+    _check_rope_pool(w, s, op, w.n_prefill)
+    assert _one_launch(w, s, 0, flags=B.DECODE_ROPE_Q, position=w.q_positions(0))
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,D", KINDS)
+@pytest.mark.parametrize("context,n", [(40, 8), (57, 12), (0, 32)])
+def test_a_prompt_piece_deferred_and_rotated(dtype, D, context, n):
+    """causal_skip: every token of the piece sees its own number of deferred rows; then the last token alone sees all of them."""
+    w = W.single_request("piece", dtype, 8, 2, D, 1.0, 23, context + n, [1], "random", k_std=D ** -0.5)
+    w.ev_stream[:], w.ev_parent[:] = 0, -1  # one stream, no fork
+    pos = w.event_positions()
+    s, op = _session(w, rope_theta=THETA, max_streams=n), OraclePool(w)
+    if context:
+        s.append_events(context, flags=B.APPEND_ROPE, positions=pos)
+    q = w._encode(np.random.default_rng(5).standard_normal((n, w.Hq, D), dtype=np.float32))
+    op.append_events(context + n, positions=pos, theta=THETA)
+    q64 = oracle.rope(oracle.widen_pool(dtype, q), pos[context:context + n], THETA)
+    for m in ([n] if n <= 12 else []) + [1]:  # (the plan of 32 of them does not ride in the kernel arguments)
+        if s.n_done < context + n:
+            s.append_events(context + n, flags=B.APPEND_ROPE | B.APPEND_DEFER, positions=pos)
+        qd = to_device(q[n - m:], dtype, s.device)
+        out, plan = torch.empty_like(qd), np.zeros(8, np.int64)
+        s.h.decode_step(0, [0] * m, [0] * m, qd, out, causal_skip=list(range(m - 1, -1, -1)), flags=B.DECODE_ROPE_Q,
+                        position=pos[context + n - m:context + n], dbg_plan=plan)
+        seen = np.arange(context + n - m + 1, context + n + 1)
+        ref, _ = oracle.attention_q64(op.g, op.k, op.v, [0] * m, seen, np.zeros(m + 1, int), [], [], [], q64[n - m:], w.scale)
+        check_close(_out64(w, out), ref, dtype, f"{m} queries")
+        assert plan[3] == 0 and plan[2] == m
+    _check_rope_pool(w, s, op, context + n)
     s.close()
 
 
