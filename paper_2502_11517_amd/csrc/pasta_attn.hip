@@ -1333,10 +1333,23 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     int64_t priv_chunk = kPrivChunk, chunk_tokens = kTile;
     if (matrix) {
       chunk_tokens = std::max<int64_t>(kTile, pc_weighted * Hkv / h->n_cus / kTile * kTile);
-      // Several requests: their prefixes do not end with a chunk, and a launch ends with its longest items, so two thirds of that
-      // (16 requests of 256 .. 4096 tokens, 1 .. 8 streams, pages of 16, append and decode step: chunks of 1024 tokens 60.3 us,
-      // 768 56.1, 512 57.1, 384 59.6, 256 64.3; one request of 8192: 256 17.3, 128 20.8).
-      if (!wide && reqs.size() > 1 && chunk_tokens >= kManyChunk) chunk_tokens = std::max<int64_t>(kManyChunk, chunk_tokens * 2 / 3 / kTile * kTile);
+      // Several prefixes rarely end with a chunk: their remainders make more work-groups than there are CUs, some CUs then have two
+      // long ones and end the launch alone.  Chunks of two thirds spread that out; where the chunks come out one per CU they only
+      // add partial rows.  So the line is the number of work-groups, those of an eighth of a chunk or less not counted.
+      // Append and decode step, one per CU -> two thirds (us; 150 drawn batches and 80 of equal prefixes, geometric means 0.93 and
+      // 0.94 by this rule, 1.01 at most; two thirds for every batch: up to 1.19):
+      //   bf16 x 128, 8 kv heads, 16 requests of 256 .. 4096 tokens   60.3 -> 56.1 (chunks of 512: 57.1, of 256: 64.3)
+      //   fp32 x 128, 13 requests of 941 .. 6604                     108.9 -> 84.9
+      //   bf16 x 64, 10 requests of 5120                              42.5 -> 31.6
+      //   not taken: bf16 x 128, 16 x 2 streams over 4096 60.8 (64.5), bf16 x 64 37.1 (43.4), fp32 x 128 8 x 8 over 8192 195 (233)
+      if (!wide && chunk_tokens >= kManyChunk) {
+        int64_t n_prefixes = 0, n_wgs = 0;
+        for (auto& q : reqs) {
+          n_prefixes += q.pc > 0;
+          n_wgs += (q.pc / chunk_tokens + (q.pc % chunk_tokens > chunk_tokens / 8)) * Hkv * row_units(q);
+        }
+        if (n_prefixes > 1 && n_wgs > h->n_cus) chunk_tokens = std::max<int64_t>(kManyChunk, chunk_tokens * 2 / 3 / kTile * kTile);
+      }
       priv_chunk = wide ? 256 : 128;  // (beside the long wide work-groups the private items get one slot per CU: longer items keep more in flight there)
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
       if (one) priv_chunk = kOneTokens;  // a stream's whole list

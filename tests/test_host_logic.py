@@ -241,6 +241,31 @@ def test_plan_arithmetic_on_the_8k_prefix_8_stream_shape():
     assert plan[5] == 0 and plan[1] == 0 and plan[2] == sum(-(-v // 128) for v in vis)
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128)])
+def test_chunks_of_several_prefixes(dtype, D):
+    """One chunk per CU (256 without a device), or two thirds of that where the remainders of several prefixes would make more."""
+    def chunk(prefixes):
+        R = len(prefixes)
+        req, sid = np.concatenate([np.repeat(np.arange(R), prefixes), np.repeat(np.arange(R), 2)]), np.concatenate([np.zeros(sum(prefixes), int), np.tile([1, 2], R)])
+        h = _handle(dtype, D=D, max_requests=R, pool_tokens=max(prefixes) + 2, max_streams=3)
+        _reserve(h, req, sid, np.where(sid > 0, 0, -1))
+        _, plan = _plan(h, np.repeat(np.arange(R), 2), np.tile([1, 2], R))
+        h.destroy()
+        assert plan[5] == sum(p for p in prefixes if p >= 64) and plan[1] == sum(-(-p // plan[4]) for p in prefixes if p >= 64) * 8
+        return int(plan[4])
+    assert chunk([4096] * 16) == 2048            # 256 work-groups: nothing to spread
+    assert chunk([3072] * 16) == 1536
+    assert chunk([4097] * 16) == 2048            # a token more opens chunks that do not count
+    assert chunk([4096] * 12) == 1024            # 1536: three each, 288 work-groups
+    assert chunk([1000 * k for k in range(1, 9)]) == 704   # 1088: 36 chunks, 288 work-groups
+    assert chunk([32768]) == 1024                # one prefix
+    assert chunk([32768, 10]) == 1024            # a second request without a shared prefix is no second prefix
+    assert chunk([32768, 100]) == 1024
+    assert chunk([2000] * 9) == 512              # the least
+    assert chunk([2000] * 10) == 512             # 576: 400 work-groups, two thirds are less than the least
+    assert chunk([1900] * 8) == 448              # below it nothing changes
+
+
 def test_requests_with_more_than_32_stacked_rows_choice_of_the_form():
     """One 32-row group per work-group, or four: the plan's count of shared-prefix work-groups tells which.  The
     library picks the four-group form where three of four waves compute on average and a chunk is four rounds
