@@ -1040,37 +1040,54 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 void* g_scratch_ptr[kMaxDevices] = {};
 
 // Steps that k_one takes: every stream sees few enough bytes of K and V per kv head that one CU reads them sooner than the
-// merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  One launch takes longer with
-// the list, hardly with the number of streams; the split form takes longer with the number of (stream, kv head) pairs, whose
-// partial rows it writes and reads.  Hence a line per kind and range of pairs, a twentieth and more inside of where both
-// sides measure the same.  16 layers of append + decode step, 8 kv heads, 20 .. 60 own tokens per stream (us, split / one):
-//                        1 stream                           3 streams                          8 streams
-//   bf16 x 128           450 tokens 8.7 / 8.8               450 10.3 / 9.0, 640 10.4 / 10.8    640 12.5 / 11.1
-//   bf16 x 128, rotated  450 11.8 / 10.1, 640 12.1 / 12.1  450 13.6 / 10.2, 640 13.6 / 12.2   640 14.0 / 12.3
-//   bf16 x 64            640 8.7 / 8.2, 900 8.6 / 9.6       640 9.1 / 8.4, 900 9.3 / 9.8       640 9.7 / 8.5
-//   bf16 x 64, rotated   640 11.5 / 8.9, 900 11.5 / 10.5    900 12.1 / 10.9                    640 12.7 / 9.5
-//   fp32 x 64            250 9.4 / 8.8, 400 9.4 / 10.7      250 9.9 / 9.0, 400 10.0 / 11.1     400 11.8 / 11.2
-//   fp32 x 64, rotated   250 12.0 / 10.4, 400 11.3 / 11.8   400 12.8 / 12.3                    400 14.5 / 12.4
-//   fp32 x 128           128 9.4 / 8.9, 250 9.8 / 11.9      128 10.3 / 9.2, 250 10.4 / 12.1    250 13.3 / 12.4
-//   fp32 x 128, rotated  128 12.7 / 10.2, 250 12.7 / 13.8   250 13.7 / 14.0                    250 19.1 / 14.4
-// (not rotated and few pairs: fewer kv heads make the split form no slower, and the lines stay well inside.)
-constexpr int kOneKiB[4][2][3] = {  // [bf16 x 128, bf16 x 64, fp32 x 128, fp32 x 64][rotated][pairs < 24, < 64, more]
-    {{192, 300, 400}, {300, 400, 512}},
-    {{192, 208, 224}, {224, 256, 256}},
-    {{112, 204, 300}, {232, 264, 400}},
-    {{112, 172, 232}, {180, 228, 280}},
+// merge launch (and, with rotary embedding ahead of k_attn, the small launch for it) takes.  One launch takes longer with the
+// list -- by rounds of eight waves' blocks -- and hardly with anything else.  The split form takes longer with a second stream, and
+// with more than 16 rows stacked over a shared prefix, where k_direct computes two row tiles.  Hence a line per kind and column:
+// [one stream, or few (stream, kv head) pairs; others; others of more than 16 stacked rows].  Each lies where both forms take about
+// the same time on the device -- the mean of warm pools and of pools that come from HBM -- and called eagerly one launch is
+// still some twentieth the sooner one.  The measured lists next to each line, append and decode step of a layer, 8 kv heads of 4 query
+// heads, 20 .. 60 own tokens per stream: tokens: us split / one, replayed graphs of 16 warm layers (of 600 MB of layers) [called]
+//                  1 stream                                      3 streams                                     8 streams
+//   bf16 x 128     384: 7.0 / 7.4 (7.8 / 8.0) [7.8 / 7.7]        512: 9.7 / 9.4 (9.9 / 10.2) [10.3 / 9.3]      512: 10.3 / 9.5 (11.0 / 10.5) [10.1 / 9.2]
+//                  448: 7.4 / 8.5 (8.0 / 9.0) [7.9 / 8.5]        576: 9.8 / 10.1 (10.0 / 11.2) [10.4 / 10.1]   576: 10.3 / 10.2 (11.0 / 11.3) [10.1 / 10.0]
+//    rotated       512: 10.6 / 10.2 (10.7 / 10.6) [10.8 / 10.0]  768: 12.8 / 12.7 (13.6 / 14.3) [13.7 / 12.6]  768: 13.3 / 12.9 (14.3 / 14.3) [14.1 / 12.7]
+//                  576: 11.0 / 10.8 (11.0 / 11.9) [10.9 / 10.6]  832: 12.9 / 13.3 (13.8 / 15.1) [13.8 / 13.1]  (plans too large)
+//   bf16 x 64      768: 6.6 / 7.8 (7.7 / 8.2) [7.6 / 8.2]        768: 8.1 / 8.3 (8.4 / 8.5) [9.3 / 9.0]        768: 9.1 / 8.8 (9.5 / 9.0) [10.1 / 9.3]
+//    rotated       960: 10.8 / 10.8 (11.1 / 11.0) [11.5 / 10.8]  960: 11.6 / 11.1 (11.7 / 11.4) [12.3 / 11.1]  768: 12.4 / 9.8 (12.8 / 10.2) [13.2 / 9.8]
+//   fp32 x 128      96: 7.8 / 6.6 (8.9 / 7.1) [9.3 / 7.8]        192: 9.5 / 9.6 (9.8 / 9.8) [10.3 / 9.8]       288: 13.2 / 12.7 (13.9 / 13.2) [13.5 / 12.5]
+//                  128: 8.1 / 6.9 (8.9 / 7.2) [9.6 / 8.1]        224: 9.9 / 11.2 (10.0 / 11.4) [10.5 / 11.1]   320: 13.2 / 13.0 (13.8 / 13.7) [13.5 / 12.9]
+//    rotated       256: 12.2 / 11.9 (12.5 / 12.4) [12.7 / 11.9]  256: 13.5 / 12.7 (13.8 / 13.4) [13.8 / 12.6]  416: 19.4 / 17.4 (20.2 / 18.5) [19.4 / 17.2]
+//                  288: 12.2 / 13.9 (12.5 / 14.5) [12.6 / 13.9]  288: 13.4 / 14.1 (14.1 / 14.9) [13.9 / 14.0]  448: 19.5 / 17.8 (20.3 / 18.9) [19.6 / 17.6]
+//   fp32 x 64      224: 7.5 / 7.0 (8.6 / 7.3) [9.3 / 8.1]        288: 8.2 / 8.6 (9.3 / 9.0) [10.3 / 9.3]       448: 11.4 / 11.5 (12.0 / 12.0) [11.8 / 11.4]
+//                  256: 7.6 / 7.1 (8.6 / 7.5) [9.3 / 8.1]        320: 8.1 / 8.8 (9.3 / 9.2) [10.2 / 9.5]       480: 11.4 / 11.5 (12.3 / 12.0) [11.9 / 11.5]
+//    rotated       384: 10.4 / 10.4 (11.6 / 11.0) [11.9 / 10.8]  448: 12.2 / 12.5 (12.5 / 12.7) [12.9 / 12.4]  512: 14.1 / 13.3 (15.1 / 14.3) [14.3 / 13.1]
+//                  416: 10.3 / 11.6 (11.3 / 12.2) [12.0 / 12.0]  480: 12.4 / 12.6 (12.6 / 13.4) [12.8 / 12.5]  544: 14.0 / 14.5 (15.1 / 15.3) [14.3 / 14.3]
+// (the first column's plain lines are older than the table: bf16 x 64 past, fp32 short of where both are even.)  More pairs do not
+// count: 4 streams x 16 heads are as 3 x 8 (fp32 x 128 over 288 10.2 / 12.5, 8 streams x 8 heads 13.2 / 12.7), one stream of 32 heads as one
+// of 8 (bf16 x 128 over 448 8.6 / 9.3).  8 query heads per kv head: 3 streams as 8 of 4 (fp32 x 64 over 384 10.8 / 9.4).  Six requests of
+// one stream: better than 3 streams (bf16 x 128 over 576 11.3 / 10.1).  One kv head: as 8 (bf16 x 128 over 500, called, 1 stream 8.1 / 8.5, 4
+// streams 9.8 / 8.9): few pairs of several streams stay in the first column, on the safe side.
+constexpr int kFewPairs = 24, kOneRowTile = 16;
+constexpr int kOneKiB[4][2][3] = {  // [bf16 x 128, bf16 x 64, fp32 x 128, fp32 x 64][rotated][column]
+    {{192, 272, 288}, {272, 384, 384}},
+    {{192, 192, 208}, {240, 240, 240}},
+    {{112, 192, 288}, {256, 256, 416}},
+    {{112, 144, 224}, {192, 224, 256}},
 };
-bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, size_t n_reqs) {
+bool small_step(const pasta_attn* h, const pasta_decode_args* a, const std::vector<ListView>& lv, const std::vector<DevReq>& reqs) {
   const pasta_attn_config& c = h->cfg;
   const int n = a->n_streams;
   // what asks for a certain form, its partials or a plan alone gets the split one
   if ((a->flags & ~(uint32_t)(PASTA_DECODE_ROPE_Q)) || a->dbg_part_ml) return false;
   if (n * c.n_kv_heads > h->n_cus) return false;
   const bool rope = (a->flags & PASTA_DECODE_ROPE_Q) || (h->pending.active && h->pending.rope);
-  const int pairs = n * c.n_kv_heads;
-  int64_t most = kOneKiB[(c.dtype == PASTA_F32 ? 2 : 0) + (c.head_dim == 64 ? 1 : 0)][rope ? 1 : 0][pairs < 24 ? 0 : pairs < 64 ? 1 : 2];
+  int stacked = 0;  // most rows over one shared prefix
+  for (const DevReq& q : reqs)
+    if (q.pc >= kTile) stacked = std::max(stacked, q.n_streams * h->G);
+  const int column = n == 1 || n * c.n_kv_heads < kFewPairs ? 0 : stacked <= kOneRowTile ? 1 : 2;
+  int64_t most = kOneKiB[(c.dtype == PASTA_F32 ? 2 : 0) + (c.head_dim == 64 ? 1 : 0)][rope ? 1 : 0][column];
   most = std::min<int64_t>(kOneTokens, (most << 10) / ((int64_t)c.head_dim * h->elem * 2));
-  int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)n_reqs * (sizeof(DevReq) / 4) + 16;  // of the split plan at least: it has to ride in the kernel arguments
+  int64_t words = (int64_t)n * (sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (sizeof(DevReq) / 4) + 16;  // of the split plan at least: it has to ride in the kernel arguments
   for (int i = 0; i < n; ++i) {
     const ListView& v = lv[i];
     if (v.prefix_len > most || v.n_ranges >= kGatherMax) return false;
@@ -1290,7 +1307,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // walker is left with NO_MFMA and what is larger still.
     const bool fits_direct = !(a->flags & PASTA_DECODE_NO_MFMA) && h->layer_elems * h->elem < ((int64_t)1 << 35);
     // (k_one rounds the weights of bf16 x 128 as k_attn does; layers that k_attn does not address keep fp32's)
-    const bool one = fits_direct && (mfma || c.dtype == PASTA_F32 || D == 64) && small_step(h, a, lv, reqs.size());
+    const bool one = fits_direct && (mfma || c.dtype == PASTA_F32 || D == 64) && small_step(h, a, lv, reqs);
     const bool direct = fits_direct && (one || !mfma);
     const bool matrix = mfma || direct;
     int64_t pc_total = 0, pc_weighted = 0;  // the second counts a prefix once per work-group that reads it

@@ -117,18 +117,19 @@ def test_requests_with_rotated_rows(dtype, D, page, defer):
     s.close()
 
 
-# KiB of K and V per kv head up to which steps of 24 .. 63 and of 64 and more (stream, kv head) pairs take one launch
-LINES = {("bf16", 128): [(300, 400), (400, 512)], ("bf16", 64): [(208, 224), (256, 256)],
-         ("f32", 128): [(204, 300), (264, 400)], ("f32", 64): [(172, 232), (228, 280)]}
+# KiB of K and V per kv head up to which a step takes one launch, (plain, rotated) x (one stream or few (stream, kv head) pairs;
+# others; others of more than 16 rows stacked over a shared prefix)
+LINES = {("bf16", 128): [(192, 272, 288), (272, 384, 384)], ("bf16", 64): [(192, 192, 208), (240, 240, 240)],
+         ("f32", 128): [(112, 192, 288), (256, 256, 416)], ("f32", 64): [(112, 144, 224), (192, 224, 256)]}
 
 
 @pytest.mark.parametrize("dtype,D", KINDS)
 @pytest.mark.parametrize("rope", [False, True])
-@pytest.mark.parametrize("n,Hkv", [(6, 4), (3, 8), (4, 16)])
-def test_the_longest_lists_of_many_pairs(dtype, D, rope, n, Hkv):
-    """The line by the number of pairs, from both sides: the longest list sees exactly the most tokens, then one more."""
-    most = min(1024, (LINES[dtype, D][rope][n * Hkv >= 64] << 10) // (2 * D * (2 if dtype == "bf16" else 4)))
-    w = W.single_request("pairs", dtype, Hkv, Hkv, D, 1.0, 24, most - 4, [3] + [2] * (n - 1), "round_robin", steps=2, k_std=D ** -0.5)
+@pytest.mark.parametrize("n,Hkv,G,column", [(1, 8, 4, 0), (2, 4, 1, 0), (1, 32, 1, 0), (6, 4, 1, 1), (3, 8, 4, 1), (4, 16, 1, 1), (3, 8, 8, 2), (6, 4, 4, 2)])
+def test_the_longest_lists_of_many_pairs(dtype, D, rope, n, Hkv, G, column):
+    """Each line from both sides: the longest list sees exactly the most tokens, then one more."""
+    most = min(1024, (LINES[dtype, D][rope][column] << 10) // (2 * D * (2 if dtype == "bf16" else 4)))
+    w = W.single_request("pairs", dtype, Hkv * G, Hkv, D, 1.0, 24, most - 4, [3] + [2] * (n - 1), "round_robin", steps=2, k_std=D ** -0.5)
     pos = w.event_positions() if rope else None
     s, op = _session(w, rope_theta=THETA if rope else 0.0), OraclePool(w)
     af, df = (B.APPEND_ROPE, B.DECODE_ROPE_Q) if rope else (0, 0)
