@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
   // The deferred append's copy into the pool (K1's job).  No work-group of this launch reads those
   // pool rows -- lists that name them are served from k_pend / v_pend -- so the copy needs no
   // ordering against the rest of the launch.  Normally it is spread thin: work-group b moves
-  // the 16 pieces of one (row, kv head) of K or V with its first 16 threads (many rows: 64), which fetch them
+  // the 16 pieces of one (row, kv head) of K or V with its first 16 threads, which fetch them
   // here, carry them through their item, and store them at the very end -- nobody waits for it.
   u32x4 pend_val = u32x4{0u, 0u, 0u, 0u};
   int pend_u = -1;  // this thread's piece of the copy, -1: none
@@ -843,13 +843,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
     return reinterpret_cast<const u32x4*>(is_v ? p.v_pend : p.k_pend)[u];
   };
   if (p.pend_n > 0) {
-    const int lanes = pend_total <= (int)gridDim.x * 16 ? 16 : 64;
-    if (pend_total <= (int)gridDim.x * lanes) {
-      if ((int)threadIdx.x < lanes && (int)(blockIdx.x * lanes + threadIdx.x) < pend_total) {
-        pend_u = blockIdx.x * lanes + threadIdx.x;
+    if (pend_total <= (int)gridDim.x * 16) {
+      if (threadIdx.x < 16 && (int)blockIdx.x * 16 < pend_total) {
+        pend_u = blockIdx.x * 16 + threadIdx.x;
         pend_val = pend_load(pend_u);
       }
-    } else {  // few work-groups, many rows: all of it here and now
+    } else {  // few work-groups, many rows: all of it here and now (carried by 64 threads each, 32 rows over 1100 .. 2000 tokens: the same)
       for (int t = blockIdx.x * kAttnThreads + threadIdx.x; t < pend_total; t += gridDim.x * kAttnThreads) {
         pend_store(t, pend_load(t));
       }

@@ -1,5 +1,5 @@
 """k_attn over several deferred rows of one stream: blocks that hold nothing else (2, 5, 31 and 32 distinct rows, listed and
-contiguous, in pools with and without pages, rotated and not), and the three ways in which their copy into the pool is spread over the launch."""
+contiguous, in pools with and without pages, rotated and not), and their copy into the pool by few and by many work-groups."""
 from __future__ import annotations
 
 import numpy as np
