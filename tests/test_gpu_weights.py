@@ -10,7 +10,7 @@ import oracle
 from paper_2502_11517_amd import binding as B
 from paper_2502_11517_amd import workloads as W
 from paper_2502_11517_amd.harness import to_device
-from test_gpu_parity import _out64, _session
+from test_gpu_parity import THETA, _out64, _session
 from util import OraclePool
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +97,25 @@ def test_fp32_results_are_not_further_off_than_by_short_sums(D, prefix, lengths)
     ref, _ = op.attention(0)
     assert np.linalg.norm(_out64(w, out) - ref) <= 2.3e-7 * np.linalg.norm(ref)
     s.close()
+
+
+@pytest.mark.parametrize("D,prefix,rope", [(128, 250, False), (128, 370, True), (64, 400, False), (64, 460, True)])
+def test_fp32_lists_read_whole_are_no_further_off_than_the_split_form(D, prefix, rope):
+    """Lists of several blocks per wave, 8 streams, in one launch: over 4 draws the error is at most 1.05 of the split form's (the draws leave
+    it some 2 % either way: 0.97 to 1.00 over 8 of them; in one chain per wave it is 1.08 to 1.15 with 128-wide heads)."""
+    err = {0: [], B.DECODE_ROW_GROUPS: []}
+    for seed in range(4):
+        w = W.single_request("whole", "f32", 32, 8, D, 1.0, 40 + seed, prefix, [30] * 8, "round_robin", k_std=D ** -0.5)
+        pos, qpos = (w.event_positions(), w.q_positions(0)) if rope else (None, None)
+        s, op = _session(w, rope_theta=THETA if rope else 0.0), OraclePool(w).append_events(w.n_prefill, **(dict(positions=pos, theta=THETA) if rope else {}))
+        s.append_events(w.n_prefill, flags=B.APPEND_ROPE if rope else 0, positions=pos)
+        q64 = oracle.widen_pool("f32", w.q(0)).astype(np.float64)
+        ref, _ = oracle.attention_q64(op.g, op.k, op.v, w.dec_request, *w.lists(0), oracle.rope(q64, qpos, THETA) if rope else q64, w.scale)
+        for flags, errs in err.items():
+            out, _, _ = s.decode(0, explicit=False, flags=flags | (B.DECODE_ROPE_Q if rope else 0), position=qpos)
+            errs.append(np.linalg.norm(_out64(w, out) - ref) / np.linalg.norm(ref))
+        plan = np.zeros(8, np.int64)
+        s.h.decode_step(0, w.dec_request, w.dec_stream, out, out, flags=B.DECODE_ROPE_Q if rope else 0, position=qpos, dbg_plan=plan)
+        assert plan[3] == 0
+        s.close()
+    assert np.mean(err[0]) <= 1.05 * np.mean(err[B.DECODE_ROW_GROUPS])
