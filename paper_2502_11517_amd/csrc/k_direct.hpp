@@ -150,8 +150,8 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
   // turns the stream's newest row, the others the query rows.  Requested here, turned behind the requests for the rows.
   // A launch this short runs its code once, so what the turning costs is code to fetch as much as arithmetic: with every
   // lane turning the planes of its operand registers in place, by a table of angles and, for deferred rows, by angles of
-  // its own, 300 + 3 x 20 .. 60 tokens, 16 layers of append and decode step, took 172.8 us; this way 139.2.
-  // (For the same reason a second copy of the block's code, with two blocks requested together, lost: 189.)
+  // its own, 300 + 3 x 20 .. 60 tokens, 16 layers of append and decode step, took 172.8 us; this way 138.4.
+  // (A second copy of the block's code, with two blocks requested together, was measured on that form alone: 189.)
   // More deferred rows than that -- the newest slots of their request, so the list's last -- are spread over the waves and go
   // to the place of the waves' O, free until they meet.  (One at a time, by the wave whose block holds them, they took 0.2 us
   // each: 16 tokens of one stream over 64, 8 kv heads, append and decode step, fp32 x 64 9.9 us, bf16 x 64 8.3; this way 7.3
@@ -295,7 +295,8 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
       mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
       const float mn = fmaxf(m_run[rt], mx * p.scale_log2e);
-      corr[rt] = fast_exp2(m_run[rt] - mn);
+      const float by = fast_exp2(m_run[rt] - mn);
+      if (kFine) corr[rt] = by;
       m_run[rt] = mn;
       float ps = 0.f;
 #pragma unroll
@@ -307,10 +308,10 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         }
         if (kFine) ps += (pr[t][rt][0] + pr[t][rt][1]) + (pr[t][rt][2] + pr[t][rt][3]);
       }
-      l_run[rt] = fmaf(l_run[rt], corr[rt], ps);
-      if (!kFine && !__all(corr[rt] == 1.f)) {  // (kFine: by weigh)
+      l_run[rt] = l_run[rt] * by + ps;
+      if (!kFine && !__all(by == 1.f)) {  // (kFine: by weigh)
 #pragma unroll
-        for (int c = 0; c < kMT; ++c) O[rt][c] *= corr[rt];
+        for (int c = 0; c < kMT; ++c) O[rt][c] *= by;
       }
     }
   };
@@ -417,16 +418,17 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
         q_turned = true;
       }
     };
-    if (!WHOLE && w >= nb) continue;
+    constexpr bool kAllTurn = ROPE && WHOLE;  // (one copy of turn_q's code for waves with a block and without)
+    if (!kAllTurn && w >= nb) continue;
+    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block, where it has one
     Blk A;
     f32x4 pr[kNT][RT];
-    if (!WHOLE || w < nb) {
+    if (!kAllTurn || w < nb) {
       load_k(A, w);
       load_v(A, w);
     }
     turn_q();
-    if (WHOLE && w >= nb) continue;
-    const int last = nb - 1 - (nb - 1 - w) % NW;  // this wave's last block
+    if (kAllTurn && w >= nb) continue;
     for (int b = w; b < last; b += NW) {  // the next block is requested half by half, as this one's places fall free
       scores(A, b, n_here, pr);
       load_k(A, b + NW);
@@ -484,33 +486,47 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
       mk[k] = k < n_act ? lds.mw[k][rr] : -INFINITY;
       ma = fmaxf(ma, mk[k]);
     }
-    constexpr int kSum = kFine ? 2 : NW;  // waves summed in a chain
-    f32x4 acc[NW / kSum];
-    float l[NW / kSum];
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+    if constexpr (kFine) {
+      f32x4 two[NW / 2];
+      float two_l[NW / 2];
 #pragma unroll
-    for (int k = 0; k < NW; ++k) {
-      if (k % kSum == 0) { acc[k / kSum] = f32x4{0.f, 0.f, 0.f, 0.f}; l[k / kSum] = 0.f; }
-      if (k < n_act) {
-        const float sc = fast_exp2(mk[k] - ma);
-        acc[k / kSum] += lds.o[k][slot] * sc;
-        l[k / kSum] = fmaf(lds.lw[k][rr], sc, l[k / kSum]);
+      for (int k = 0; k < NW; ++k) {
+        if (k % 2 == 0) { two[k / 2] = f32x4{0.f, 0.f, 0.f, 0.f}; two_l[k / 2] = 0.f; }
+        if (k < n_act) {
+          const float sc = fast_exp2(mk[k] - ma);
+          two[k / 2] += lds.o[k][slot] * sc;
+          two_l[k / 2] = fmaf(lds.lw[k][rr], sc, two_l[k / 2]);
+        }
+      }
+#pragma unroll
+      for (int n = NW / 4; n > 0; n /= 2)
+#pragma unroll
+        for (int k = 0; k < n; ++k) { two[k] += two[k + n]; two_l[k] += two_l[k + n]; }
+      acc = two[0];
+      l = two_l[0];
+    } else {
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        if (k < n_act) {
+          const float sc = fast_exp2(mk[k] - ma);
+          acc += lds.o[k][slot] * sc;
+          l = fmaf(lds.lw[k][rr], sc, l);
+        }
       }
     }
-#pragma unroll
-    for (int n = NW / kSum / 2; n > 0; n /= 2)
-#pragma unroll
-      for (int k = 0; k < n; ++k) { acc[k] += acc[k + n]; l[k] += l[k + n]; }
     if (rr >= R) continue;
     if constexpr (WHOLE) {
       const long long row = (long long)it.q_stream * p.Hq + g * G + rr;
-      if (l[0] == 0.f) acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};  // (nothing weighed anything: 0 / 0, as behind the merge)
-      const float o[4] = {acc[0][0] / l[0], acc[0][1] / l[0], acc[0][2] / l[0], acc[0][3] / l[0]};
+      if (l == 0.f) acc = f32x4{0.f, 0.f, 0.f, 0.f};  // (nothing weighed anything: 0 / 0, as behind the merge)
+      const float o[4] = {acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l};
       if constexpr (sizeof(T) == 4) reinterpret_cast<f32x4*>(p.out)[row * kPR + pc] = f32x4{o[0], o[1], o[2], o[3]};
       else reinterpret_cast<u32x2*>(p.out)[row * kPR + pc] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
-      if (p.lse && pc == 0) p.lse[row] = (ma + __log2f(l[0])) * kLn2;
+      if (p.lse && pc == 0) p.lse[row] = (ma + __log2f(l)) * kLn2;
     } else {
-      *reinterpret_cast<f32x4*>(p.part_acc + (it.part_row0 + rr) * D + 4 * pc) = acc[0];
-      if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(l[0] > 0.f ? ma : -INFINITY, l[0]);
+      *reinterpret_cast<f32x4*>(p.part_acc + (it.part_row0 + rr) * D + 4 * pc) = acc;
+      if (pc == 0) p.part_ml[it.part_row0 + rr] = make_float2(l > 0.f ? ma : -INFINITY, l);
     }
   }
 }
