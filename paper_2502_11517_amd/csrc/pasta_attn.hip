@@ -466,26 +466,11 @@ int launch_private_g(int G, dim3 grid, hipStream_t st, const DecodeParams& p) {
   }
   return PASTA_OK;
 }
-template <typename T, int D, int NT>
-int launch_merge_nt(int G, dim3 grid, hipStream_t st, const DecodeParams& p) {
-  switch (G) {
-    case 1: k_merge<T, D, 1, NT><<<grid, NT, 0, st>>>(p); break;
-    case 2: k_merge<T, D, 2, NT><<<grid, NT, 0, st>>>(p); break;
-    case 4: k_merge<T, D, 4, NT><<<grid, NT, 0, st>>>(p); break;
-    case 8: k_merge<T, D, 8, NT><<<grid, NT, 0, st>>>(p); break;
-    default: return PASTA_E_INVAL;
-  }
-  return PASTA_OK;
-}
-// Width of the merge work-groups: wide for steps with few output rows (a chain of latencies);
-// with many rows the launch is bound by the rate at which wavefronts start, so it gets as few
-// as the rows' parts can feed: one group of D threads when a row has about a batch of parts.
 template <typename T, int D>
-int launch_merge_g(int G, dim3 grid, hipStream_t st, const DecodeParams& p, int64_t total_parts) {
-  const int64_t rows = (int64_t)grid.x * grid.y * grid.z;
-  if (rows < kMergeManyRows) return launch_merge_nt<T, D, kMergeThreads>(G, grid, st, p);
-  if (total_parts <= 8 * rows) return launch_merge_nt<T, D, D>(G, grid, st, p);
-  return launch_merge_nt<T, D, kMergeThreadsSmall>(G, grid, st, p);
+void launch_merge_g(dim3 grid, hipStream_t st, const MergeParams& p, int64_t parts) {
+  if (parts <= merge_batch(64, D)) k_merge<T, D, 64><<<grid, 64, 0, st>>>(p);
+  else if (parts <= merge_batch(128, D)) k_merge<T, D, 128><<<grid, 128, 0, st>>>(p);
+  else k_merge<T, D, 256><<<grid, 256, 0, st>>>(p);
 }
 
 int launch_private(const pasta_attn* h, dim3 grid, hipStream_t st, const DecodeParams& p) {
@@ -496,13 +481,15 @@ int launch_private(const pasta_attn* h, dim3 grid, hipStream_t st, const DecodeP
                  : launch_private_g<uint16_t, 128>(h->G, grid, st, p);
 }
 // grid = (Hkv, G, n); total_parts = partial rows that the launch reads, over all its output rows
-int launch_merge(const pasta_attn* h, dim3 grid, hipStream_t st, const DecodeParams& p, int64_t total_parts) {
-  const int D = h->cfg.head_dim;
-  if (h->cfg.dtype == PASTA_F32)
-    return D == 64 ? launch_merge_g<float, 64>(h->G, grid, st, p, total_parts)
-                   : launch_merge_g<float, 128>(h->G, grid, st, p, total_parts);
-  return D == 64 ? launch_merge_g<uint16_t, 64>(h->G, grid, st, p, total_parts)
-                 : launch_merge_g<uint16_t, 128>(h->G, grid, st, p, total_parts);
+void launch_merge(const pasta_attn* h, dim3 grid, hipStream_t st, const MergeParams& p, int64_t total_parts) {
+  const int64_t rows = (int64_t)grid.x * grid.y * grid.z, parts = (total_parts + rows - 1) / rows;
+  if (h->cfg.dtype == PASTA_F32) {
+    if (h->cfg.head_dim == 64) launch_merge_g<float, 64>(grid, st, p, parts);
+    else launch_merge_g<float, 128>(grid, st, p, parts);
+  } else {
+    if (h->cfg.head_dim == 64) launch_merge_g<uint16_t, 64>(grid, st, p, parts);
+    else launch_merge_g<uint16_t, 128>(grid, st, p, parts);
+  }
 }
 
 struct ListPatches {  // entries of the device-resident lists that an append brings up to date
@@ -1714,13 +1701,6 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     p.clock_row0 = h->part_rows_cap - 16 * PASTA_CLK_WGS + (a->layer & 1) * 8 * PASTA_CLK_WGS;  // the tail of the (m, l) array, two halves
 #endif
     p.single_req = reqs.size() == 1 ? 1 : 0;
-    if (p.single_req && n <= 16) {  // item ranges of the streams as kernel-argument scalars
-      p.single_req = 2;
-      for (int i = 0; i < n; ++i) {
-        p.s_items[2 * i] = streams[i].item_begin;
-        p.s_items[2 * i + 1] = streams[i].item_end - streams[i].item_begin;
-      }
-    }
     p.req0 = reqs[0];
 
     const bool rope = rope_q || p.pend_rope;
@@ -1804,8 +1784,19 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     for (int i = 0; i < n; ++i)
       merge_parts += (int64_t)(reqs[stream_req_idx[i]].n_chunks + streams[i].item_end - streams[i].item_begin) * c.n_q_heads;
     if (!probe && !partials_only && !one) {
-      rc = launch_merge(h, dim3((unsigned)Hkv, (unsigned)G, (unsigned)n), st, p, merge_parts);
-      if (rc != PASTA_OK) return rc;
+      MergeParams mp;  // (what is not filled in is not read)
+      mp.out = p.out;
+      mp.lse = p.lse;
+      mp.part_acc = p.part_acc;
+      mp.part_ml = p.part_ml;
+      mp.meta = n <= kMergeRecs ? nullptr : p.meta;
+      mp.off_streams = p.off_streams;
+      mp.priv_part_base = p.priv_part_base;
+      mp.Hkv = Hkv;
+      mp.G = G;
+      for (int i = 0; i < n && n <= kMergeRecs; ++i)
+        mp.rec[i] = MergeRec{streams[i].m_pre0, streams[i].m_n_pre, streams[i].m_R, streams[i].item_begin, streams[i].item_end - streams[i].item_begin};
+      launch_merge(h, dim3((unsigned)Hkv, (unsigned)G, (unsigned)n), st, mp, merge_parts);
     }
     if (meta_slot >= 0) {
       rc = ring_give(h);

@@ -126,8 +126,6 @@ struct DecodeParams {
   // q / k_pend pointing at those; k_direct and k_one go by both flags themselves, as they load the rows.
   int rope_q;           // 1: Q rows are to be turned by their streams' position ids
   int pend_rope;        // 1: the deferred K rows are still unrotated (PASTA_APPEND_ROPE), to be turned by pend_pos
-  int32_t s_items[32];  // single_req with <= 16 streams: stream i's private items are
-                        //   [s_items[2i], s_items[2i] + s_items[2i+1]) -- spares the merge a table look-up
   const uint8_t* dense_mask;  // comparison mode: 0/1 per (stream, slot); null otherwise
   const DevItem* items;       // a plan kept on the device (k_plan): the private work items and, priv_chunk entries per
   const int32_t* codes;       // item, the row of every token (physical row, or -(1 + row) of a deferred append); else null
@@ -162,13 +160,6 @@ __device__ __forceinline__ int32_t meta_word(const DecodeParams& p, int word) {
   typedef const char __attribute__((address_space(4))) * kernarg_ptr;
   kernarg_ptr ka = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   return *(const int32_t __attribute__((address_space(4)))*)(ka + __builtin_offsetof(DecodeParams, inline_meta) + 4 * word);
-}
-
-__device__ __forceinline__ const int32_t* s_items_of(const DecodeParams& p) {
-  (void)p;
-  typedef const char __attribute__((address_space(4))) * kernarg_ptr;
-  kernarg_ptr ka = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-  return (const int32_t*)(ka + __builtin_offsetof(DecodeParams, s_items));
 }
 
 __device__ __forceinline__ const int32_t* pend_dst_of(const DecodeParams& p) {
