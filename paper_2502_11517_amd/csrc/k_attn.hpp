@@ -73,7 +73,7 @@ struct BlockRegs { u32x4 k[8], v[8]; };  // one lane's share of a 32-token block
 // (FORM only keeps the instantiations of different kernels apart: the host pass of the compiler cannot
 // check this body -- it has no device builtins -- and refuses a specialization it has already tried)
 template <bool PAGED, bool GATHER, bool DENSE, bool LONG, bool PROBE, bool KEPT, int FORM>
-__device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi) {
+__device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, const_words meta, int wi) {
   constexpr int D = 128;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -86,9 +86,10 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
   int req, g, R, n_tok, slot0, stride, gather_pos, pend0, pend_src0;
   int row0 = 0;  // first stacked row of this item's row group (shared-prefix items)
   long long part_row0;
-  const int32_t* req_streams = nullptr;
+  const_words req_streams = nullptr;
   int q_stream = 0, n_req_streams = 0;
   bool listed = false;
+  const int my_tok = kBlock * w + l32 + 4 * kBlock * hh;  // gather items: this lane's token of the wave's first two blocks, all it can have
   if constexpr (!GATHER) {
     DevReq rq;
     if (p.single_req) {  // scalar loads from the kernel arguments
@@ -97,13 +98,7 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
       rq.chunk_tokens = p.req0.chunk_tokens; rq.part_base = p.req0.part_base;
       rq.pend0 = p.req0.pend0; rq.pend_src0 = p.req0.pend_src0;
     } else {
-      const DevReq* reqs = reinterpret_cast<const DevReq*>(meta + p.off_reqs);
-      int qi = 0;
-      for (; qi < p.n_reqs - 1; ++qi) {
-        const int b = reqs[qi].wg_begin;
-        if (wi >= b && wi < b + reqs[qi].n_chunks * p.Hkv * ((reqs[qi].n_streams * G + 31) >> 5)) break;
-      }
-      rq = reqs[qi];
+      rq = record<DevReq>(meta + p.off_reqs, request_of(p, meta, wi));
       req_streams = meta + p.off_req_streams + rq.stream0;
     }
     // kv head = work-group index mod Hkv: with 8 kv heads every work-group of head g (private
@@ -129,19 +124,20 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
     pend0 = rq.pend0;
     pend_src0 = rq.pend_src0;
   } else {
-    const int item = wi / p.Hkv;
+    const int item = __builtin_amdgcn_readfirstlane(wi / p.Hkv);
     g = wi % p.Hkv;
     // the work item: of a plan kept on the device its ranges are resolved and its tokens' rows written out
     // (k_plan); otherwise both are worked out here from the blob
-    const DevItem it = KEPT ? p.items[item] : reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
-    const int nr = it.n_ranges > 1 ? it.n_ranges : 0;  // blob: the ranges to bring into LDS
+    int code = 0;  // kept: the row of token my_tok, read beside the item's record
+    if (KEPT && my_tok < p.priv_chunk) code = p.codes[(long long)item * p.priv_chunk + my_tok];
+    const DevItem it = record<DevItem>(KEPT ? words_at(p.items) : meta + p.off_items, item);
     const bool coded = KEPT && (PAGED || it.n_ranges > 0);
     if (KEPT) {
       req = coded ? 0 : -it.n_ranges; pend0 = coded ? INT32_MAX : it.range_first; pend_src0 = it.tok_begin;
     } else if (p.single_req) {  // scalars from the kernel arguments
       req = p.req0.req; pend0 = p.req0.pend0; pend_src0 = p.req0.pend_src0;
     } else {
-      const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[it.stream];
+      const DevStream st = record<DevStream>(meta + p.off_streams, it.stream);
       req = st.req; pend0 = st.pend0; pend_src0 = st.pend_src0;
     }
     R = G;
@@ -158,34 +154,33 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
       for (int j = tid; j < kGatherMax; j += kAttnThreads)
         lds.mask[j] = j < n_tok ? p.dense_mask[mb + slot0 + j] : 0;  // published by the Q barrier
     }
-    if (KEPT && coded) {
-      const int32_t* codes = p.codes + (long long)item * p.priv_chunk;
-      for (int j = tid; j < n_tok; j += kAttnThreads) {
-        const int code = codes[j];
-        lds.rows[j] = code;
-        if (p.dbg_rows && g == 0) p.dbg_rows[gather_pos + j] = phys_of_code(p, code);
+    // A wave brings the rows of its own blocks alone into LDS, so nobody waits for another wave: what stands between a private item's
+    // start and its first request is the launch's longest chain (2.3 us against 1.1 of a shared-prefix item).  With the records by scalar
+    // loads, the kept codes beside them and a barrier less, an append and decode step of 1024 + 4 x 32 .. 256 tokens went from 10.5
+    // to 10.3 us.  (Up to eight ranges in scalar registers instead of LDS: slower, 10.4; the code that selects them is fetched, too.)
+    auto put_row = [&](int j, int row, int phys) {
+      if (j >= n_tok) return;
+      lds.rows[j] = row;
+      if (p.dbg_rows && g == 0) p.dbg_rows[gather_pos + j] = phys;
+    };
+    if (KEPT && coded) put_row(my_tok, code, p.dbg_rows && my_tok < n_tok ? phys_of_code(p, code) : 0);
+    if (!KEPT && listed) {  // ranges the item overlaps -> LDS, then every token of the item -> row code; deferred rows: -(1 + row)
+      for (int r = tid; r < it.n_ranges; r += kAttnThreads) lds.ranges[r] = record<DevRange>(meta + p.off_ranges, it.range_first + r);
+      __syncthreads();
+      const int tok = it.tok_begin + min(my_tok, n_tok - 1);
+      int lo = 0, hi = it.n_ranges - 1;  // last range with cum <= tok
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (lds.ranges[mid].cum <= tok) lo = mid; else hi = mid - 1;
       }
-      __syncthreads();
+      const DevRange rg = lds.ranges[lo];
+      const int slot = rg.start + (tok - rg.cum) * rg.stride;
+      const int phys = phys_row(p.lay, p.page_table, req, slot);
+      put_row(my_tok, slot >= pend0 ? -1 - (pend_src0 + (slot - pend0)) : phys, phys);
     }
-    if (!KEPT && listed) {  // ranges the item overlaps -> LDS, then every token of the item -> row code
-      const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
-      for (int r = tid; r < nr; r += kAttnThreads) lds.ranges[r] = ranges[it.range_first + r];
-      __syncthreads();
-      for (int j = tid; j < n_tok; j += kAttnThreads) {
-        const int tok = it.tok_begin + j;
-        int lo = 0, hi = nr - 1;  // last range with cum <= tok
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (lds.ranges[mid].cum <= tok) lo = mid; else hi = mid - 1;
-        }
-        const DevRange rg = lds.ranges[lo];
-        const int slot = rg.start + (tok - rg.cum) * rg.stride;
-        const int phys = phys_row(p.lay, p.page_table, req, slot);
-        lds.rows[j] = slot >= pend0 ? -1 - (pend_src0 + (slot - pend0)) : phys;  // deferred rows: -(1 + row)
-        if (p.dbg_rows && g == 0) p.dbg_rows[gather_pos + j] = phys;
-      }
-      __syncthreads();
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   // (work-group-uniform values, but loaded per lane: tell the compiler, so that the branches on
   // them are scalar and its wait-count bookkeeping sees an exhaustive if / else)
@@ -451,14 +446,13 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
 
   auto report_rows = [&]() {
     if (p.dbg_rows && g == 0 && row0 == 0 && !listed) {  // listed items reported their rows while expanding
-      const DevStream* streams = reinterpret_cast<const DevStream*>(meta + p.off_streams);
       for (int j = tid; j < n_tok; j += kAttnThreads) {
         const int phys = phys_of(j);
         if constexpr (GATHER) {
           p.dbg_rows[gather_pos + j] = phys;
         } else {
           for (int k = 0; k < n_req_streams; ++k)
-            p.dbg_rows[streams[req_streams ? req_streams[k] : k].gather_base + gather_pos + j] = phys;
+            p.dbg_rows[record<DevStream>(meta + p.off_streams, req_streams ? req_streams[k] : k).gather_base + gather_pos + j] = phys;
         }
       }
     }
@@ -803,7 +797,7 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
 }
 
 template <bool PAGED, bool PROBE, bool KEPT>
-__device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi);
+__device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const_words meta, int wi);
 
 // One launch for all partials of a decode step; the shared-prefix items' work-groups come
 // first, the private (gather) items' after them.
@@ -820,7 +814,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
   static_assert(!LONG || !DENSE, "the long-item variant exists for the list mode");
   static_assert(!WIDE || (!DENSE && !LONG), "the wide form replaces the shared-prefix items of the list mode");
   __shared__ AttnLds lds;
-  const int32_t* meta = meta_of(p);
+  const const_words meta = meta_words(p);
   // The deferred append's copy into the pool (K1's job).  No work-group of this launch reads those
   // pool rows -- lists that name them are served from k_pend / v_pend -- so the copy needs no
   // ordering against the rest of the launch.  Normally it is spread thin: work-group b moves
@@ -880,7 +874,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
 // owns its rows' (m, l, O) for the whole chunk.  Q stays in registers (the B operands of S^T = K Q^T,
 // fetched once per item).
 template <bool PAGED, bool PROBE, bool KEPT>
-__device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const int32_t* meta, int wi) {
+__device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const_words meta, int wi) {
   constexpr int D = 128;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -891,20 +885,14 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
 
   // ---- decode the work item
   DevReq rq;
-  const int32_t* req_streams = nullptr;
+  const_words req_streams = nullptr;
   if (p.single_req) {
     rq.req = p.req0.req; rq.pc = p.req0.pc; rq.n_streams = p.req0.n_streams; rq.stream0 = 0;
     rq.wg_begin = p.req0.wg_begin; rq.n_chunks = p.req0.n_chunks;
     rq.chunk_tokens = p.req0.chunk_tokens; rq.part_base = p.req0.part_base;
     rq.pend0 = p.req0.pend0; rq.pend_src0 = p.req0.pend_src0;
   } else {
-    const DevReq* reqs = reinterpret_cast<const DevReq*>(meta + p.off_reqs);
-    int qi = 0;
-    for (; qi < p.n_reqs - 1; ++qi) {
-      const int b = reqs[qi].wg_begin;
-      if (wi >= b && wi < b + reqs[qi].n_chunks * p.Hkv * ((reqs[qi].n_streams * G + 127) >> 7)) break;
-    }
-    rq = reqs[qi];
+    rq = record<DevReq>(meta + p.off_reqs, request_of(p, meta, wi));
     req_streams = meta + p.off_req_streams + rq.stream0;
   }
   const int R_all = rq.n_streams * G;
@@ -944,11 +932,10 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
     }
   }
   if (p.dbg_rows && g == 0 && quad == 0) {
-    const DevStream* streams = reinterpret_cast<const DevStream*>(meta + p.off_streams);
     for (int j = tid; j < n_tok; j += kAttnThreads) {
       const int phys = phys_row(p.lay, p.page_table, req, slot0 + j);
       for (int k = 0; k < rq.n_streams; ++k)
-        p.dbg_rows[streams[req_streams ? req_streams[k] : k].gather_base + slot0 + j] = phys;
+        p.dbg_rows[record<DevStream>(meta + p.off_streams, req_streams ? req_streams[k] : k).gather_base + slot0 + j] = phys;
     }
   }
 

@@ -98,7 +98,7 @@ __device__ __forceinline__ void rope_lane(u32x4 (&x)[NP], int q, int pos, const 
 struct DirItem {
   int n_tok, R, g;
   long long part_row0;
-  const int32_t* req_streams;  // shared-prefix item: the request's streams (null: stack block s is stream s)
+  const_words req_streams;     // shared-prefix item: the request's streams (null: stack block s is stream s)
   int row0;                    // ... its first stacked row
   int q_stream;                // private item: its stream
   int q_pos;                   // (WHOLE) its query's position id,
@@ -110,7 +110,7 @@ struct DirItem {
 // heads of one stream; otherwise rows row0 .. of the request's stack.
 // WHOLE: the item is all that its stream sees, and what is written is the result instead of a partial row.
 template <typename T, int D, int RT, int NW, bool GATHER, bool ROPE, bool WHOLE, class Lds, class CodeOf>
-__device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, const int32_t* meta, const DirItem& it, CodeOf code_of) {
+__device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, const_words meta, const DirItem& it, CodeOf code_of) {
   typedef DirBlock<T, D> Blk;
   constexpr int kTok = Blk::kTok, kNT = Blk::kNT, kNP = Blk::kNP, kMT = D / 16;
   constexpr int kPieceRow = D * (int)sizeof(T) / 16;
@@ -143,7 +143,7 @@ __device__ __forceinline__ void direct_rows(const DecodeParams& p, Lds& lds, con
     for (int kk = 0; kk < kNP; ++kk) qf[rt][kk] = *reinterpret_cast<const u32x4*>(src + kk * 64);
     qpos[rt] = 0;
     if constexpr (ROPE) {
-      if (!WHOLE && p.rope_q) qpos[rt] = reinterpret_cast<const DevStream*>(meta + p.off_streams)[s].pos;
+      if (!WHOLE && p.rope_q) qpos[rt] = record<DevStream>(meta + p.off_streams, s).pos;
     }
   }
 
@@ -568,7 +568,7 @@ __device__ __forceinline__ uint32_t direct_code(const DecodeParams& p, int req, 
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
   __shared__ DirLds<D, 2, 4> lds;
-  const int32_t* meta = meta_of(p);
+  const const_words meta = meta_words(p);
   const int tid = threadIdx.x;
   if (p.pend_n > 0) direct_copy_pending<T, D, ROPE>(p, (int)blockIdx.x, (int)gridDim.x);
   const int n_prefix_wgs = (int)gridDim.x - p.n_mfma_items * p.Hkv;
@@ -583,13 +583,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
     if (p.single_req) {
       rq = p.req0;
     } else {
-      const DevReq* reqs = reinterpret_cast<const DevReq*>(meta + p.off_reqs);
-      int qi = 0;
-      for (; qi < p.n_reqs - 1; ++qi) {
-        const int b = reqs[qi].wg_begin;
-        if (wi >= b && wi < b + reqs[qi].n_chunks * p.Hkv * ((reqs[qi].n_streams * G + 31) >> 5)) break;
-      }
-      rq = reqs[qi];
+      rq = record<DevReq>(meta + p.off_reqs, request_of(p, meta, wi));
       it.req_streams = meta + p.off_req_streams + rq.stream0;
     }
     const int R_all = rq.n_streams * G, n_rg = (R_all + 31) >> 5;
@@ -602,13 +596,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
     it.n_tok = __builtin_amdgcn_readfirstlane(min(rq.chunk_tokens, rq.pc - slot0));
     it.part_row0 = rq.part_base + (long long)(it.g * rq.n_chunks + c) * R_all + it.row0;
     const bool report = p.dbg_rows && it.g == 0 && it.row0 == 0;
-    const DevStream* streams = reinterpret_cast<const DevStream*>(meta + p.off_streams);
     auto code_of = [&](int j) -> uint32_t {
       int phys;
       const uint32_t code = direct_code<T, D>(p, rq.req, slot0 + j, it.g, rq.pend0, rq.pend_src0, phys);
       if (report)
         for (int k = 0; k < rq.n_streams; ++k)
-          p.dbg_rows[streams[it.req_streams ? it.req_streams[k] : k].gather_base + slot0 + j] = phys;
+          p.dbg_rows[record<DevStream>(meta + p.off_streams, it.req_streams ? it.req_streams[k] : k).gather_base + slot0 + j] = phys;
       return code;
     };
     if (it.R > 16) direct_rows<T, D, 2, 4, false, ROPE, false>(p, lds, meta, it, code_of);
@@ -617,24 +610,22 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_direct(DecodeParams p) {
   }
   // ---- a piece of one stream's private list
   const int wi = (int)blockIdx.x - n_prefix_wgs;
-  const int item = wi / p.Hkv;
+  const int item = __builtin_amdgcn_readfirstlane(wi / p.Hkv);
   it.g = __builtin_amdgcn_readfirstlane(wi % p.Hkv);
   const bool kept = p.codes != nullptr;  // a plan kept on the device: its tokens' rows are written out
-  const DevItem di = kept ? p.items[item] : reinterpret_cast<const DevItem*>(meta + p.off_items)[item];
+  const DevItem di = record<DevItem>(kept ? words_at(p.items) : meta + p.off_items, item);
   const int32_t* codes = p.codes + (long long)item * p.priv_chunk;
-  int nr = !kept && di.n_ranges > 1 ? di.n_ranges : 0;
+  const int nr = !kept && di.n_ranges > 1 ? di.n_ranges : 0;
   int req = 0, pend0 = INT32_MAX, pend_src0 = 0;
   if (kept) {
   } else if (p.single_req) {
     req = p.req0.req; pend0 = p.req0.pend0; pend_src0 = p.req0.pend_src0;
   } else {
-    const DevStream st = reinterpret_cast<const DevStream*>(meta + p.off_streams)[di.stream];
+    const DevStream st = record<DevStream>(meta + p.off_streams, di.stream);
     req = st.req; pend0 = st.pend0; pend_src0 = st.pend_src0;
   }
-  nr = __builtin_amdgcn_readfirstlane(nr);
   if (nr > 0) {  // the ranges the piece overlaps -> LDS
-    const DevRange* ranges = reinterpret_cast<const DevRange*>(meta + p.off_ranges);
-    for (int k = tid; k < nr; k += kAttnThreads) lds.ranges[k] = ranges[di.range_first + k];
+    for (int k = tid; k < nr; k += kAttnThreads) lds.ranges[k] = record<DevRange>(meta + p.off_ranges, di.range_first + k);
     __syncthreads();
   }
   it.n_tok = __builtin_amdgcn_readfirstlane(di.tok_count);
@@ -690,7 +681,7 @@ __global__ __launch_bounds__(kOneWaves * 64) void k_one(DecodeParams p) {
   }
   // The plan always rides in the kernel arguments here (small_step): its records are read with scalar loads
   // (8 kv heads x 128, 128 .. 300 + 1 .. 8 x 20 .. 60 tokens: 0.3 us of 6.4 .. 8.4).
-  typedef const int32_t __attribute__((address_space(4))) * words;
+  typedef const_words words;
   typedef const char __attribute__((address_space(4))) * kernarg_ptr;
   const words meta = (words)((kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr() + __builtin_offsetof(DecodeParams, inline_meta));
   const int item = __builtin_amdgcn_readfirstlane((int)blockIdx.x / p.Hkv);
