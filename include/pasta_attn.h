@@ -318,7 +318,7 @@ typedef struct {
                                    dbg_plan[4]); the private part of (item j, kv head g, head in group i) is row
                                    dbg_plan[7] + (j * Hkv + g) * G + i, the items of a stream being consecutive
                                    128-token pieces of its list beyond the common prefix, stream after stream
-                                   (256-token pieces when the step takes the four-groups-per-work-group form,
+                                   (or 64-token pieces, fp32 128-wide heads; 256-token pieces when the step takes the four-groups-per-work-group form,
                                    see PASTA_DECODE_FOUR_GROUPS; a step that reads the device-resident lists cuts the
                                    visible head beyond the common prefix and the range list into pieces separately). */
   void *prof_event_start;       /* hipEvent_t or NULL (both or neither): they receive the start and the */

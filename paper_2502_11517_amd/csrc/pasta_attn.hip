@@ -1355,6 +1355,35 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         if (n_prefixes > 1 && n_wgs > h->n_cus) chunk_tokens = std::max<int64_t>(kManyChunk, chunk_tokens * 2 / 3 / kTile * kTile);
       }
       priv_chunk = wide ? 256 : 128;  // (beside the long wide work-groups the private items get one slot per CU: longer items keep more in flight there)
+      if (direct && !one && c.dtype == PASTA_F32 && D == 128) {
+        // The blocks of this kind are 16 tokens: pieces of 64 give each of four waves one, as 128 do elsewhere.  Not where they make more
+        // CUs take a first or a second work-group than there are, where beyond that they are more than 1.4 times as many, or where they make
+        // the plan too large for the kernel arguments.  Append and decode step of 8 kv heads, pieces of 128 -> 64 (us; work-groups):
+        //   1024 + 4 x 64 .. 512 tokens 10.9 -> 9.9 (176 -> 216), 4096 + 8 x 64 .. 512 20.4 -> 18.8 (384 -> 496), six requests of
+        //     1024 + 4 x 64 .. 256 30.3 -> 25.8 (600 -> 832)
+        //   not taken: 1024 + 6 x 64 .. 512 12.2 -> 14.4 (216 -> 288), 4096 + 8 x 300 .. 512 20.5 -> 22.6 (472 -> 656), six requests of
+        //     1024 + 4 x 300 .. 512 35.9 -> 37.2 (960 -> 1560)
+        struct At { int64_t words, wgs; };
+        auto plan_at = [&](int64_t piece) {
+          At at{(int64_t)n * (int64_t)(sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (int64_t)(sizeof(DevReq) / 4) + 8, 0};
+          int64_t items = 0;
+          for (int i = 0; i < n; ++i) {
+            const ListView& v = lv[i];
+            int64_t priv = (int64_t)v.prefix_len - reqs[stream_req_idx[i]].pc;
+            for (int k = 0; k < v.n_ranges; ++k) priv += v.at(k).count;
+            at.words += ((int64_t)v.n_ranges + 1) * 4;
+            items += (priv + piece - 1) / piece;
+          }
+          at.words += items * (int64_t)(sizeof(DevItem) / 4);
+          at.wgs = items * Hkv;
+          for (auto& q : reqs) at.wgs += (q.pc + chunk_tokens - 1) / chunk_tokens * Hkv * row_units(q);
+          return at;
+        };
+        const At by_64 = plan_at(64), by_128 = plan_at(128);
+        auto turn = [&](int64_t wgs) { return std::min<int64_t>((wgs + h->n_cus - 1) / h->n_cus, 3); };
+        if (turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs) &&
+            (by_64.words <= kInlineMetaWords || by_128.words > kInlineMetaWords)) priv_chunk = 64;
+      }
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
       if (one) priv_chunk = kOneTokens;  // a stream's whole list
       else if (h->tune_priv_chunk >= 32) priv_chunk = std::min<int64_t>(h->tune_priv_chunk / 32 * 32, kGatherMax);  // whole 32-token blocks

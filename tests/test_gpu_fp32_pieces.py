@@ -1,0 +1,35 @@
+"""Private pieces of fp32 steps of 128-wide heads (GPU): 64 tokens where they do not make another turn of work-groups or the plan too large
+for the kernel arguments, 128 elsewhere -- either way against the oracle, around a piece's and a block's end."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2502_11517_amd import binding as B
+from paper_2502_11517_amd import workloads as W
+from util import OraclePool, check_close, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hkv,prefix,lengths,inter,piece", [
+    (8, 1024, [15, 64, 65, 128], "round_robin", 64), (8, 1024, [63, 16, 129, 17], "random", 64), (1, 300, [193, 1], "random", 64),
+    (8, 1024, [250] * 6, "round_robin", 128), (8, 1024, [320] * 8, "random", 64), (8, 1024, [140] * 8, "round_robin", 128),
+])
+def test_pieces_of_fp32_lists(hkv, prefix, lengths, inter, piece):
+    from paper_2502_11517_amd.harness import Session, to_host_bits
+    w = W.single_request("pieces", "f32", 4 * hkv, hkv, 128, 1.0, 61, prefix, lengths, inter, k_std=128 ** -0.5)
+    s = Session(w)
+    s.append_events(w.n_prefill)
+    pl, offs, _, ct, _ = w.lists(0)
+    pc = int(pl.min())
+    private = [int(pl[i]) - pc + int(ct[offs[i]:offs[i + 1]].sum()) for i in range(w.n)]
+    plan = np.zeros(8, np.int64)
+    s.h.decode_step(0, w.dec_request, w.dec_stream, None, None, lists=w.lists(0), flags=B.DECODE_PLAN_ONLY, dbg_plan=plan)
+    assert plan[2] == sum(-(-t // piece) for t in private), (plan, private)
+    ref, lse_ref = OraclePool(w).append_events(w.n_prefill).attention()
+    for explicit in (True, False):
+        out, lse, _ = s.decode(0, explicit=explicit, flags=B.DECODE_ROW_GROUPS)
+        check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
+        assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= 1e-4
+    s.close()
