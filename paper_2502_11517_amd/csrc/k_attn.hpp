@@ -865,14 +865,42 @@ __global__ __launch_bounds__(kAttnThreads, 2) void k_attn(DecodeParams p) {
 
 // K2 for a request with MORE than 32 stacked rows (many streams, or a wide GQA group): the rows are
 // served in groups of 32, and here the four waves of a work-group take one row group EACH over the
-// same tokens.  Work item = (request, kv head, split-K chunk, four row groups).  A round is four
-// 32-token blocks: wave w brings block 4 r + w into tile w (through its registers, requested one
-// round ahead), a barrier publishes the four tiles, every wave computes all four blocks for its own
-// 32 rows, a second barrier frees the tiles.  So the chunk crosses the memory system once per FOUR
-// row groups (the row-group form of attn_item reads it once per group -- from L2, but the L2-to-CU
-// traffic is what that form is bound by), and there is nothing to combine at the end: each wave
-// owns its rows' (m, l, O) for the whole chunk.  Q stays in registers (the B operands of S^T = K Q^T,
-// fetched once per item).
+// same tokens.  Work item = (request, kv head, split-K chunk, four row groups).  The chunk goes through a ring
+// of four 32-token tiles in LDS, filled by loads straight into it: all waves bring a quarter of a tile each, three
+// tiles are on their way while one is computed, and one barrier per tile both publishes it and frees the tile
+// before it.  So the chunk crosses the memory system once per FOUR row groups (the row-group form of attn_item
+// reads it once per group -- from L2, but the L2-to-CU traffic is what that form is bound by), and there is
+// nothing to combine at the end: each wave owns its rows' (m, l, O) for the whole chunk.  Q stays in registers
+// (the B operands of S^T = K Q^T, fetched once per item).
+// What bounds it: with one such work-group per CU, the chain of one wave's tile (0.65 us where the products and the vector work alone
+// take 0.2 each); its requests alone are served at 6.2 TB/s.  Before, a round of four tiles came through registers, one round ahead, and
+// its scores waited for one LDS read after the other: append and decode step, 8 kv heads (us) 32k + 16 streams of 8 heads 46.2 -> 40.0,
+// the same with a nested fork and 256 .. 2048 own tokens 57.0 -> 54.8, 16k + 32 streams of 4 heads 30.0 -> 27.6, 32k + 12 streams of 8
+// heads in pages of 8 tokens 58.0 -> 44.1.
+constexpr int kRingTiles = 4;
+
+// The V^T operands of a 32-token tile: [contraction step][M-tile][token rows 8 e4 .. 8 e4 + 7 of the step].  All sixteen
+// transposing reads in one block that waits for them itself: as single intrinsics each gets a wait for the last load into LDS
+// that was issued, which here is the one three tiles ahead.
+__device__ __forceinline__ void lds_read_v(u32x2 (&x)[2][4][2], const uint32_t (&at)[4]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %16 offset:8192\n\tds_read_b64_tr_b16 %1, %16 offset:10240\n\t"
+      "ds_read_b64_tr_b16 %2, %17 offset:8192\n\tds_read_b64_tr_b16 %3, %17 offset:10240\n\t"
+      "ds_read_b64_tr_b16 %4, %18 offset:8192\n\tds_read_b64_tr_b16 %5, %18 offset:10240\n\t"
+      "ds_read_b64_tr_b16 %6, %19 offset:8192\n\tds_read_b64_tr_b16 %7, %19 offset:10240\n\t"
+      "ds_read_b64_tr_b16 %8, %16 offset:12288\n\tds_read_b64_tr_b16 %9, %16 offset:14336\n\t"
+      "ds_read_b64_tr_b16 %10, %17 offset:12288\n\tds_read_b64_tr_b16 %11, %17 offset:14336\n\t"
+      "ds_read_b64_tr_b16 %12, %18 offset:12288\n\tds_read_b64_tr_b16 %13, %18 offset:14336\n\t"
+      "ds_read_b64_tr_b16 %14, %19 offset:12288\n\tds_read_b64_tr_b16 %15, %19 offset:14336\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(x[0][0][0]), "=&v"(x[0][0][1]), "=&v"(x[0][1][0]), "=&v"(x[0][1][1]), "=&v"(x[0][2][0]), "=&v"(x[0][2][1]), "=&v"(x[0][3][0]),
+        "=&v"(x[0][3][1]), "=&v"(x[1][0][0]), "=&v"(x[1][0][1]), "=&v"(x[1][1][0]), "=&v"(x[1][1][1]), "=&v"(x[1][2][0]), "=&v"(x[1][2][1]),
+        "=&v"(x[1][3][0]), "=&v"(x[1][3][1])
+      : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3])
+      : "memory");
+}
+static_assert(offsetof(AttnTile, vt) == 8192 && sizeof(AttnTile) == 16384, "offsets of lds_read_v");
+
 template <bool PAGED, bool PROBE, bool KEPT>
 __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& lds, const_words meta, int wi) {
   constexpr int D = 128;
@@ -907,7 +935,7 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
   const int R = __builtin_amdgcn_readfirstlane(max(0, min(32, R_all - row0)));  // 0: a wave that only carries tiles
   const int slot0 = __builtin_amdgcn_readfirstlane(c * rq.chunk_tokens);  // a multiple of 64
   const int n_tok = __builtin_amdgcn_readfirstlane(min(rq.chunk_tokens, rq.pc - slot0));
-  const int n_blocks = (n_tok + kBlock - 1) / kBlock;
+  const int n_tiles = (n_tok + kBlock - 1) / kBlock;
   const long long part_row0 = rq.part_base + (long long)(g * rq.n_chunks + c) * R_all + row0;
   const int pend0 = __builtin_amdgcn_readfirstlane(rq.pend0);  // slots from here on are rows of a deferred append
   const int pend_src0 = __builtin_amdgcn_readfirstlane(rq.pend_src0);
@@ -923,13 +951,10 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
   {
     const int ra = row0 + l32;
     const bool live = l32 < R;
-    const int s = live ? (req_streams ? req_streams[ra / G] : ra / G) : 0;
+    const int row = min(ra, R_all - 1) / G, s = req_streams ? req_streams[row] : row;
     const char* qrow = reinterpret_cast<const char*>(p.q) + (long long)(s * p.Hq + (g * G + (live ? ra % G : 0))) * (D * 2);
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      qreg[kk] = *reinterpret_cast<const u32x4*>(qrow + (2 * kk + hh) * 16);
-      if (!live) qreg[kk] = u32x4{0u, 0u, 0u, 0u};  // rows past R are zero
-    }
+    for (int kk = 0; kk < 8; ++kk) qreg[kk] = *reinterpret_cast<const u32x4*>(qrow + (2 * kk + hh) * 16);
   }
   if (p.dbg_rows && g == 0 && quad == 0) {
     for (int j = tid; j < n_tok; j += kAttnThreads) {
@@ -939,62 +964,92 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
     }
   }
 
-  // ---- block loads: lane -> piece (lane & 15) of rows (lane >> 4) + 4 i.  A full block inside the
-  // chunk is two runs of 16 consecutive slots, each inside one page (pages of 16 tokens or more):
-  // wave-uniform base per run (page-table entries through scalar loads), lane part in the offset
-  // register, row step in the scalar offset.  The chunk's ragged last block takes one address per row.
+  // ---- tile loads, straight into LDS: of a tile's 32 tokens wave w brings rows 8 w .. 8 w + 7, two loads of K and two of V
+  // (lane l lands at piece l % 16 of row l / 16 of four, so the swizzle is on the global side).  A full tile's eight rows lie
+  // in one page (pages of 8 tokens or more): a wave-uniform base in the scalar offset, a lane part worked out once; the
+  // page-table entry comes by a scalar load, a tile ahead.  Ragged tiles and those with deferred rows: an address per row.
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const __amdgpu_buffer_rsrc_t k_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kb), 0, -1, kRawBuffer);
+  const __amdgpu_buffer_rsrc_t v_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vb), 0, -1, kRawBuffer);
   const uint32_t row_bytes = (uint32_t)p.lay.slot_stride * 2u;
-  const uint32_t lane_n = (uint32_t)rbase * row_bytes + (uint32_t)(piece * 16);
-  const bool runs_ok = !PAGED || p.lay.page_shift >= 4;
-  auto load_block = [&](BlockRegs& br, int b) {
-    if (runs_ok && b * kBlock + kBlock <= n_tok && slot0 + b * kBlock + kBlock <= pend0) {
-      int pp[2] = {0, 0};
-      if constexpr (PAGED) {
+  const uint32_t piece_k[2] = {(uint32_t)(piece ^ rbase ^ (8 * (w & 1))) * 16u, (uint32_t)(piece ^ rbase ^ (8 * (w & 1)) ^ 4) * 16u};
+  const uint32_t piece_v = (uint32_t)(piece ^ (rbase << 2)) * 16u;
+  const uint32_t lane_row = (uint32_t)rbase * row_bytes;
+  auto full = [&](int t) -> bool {  // 32 existing tokens, none of them a deferred row
+    return (!PAGED || p.lay.page_shift >= 3) && t * kBlock + kBlock <= n_tok && slot0 + t * kBlock + kBlock <= pend0;
+  };
+  auto page_of = [&](int t) -> int {  // page-table entry of this wave's rows of tile t
+    if constexpr (PAGED) {
+      if (t < n_tiles && full(t)) return scalar_load_i32(p.page_table, req * p.lay.pages_per_request + ((slot0 + t * kBlock + 8 * w) >> p.lay.page_shift));
+    }
+    return 0;
+  };
+  auto request = [&](int t, int page) {  // four loads at least
+    AttnTile& tile = lds.tile[t % kRingTiles];
+    u32x4 *const kd = tile.kt + 128 * w, *const vd = tile.vt + 128 * w;
+    if (full(t)) {
+      const int slot = slot0 + t * kBlock + 8 * w;
+      const int phys = PAGED ? ((page << p.lay.page_shift) | (slot & p.lay.page_mask)) : req * p.lay.pool_tokens + slot;
+      const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(elem_off(p.lay, phys, g) * 2));
 #pragma unroll
-        for (int hb = 0; hb < 2; ++hb)
-          pp[hb] = scalar_load_i32(p.page_table, req * p.lay.pages_per_request + ((slot0 + b * kBlock + 16 * hb) >> p.lay.page_shift));
+      for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rs, (lds_ptr)(kd + 64 * i), 16, lane_row + piece_k[i], base + (uint32_t)(4 * i) * row_bytes, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rs, (lds_ptr)(vd + 64 * i), 16, lane_row + piece_v, base + (uint32_t)(4 * i) * row_bytes, 0, 0);
+    } else {
+      const __amdgpu_buffer_rsrc_t kp_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kpend), 0, -1, kRawBuffer);
+      const __amdgpu_buffer_rsrc_t vp_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vpend), 0, -1, kRawBuffer);
+      uint32_t off[2];
+      bool pnd[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int slot = slot0 + min(t * kBlock + 8 * w + 4 * i + rbase, n_tok - 1);  // rows past the end repeat the last one
+        pnd[i] = slot >= pend0;  // (a single stream that has not forked: its newest row is part of its prefix)
+        off[i] = pnd[i] ? (uint32_t)(((pend_src0 + (slot - pend0)) * p.Hkv + g) * (D * 2))
+                        : (uint32_t)(elem_off(p.lay, phys_row(p.lay, p.page_table, req, slot), g) * 2);
+      }
+      // (lanes that are switched off neither read nor write their place; where a group of rows needs both kinds, the
+      // counted waits below wait for a little more than they have to)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (pnd[i]) __builtin_amdgcn_raw_ptr_buffer_load_lds(kp_rs, (lds_ptr)(kd + 64 * i), 16, off[i] + piece_k[i], 0, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rs, (lds_ptr)(kd + 64 * i), 16, off[i] + piece_k[i], 0, 0, 0);
       }
 #pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        const int t = slot0 + b * kBlock + 16 * hb;
-        const int phys = PAGED ? ((pp[hb] << p.lay.page_shift) | (t & p.lay.page_mask)) : req * p.lay.pool_tokens + t;
-        const long long off = elem_off(p.lay, phys, g) * 2;
-        const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kb + off), 0, 0x7fffffff, kRawBuffer);
-        const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vb + off), 0, 0x7fffffff, kRawBuffer);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          br.k[4 * hb + i] = __builtin_amdgcn_raw_buffer_load_b128(kr, lane_n, (uint32_t)(4 * i) * row_bytes, 0);
-          br.v[4 * hb + i] = __builtin_amdgcn_raw_buffer_load_b128(vr, lane_n, (uint32_t)(4 * i) * row_bytes, 0);
-        }
+      for (int i = 0; i < 2; ++i) {
+        if (pnd[i]) __builtin_amdgcn_raw_ptr_buffer_load_lds(vp_rs, (lds_ptr)(vd + 64 * i), 16, off[i] + piece_v, 0, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rs, (lds_ptr)(vd + 64 * i), 16, off[i] + piece_v, 0, 0, 0);
       }
-      return;
     }
-    long long off[8];
-    bool pnd[8];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int page = 0;  // of the next tile to be requested
+  for (int t = 0; t < kRingTiles - 1 && t < n_tiles; ++t) request(t, page_of(t));
+  page = page_of(kRingTiles - 1);
+  if (l32 >= R) {  // rows past R are zero (behind the requests: Q is waited for here)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int t = slot0 + min(b * kBlock + rbase + 4 * i, n_tok - 1);  // rows past the end repeat the last one
-      pnd[i] = t >= pend0;  // (a single stream that has not forked: its newest row is part of its prefix)
-      const long long off_pool = elem_off(p.lay, pnd[i] ? 0 : phys_row(p.lay, p.page_table, req, t), g) * 2;
-      const long long off_pend = ((long long)(pend_src0 + (t - pend0)) * p.Hkv + g) * D * 2;
-      off[i] = (pnd[i] ? off_pend : off_pool) + piece * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      br.k[i] = *reinterpret_cast<const u32x4*>((pnd[i] ? kpend : kb) + off[i]);
-      br.v[i] = *reinterpret_cast<const u32x4*>((pnd[i] ? vpend : vb) + off[i]);
+    for (int kk = 0; kk < 8; ++kk) qreg[kk] = u32x4{0u, 0u, 0u, 0u};
+  }
+  // Tile t is complete, and nobody reads the tile two before it any more (V of the tile before it went to registers ahead of the
+  // barrier): its place takes the next one.
+  auto arrive = [&](int t) {
+    const int behind = min(n_tiles - 1 - t, kRingTiles - 2);  // tiles requested after t
+    if (behind == 2) wait_vmcnt<8>();
+    else if (behind == 1) wait_vmcnt<4>();
+    else wait_vmcnt<0>();
+    lds_barrier();
+    if (t + kRingTiles - 1 < n_tiles) {
+      request(t + kRingTiles - 1, page);
+      page = page_of(t + kRingTiles);
     }
   };
-  BlockRegs br;
-  const int n_rounds = (n_blocks + 3) >> 2;
-  if (w < n_blocks) load_block(br, w);
 
   if constexpr (PROBE) {  // read-only form: the same requests, nothing computed
-    u32x4 acc = u32x4{0u, 0u, 0u, 0u};
-    for (int b = w; b < n_blocks; b += 4) {
-      if (b != w) load_block(br, b);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc = acc ^ br.k[i] ^ br.v[i] ^ qreg[i];
+    u32x4 acc = qreg[0] ^ qreg[1] ^ qreg[2] ^ qreg[3] ^ qreg[4] ^ qreg[5] ^ qreg[6] ^ qreg[7];
+    for (int t = 0; t < n_tiles; ++t) {
+      arrive(t);
+      acc = acc ^ lds.tile[t % kRingTiles].kt[tid] ^ lds.tile[t % kRingTiles].vt[tid];
     }
     if ((acc[0] ^ acc[1] ^ acc[2] ^ acc[3]) == 0x9E3779B9u && n_tok < 0) p.part_ml[part_row0] = make_float2(0.f, 0.f);
     return;
@@ -1008,111 +1063,132 @@ __device__ __forceinline__ void attn_item_wide(const DecodeParams& p, AttnLds& l
 #pragma unroll
     for (int i = 0; i < 16; ++i) O[mt][i] = 0.f;
 
-  u32x4* ktw = lds.tile[w].kt;
-  u32x4* vtw = lds.tile[w].vt;
-  // V^T reads (see attn_item): byte offset inside a tile's V half, per M-tile
-  int vrd[4];
+  uint32_t v_at[4];  // V^T reads (see attn_item): this lane's places in tile 0, offsets to its V half in the instructions
   {
     const int bl = lane & 15, cblk = (lane >> 4) & 1, r2 = bl >> 2;
+    const uint32_t tiles = (uint32_t)(uintptr_t)(lds_ptr)(void*)&lds.tile[0];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
-      vrd[mt] = (4 * hh + r2) * 256 + (mt ^ r2) * 64 + (2 * cblk + ((bl >> 1) & 1)) * 16 + (bl & 1) * 8;
+      v_at[mt] = tiles + (uint32_t)((4 * hh + r2) * 256 + (mt ^ r2) * 64 + (2 * cblk + ((bl >> 1) & 1)) * 16 + (bl & 1) * 8);
   }
-  // One block after the other, online softmax in log2 units.  (Two blocks per softmax step, their S^T chains
-  // interleaved, took the same time: the launch is bound by what it has in flight, not by this chain.)
-  auto block_compute = [&](int t, int b) {  // block b, in tile t, for this wave's rows
-    const u32x4* kt = lds.tile[t].kt;
-    const char* vt = reinterpret_cast<const char*>(lds.tile[t].vt);
-    f32x16 S;
+  // One tile after the other, online softmax in log2 units, one tile's matrix work beside the other's vector work: the scores of
+  // tile t + 1 are issued between the exponentials of tile t, the row maxima of t + 1 between the products of t with V.  The chunk's
+  // ragged end comes by itself behind the full tiles.
+  const char* k_at[8];  // K reads: this lane's places in tile 0
 #pragma unroll
-    for (int i = 0; i < 16; ++i) S[i] = 0.f;
-    {
-      u32x4 a[2];
-      a[0] = kt[l32 * 16 + (hh ^ (l32 & 15))];
+  for (int kk = 0; kk < 8; ++kk) k_at[kk] = reinterpret_cast<const char*>(&lds.tile[0].kt[l32 * 16 + ((2 * kk + hh) ^ (l32 & 15))]);
+  u32x4 kx[8];
+  u32x2 vx[2][4][2];
+  f32x16 S;
+  float mx = -INFINITY;  // row maximum of the tile in S, in log2 units
+  auto at_tile = [&](int t) -> uint32_t { return (uint32_t)(t % kRingTiles) * (uint32_t)sizeof(AttnTile); };
+  auto read_k = [&](int t) {
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        if (kk + 1 < 8) a[(kk + 1) & 1] = kt[l32 * 16 + ((2 * kk + 2 + hh) ^ (l32 & 15))];
-        S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(&a[kk & 1]),
-                                                    *reinterpret_cast<const bf16x8*>(&qreg[kk]), S, 0, 0, 0);
-      }
-    }
-    if (b * kBlock + kBlock > n_tok) {  // the chunk's ragged last block: tokens past its end are hidden
-      asm volatile("" ::: "memory");
-      const int left = n_tok - (b * kBlock + 4 * hh);
+    for (int kk = 0; kk < 8; ++kk) kx[kk] = *reinterpret_cast<const u32x4*>(k_at[kk] + at_tile(t));
+  };
+  auto read_v = [&](int t) {
+    const uint32_t tile = at_tile(t), at[4] = {v_at[0] + tile, v_at[1] + tile, v_at[2] + tile, v_at[3] + tile};
+    lds_read_v(vx, at);
+  };
+  auto score = [&](f32x16& Z, int kk) {
+    Z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kx[kk]), __builtin_bit_cast(bf16x8, qreg[kk]), Z, 0, 0, 0);
+  };
+  auto row_max = [&](const f32x16& Z) {
+    float x = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) S[i] = (8 * (i >> 2) + (i & 3)) < left ? S[i] : -INFINITY;
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave)) * p.scale_log2e;
-    const float mn = fmaxf(m_run, mx);
-    const float corr = fast_exp2(m_run - mn);
+    for (int i = 0; i < 16; ++i) x = fmaxf(x, Z[i]);
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])) * p.scale_log2e;
+  };
+  // the tile in S: the running maximum takes its row maxima in, what has been summed so far is rescaled (moves rarely once a few tiles are in)
+  auto new_max = [&]() {
+    const float mn = fmaxf(m_run, mx), corr = fast_exp2(m_run - mn);
     m_run = mn;
-    float ps = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      S[i] = fast_exp2(fmaf(S[i], p.scale_log2e, -mn));
-      ps += S[i];
-    }
-    l_run = l_run * corr + ps;
-    bf16x8 P[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      u32x4 pk;
-      pk[0] = pack_bf16x2(S[8 * ks + 0], S[8 * ks + 1]);
-      pk[1] = pack_bf16x2(S[8 * ks + 2], S[8 * ks + 3]);
-      pk[2] = pack_bf16x2(S[8 * ks + 4], S[8 * ks + 5]);
-      pk[3] = pack_bf16x2(S[8 * ks + 6], S[8 * ks + 7]);
-      P[ks] = *reinterpret_cast<const bf16x8*>(&pk);
-    }
-    if (!__all(corr == 1.f)) {  // the running max moves rarely once a few blocks are in
+    l_run *= corr;
+    if (!__all(corr == 1.f)) {
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) O[mt][i] *= corr;
     }
+  };
+  auto products = [&](const u32x4 (&P)[2]) {  // P^T as B operands: contraction step ks holds the weights of registers 8 ks .. 8 ks + 7
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        s16x4 part[2];
-#pragma unroll
-        for (int e4 = 0; e4 < 2; ++e4)
-          part[e4] = lds_read_tr16(reinterpret_cast<const uint16_t*>(vt + vrd[mt] + (16 * ks + 8 * e4) * 256));
-        u32x4 a4;
-        a4[0] = reinterpret_cast<const uint32_t*>(&part[0])[0];
-        a4[1] = reinterpret_cast<const uint32_t*>(&part[0])[1];
-        a4[2] = reinterpret_cast<const uint32_t*>(&part[1])[0];
-        a4[3] = reinterpret_cast<const uint32_t*>(&part[1])[1];
-        O[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(&a4), P[ks], O[mt], 0, 0, 0);
+        const u32x4 a4 = u32x4{vx[ks][mt][0][0], vx[ks][mt][0][1], vx[ks][mt][1][0], vx[ks][mt][1][1]};
+        O[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, P[ks]), O[mt], 0, 0, 0);
       }
+  };
+  // tile t, whose scores, row maxima and V operands are in registers; with a tile behind it that one's are then
+  auto tile_step = [&](int t, auto has_next) {
+    if constexpr (has_next.value) read_k(t + 1);
+    new_max();
+    f32x16 Z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) Z[i] = 0.f;
+    float ps = 0.f;
+    u32x4 P[2];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {  // (left to itself, the scheduler puts the eight dependent products behind each other)
+      if constexpr (has_next.value) score(Z, kk);
+      const float a = fast_exp2(fmaf(S[2 * kk], p.scale_log2e, -m_run)), b = fast_exp2(fmaf(S[2 * kk + 1], p.scale_log2e, -m_run));
+      ps += a;
+      ps += b;
+      P[kk / 4][kk % 4] = pack_bf16x2(a, b);
+      if constexpr (has_next.value) __builtin_amdgcn_sched_barrier(0);
+    }
+    l_run += ps;
+    products(P);
+    if constexpr (has_next.value) {
+      S = Z;
+      mx = row_max(Z);
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // 2 vector instructions
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      read_v(t + 1);
     }
   };
-
-  for (int r = 0; r < n_rounds; ++r) {
-    if (4 * r + w < n_blocks) {  // this wave's block of the round: registers -> its tile
+  const int n_full = n_tok / kBlock;
+  if (n_full > 0) {
+    arrive(0);
+    read_k(0);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int rr = rbase + 4 * i;
-        ktw[rr * 16 + (piece ^ (rr & 15))] = br.k[i];
-        vtw[rr * 16 + (piece ^ v_swizzle(rr))] = br.v[i];
-      }
-    }
-    if (4 * (r + 1) + w < n_blocks) load_block(br, 4 * (r + 1) + w);  // in flight while this round is computed
-    lds_barrier();  // the round's tiles are complete (it does not wait for the loads just requested)
-    if (r == 0) PASTA_CLK(1);
-    if (r == 1) PASTA_CLK(2);
-    if (R > 0) {
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (4 * r + t < n_blocks) block_compute(t, 4 * r + t);
+    for (int kk = 0; kk < 8; ++kk) score(S, kk);
+    read_v(0);
+    mx = row_max(S);
+    PASTA_CLK(1);
+    for (int t = 0; t + 1 < n_full; ++t) {
+      arrive(t + 1);
+      if (t == 0) PASTA_CLK(2);
+      tile_step(t, std::true_type{});
+      if (t == 0) PASTA_CLK(3);
+      if (t == 1) PASTA_CLK(4);
     }
-    lds_barrier();  // every wave is done with the tiles
-    if (r == 0) PASTA_CLK(3);
-    if (r == 1) PASTA_CLK(4);
+    tile_step(n_full - 1, std::false_type{});
+  }
+  if (n_full < n_tiles) {
+    arrive(n_full);
+    read_k(n_full);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) score(S, kk);
+    read_v(n_full);
+    const int left = n_tok - n_full * kBlock;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 8 * (i >> 2) + 4 * hh + (i & 3) < left ? S[i] : -INFINITY;
+    mx = row_max(S);
+    tile_step(n_full, std::false_type{});
   }
   PASTA_CLK(6);
+  lds_barrier();  // nobody reads the ring any more
 
   // ---- this wave's rows leave through its own tile: [32 rows][32 pieces of 4 floats], piece c of
   // row r at c ^ r, then 512-byte rows go out whole
