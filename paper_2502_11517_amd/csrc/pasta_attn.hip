@@ -1363,25 +1363,33 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         //     1024 + 4 x 64 .. 256 30.3 -> 25.8 (600 -> 832)
         //   not taken: 1024 + 6 x 64 .. 512 12.2 -> 14.4 (216 -> 288), 4096 + 8 x 300 .. 512 20.5 -> 22.6 (472 -> 656), six requests of
         //     1024 + 4 x 300 .. 512 35.9 -> 37.2 (960 -> 1560)
-        struct At { int64_t words, wgs; };
+        // Nor where the call has no room for the additional items and rows that it has for 128's (kept plan, metadata, partial rows).
+        struct At { int64_t words, wgs, items, rows; };
         auto plan_at = [&](int64_t piece) {
-          At at{(int64_t)n * (int64_t)(sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (int64_t)(sizeof(DevReq) / 4) + 8, 0};
-          int64_t items = 0;
+          At at{(int64_t)n * (int64_t)(sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (int64_t)(sizeof(DevReq) / 4) + 8, 0, 0, 0};
           for (int i = 0; i < n; ++i) {
             const ListView& v = lv[i];
             int64_t priv = (int64_t)v.prefix_len - reqs[stream_req_idx[i]].pc;
             for (int k = 0; k < v.n_ranges; ++k) priv += v.at(k).count;
             at.words += ((int64_t)v.n_ranges + 1) * 4;
-            items += (priv + piece - 1) / piece;
+            at.items += (priv + piece - 1) / piece;
           }
-          at.words += items * (int64_t)(sizeof(DevItem) / 4);
-          at.wgs = items * Hkv;
-          for (auto& q : reqs) at.wgs += (q.pc + chunk_tokens - 1) / chunk_tokens * Hkv * row_units(q);
+          at.words += at.items * (int64_t)(sizeof(DevItem) / 4);
+          at.wgs = at.items * Hkv;
+          at.rows = at.items * c.n_q_heads;
+          for (auto& q : reqs) {
+            const int64_t chunks = (q.pc + chunk_tokens - 1) / chunk_tokens * Hkv;
+            at.wgs += chunks * row_units(q);
+            at.rows += chunks * q.n_streams * G;
+          }
           return at;
         };
         const At by_64 = plan_at(64), by_128 = plan_at(128);
         auto turn = [&](int64_t wgs) { return std::min<int64_t>((wgs + h->n_cus - 1) / h->n_cus, 3); };
-        if (turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs) &&
+        // (a list on the device can have an item more than here, its prefix's rest and its ranges apart; an entry per item goes with the words)
+        const bool fits_64 = (by_64.words <= kInlineMetaWords || by_64.items + n <= h->plan_items_cap || by_128.items > h->plan_items_cap) &&
+                             (by_64.words + by_64.items + n + 8) * 4 <= (int64_t)h->meta_bytes && by_64.rows + (int64_t)n * c.n_q_heads <= part_rows_cap;
+        if (fits_64 && turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs) &&
             (by_64.words <= kInlineMetaWords || by_128.words > kInlineMetaWords)) priv_chunk = 64;
       }
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;

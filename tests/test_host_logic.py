@@ -411,6 +411,19 @@ def test_sync_argument_checks_and_retire_only():
     h.destroy()
 
 
+@pytest.mark.parametrize("n,piece", [(10000, 64), (24000, 128)])
+def test_fp32_pieces_leave_room_for_the_kept_plan(n, piece):
+    """fp32 x 128, n lists of which two in five have 100 tokens, the rest 40: pieces of 64 tokens, but not where the items of
+    128 have room in the plan kept on the device (32768) and those of 64 do not."""
+    h = _handle("f32", 8, 8, 128, max_streams=n, max_ranges=2 * n, pool_tokens=256)
+    h.append_kv(0, [0] * 256, [0] * 256, None, None, flags=B.APPEND_RESERVE_ONLY)
+    count = np.where(np.arange(n) % 5 < 2, 100, 40).astype(np.int32)
+    z = np.zeros(n, np.int32)
+    _, plan = _plan(h, z, np.arange(n, dtype=np.int32), lists=(z, np.arange(n + 1, dtype=np.int32), z, count, z + 1))
+    assert plan[2] == int((-(-count // piece)).sum())
+    h.destroy()
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_replay_plan_equals_the_oracles_interpreter(seed):
     """The library's trace replay (planning run: host bookkeeping only) against the oracle's
