@@ -1826,6 +1826,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       mp.lse = p.lse;
       mp.part_acc = p.part_acc;
       mp.part_ml = p.part_ml;
+      static_assert(kInlineMetaWords / (sizeof(DevStream) / 4) <= kMergeRecs, "a plan of more streams lies on the device");
       mp.meta = n <= kMergeRecs ? nullptr : p.meta;
       mp.off_streams = p.off_streams;
       mp.priv_part_base = p.priv_part_base;
