@@ -1365,13 +1365,19 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         //     1024 + 4 x 300 .. 512 35.9 -> 37.2 (960 -> 1560)
         // Nor where the call has no room for the additional items and rows that it has for 128's (kept plan, metadata, partial rows).
         struct At { int64_t words, wgs, items, rows; };
+        const int64_t stream_words = (int64_t)n * (int64_t)(sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (int64_t)(sizeof(DevReq) / 4);
+        const bool maintained = !explicit_mode && !a->causal_skip;
+        int64_t whole_heads = 0;  // streams without a range of their own for what their prefix has beyond the common one
         auto plan_at = [&](int64_t piece) {
-          At at{(int64_t)n * (int64_t)(sizeof(DevStream) / 4 + 1) + (int64_t)reqs.size() * (int64_t)(sizeof(DevReq) / 4) + 8, 0, 0, 0};
+          At at{stream_words, 0, 0, 0};
+          whole_heads = 0;
           for (int i = 0; i < n; ++i) {
             const ListView& v = lv[i];
-            int64_t priv = (int64_t)v.prefix_len - reqs[stream_req_idx[i]].pc;
+            const int32_t pc = reqs[stream_req_idx[i]].pc;
+            int64_t priv = (int64_t)v.prefix_len - pc;
             for (int k = 0; k < v.n_ranges; ++k) priv += v.at(k).count;
-            at.words += ((int64_t)v.n_ranges + 1) * 4;
+            whole_heads += v.prefix_len == pc;
+            at.words += ((int64_t)v.n_ranges + (v.prefix_len > pc)) * (int64_t)(sizeof(DevRange) / 4);
             at.items += (priv + piece - 1) / piece;
           }
           at.words += at.items * (int64_t)(sizeof(DevItem) / 4);
@@ -1386,11 +1392,16 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         };
         const At by_64 = plan_at(64), by_128 = plan_at(128);
         auto turn = [&](int64_t wgs) { return std::min<int64_t>((wgs + h->n_cus - 1) / h->n_cus, 3); };
+        // Counted as it is (the launch), with 8 words more (the no-alloc entry) and with a further range per stream (the choice of the lists
+        // on the device, below): by none of these may the plan be within the arguments with pieces of 128 and beyond them with 64.
+        const int64_t counted_more = 8 + whole_heads * (int64_t)(sizeof(DevRange) / 4);
+        auto leaves = [&](int64_t more) { return by_64.words + more > kInlineMetaWords && by_128.words + more <= kInlineMetaWords; };
+        const bool left_inline = !leaves(0) && !(no_alloc && leaves(8)) && !(maintained && leaves(counted_more));
         // (a list on the device can have an item more than here, its prefix's rest and its ranges apart; an entry per item goes with the words)
-        const bool fits_64 = (by_64.words <= kInlineMetaWords || by_64.items + n <= h->plan_items_cap || by_128.items > h->plan_items_cap) &&
-                             (by_64.words + by_64.items + n + 8) * 4 <= (int64_t)h->meta_bytes && by_64.rows + (int64_t)n * c.n_q_heads <= part_rows_cap;
-        if (fits_64 && turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs) &&
-            (by_64.words <= kInlineMetaWords || by_128.words > kInlineMetaWords)) priv_chunk = 64;
+        const bool inline_64 = by_64.words + (maintained ? counted_more : 0) <= kInlineMetaWords && !(a->flags & PASTA_DECODE_DEVICE_LISTS);
+        const bool fits_64 = (inline_64 || by_64.items + n <= h->plan_items_cap || by_128.items > h->plan_items_cap) &&
+                             (by_64.words + by_64.items + counted_more + n) * 4 <= (int64_t)h->meta_bytes && by_64.rows + (int64_t)n * c.n_q_heads <= part_rows_cap;
+        if (fits_64 && left_inline && turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs)) priv_chunk = 64;
       }
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
       if (one) priv_chunk = kOneTokens;  // a stream's whole list

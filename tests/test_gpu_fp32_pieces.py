@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2502_11517_amd import binding as B
 from paper_2502_11517_amd import workloads as W
@@ -32,4 +33,19 @@ def test_pieces_of_fp32_lists(hkv, prefix, lengths, inter, piece):
         out, lse, _ = s.decode(0, explicit=explicit, flags=B.DECODE_ROW_GROUPS)
         check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
         assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= 1e-4
+    s.close()
+
+
+@pytest.mark.parametrize("length", [79, 80, 83])  # by pieces of 64 (and 8 words of room) the plan takes 766 / 770 / 798 of 768 words, by 128 734 / 738 / 766
+def test_noalloc_takes_what_fits_by_pieces_of_128(length):
+    from paper_2502_11517_amd.harness import Session, to_device, to_host_bits
+    w = W.single_request("pieces", "f32", 8, 2, 128, 1.0, 61, 512, [length] * 4, "random", k_std=128 ** -0.5)
+    s = Session(w)
+    s.append_events(w.n_prefill)
+    ref, lse_ref = OraclePool(w).append_events(w.n_prefill).attention()
+    q = to_device(w.q(0), w.dtype, s.device)
+    out, lse = torch.full_like(q, float("nan")), torch.empty(w.n, w.Hq, dtype=torch.float32, device=s.device)
+    s.h.decode_step_noalloc(0, w.dec_request, w.dec_stream, q, out, lists=w.lists(0), out_lse=lse, flags=B.DECODE_ROW_GROUPS)
+    check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
+    assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= 1e-4
     s.close()

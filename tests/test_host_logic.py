@@ -424,6 +424,61 @@ def test_fp32_pieces_leave_room_for_the_kept_plan(n, piece):
     h.destroy()
 
 
+@pytest.mark.parametrize("lists", ["explicit", "maintained", "causal"])
+@pytest.mark.parametrize("goes_on", [False, True])
+def test_fp32_pieces_leave_a_small_plan_in_the_kernel_arguments(goes_on, lists):
+    """Four fp32 x 128 streams of 26 .. 40 ranges each behind a prefix of 512: pieces of 64 tokens, but not where the plan fits the kernel
+    arguments (768 words) with pieces of 128 and does not with those of 64.  A stream's tokens that go on from the common prefix are a
+    range more.  Whether maintained lists are read from their copy on the device is decided as if every stream had such tokens."""
+    seen = set()
+    for n_ranges in range(26, 41):
+        h = _handle("f32", 8, 2, 128, pool_tokens=4096, max_streams=8)
+        _reserve(h, [0] * 512, [0] * 512)
+        sid = [1, 2, 3, 4]
+        ev = [] if goes_on else [5]                  # (a row of a stream that is not in the step, or stream 1 goes on from the prefix)
+        for k in range(n_ranges):
+            for i in sid:                            # runs of 3 and 4 in turn: each a range of its own
+                ev += [i] * (3 + (k + (i == 2)) % 2)
+        par = [0 if i and i not in ev[:j] else -1 for j, i in enumerate(ev)]
+        _reserve(h, [0] * len(ev), ev, par)
+        views = [h.stream_list(0, i) for i in sid]
+        heads, tokens = [v[0] - 512 for v in views], [int(v[2].sum()) for v in views]
+        assert [x > 0 for x in heads] == [goes_on, False, False, False]
+
+        def words(piece):                            # of the plan sent whole
+            return 4 * 25 + 10 + 4 * sum(len(v[1]) + (x > 0) for v, x in zip(views, heads)) + 8 * sum(-(-(x + t) // piece) for x, t in zip(heads, tokens))
+
+        more = 8 + 4 * heads.count(0)
+        kw = {}
+        if lists == "explicit":
+            kw = dict(lists=([v[0] for v in views], np.cumsum([0] + [len(v[1]) for v in views]), *(np.concatenate([v[k] for v in views]) for k in (1, 2, 3))))
+        elif lists == "causal":
+            kw = dict(causal_skip=np.zeros(4, np.int32))
+        plan = np.zeros(8, np.int64)
+        h.decode_step(0, [0] * 4, sid, None, None, flags=B.DECODE_PLAN_ONLY, dbg_plan=plan, **kw)
+        counts = [0, more] if lists == "maintained" else [0]
+        piece = 128 if any(words(64) + m > 768 >= words(128) + m for m in counts) else 64
+        seen.add(piece)
+        if lists == "maintained" and words(piece) + more > 768:
+            assert plan[6] == 4 * (4 * 25 + 10) and plan[2] == sum(-(-x // piece) + -(-t // piece) for x, t in zip(heads, tokens))
+        else:
+            assert plan[6] == 4 * words(piece) and plan[2] == sum(-(-(x + t) // piece) for x, t in zip(heads, tokens)), (n_ranges, plan)
+        h.destroy()
+    assert seen == {64, 128}
+
+
+def test_fp32_pieces_leave_room_for_the_lists_on_the_device():
+    """A handle of one stream of 1024 tokens has room for 12 items in the plan made from the lists on the device: 8 pieces of 128 tokens and
+    one more, not 16 of 64.  A step that asks for those lists gets them (its plan holds records alone)."""
+    h = _handle("f32", 8, 2, 128, max_streams=1, max_ranges=64, pool_tokens=1024)
+    _reserve(h, [0] * 1024, [0] * 1024)
+    _, plan = _plan(h, [0], [0], flags=B.DECODE_DEVICE_LISTS | B.DECODE_NO_SHARE)
+    assert plan[6] == 4 * (25 + 10) and plan[2] == 8
+    _, plan = _plan(h, [0], [0], flags=B.DECODE_NO_SHARE)
+    assert plan[2] == 16
+    h.destroy()
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_replay_plan_equals_the_oracles_interpreter(seed):
     """The library's trace replay (planning run: host bookkeeping only) against the oracle's
