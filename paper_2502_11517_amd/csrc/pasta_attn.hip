@@ -62,6 +62,7 @@ struct ListView {  // one stream's visible list for this call
   const Range* ranges;   // maintained mode
   int32_t n_ranges;
   const int32_t *start, *count, *stride;  // explicit mode (ranges == nullptr)
+  int64_t range_tokens;      // tokens in the ranges
   Range at(int k) const { return ranges ? ranges[k] : Range{start[k], count[k], stride[k]}; }
 };
 
@@ -1190,7 +1191,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         if (r0 < 0 || r1 < r0 || (i == 0 && r0 != 0)) return PASTA_E_INVAL;
         if (r1 > r0 && (!a->range_start || !a->range_count || !a->range_stride)) return PASTA_E_INVAL;
         v = ListView{a->prefix_len[i], nullptr, r1 - r0, a->range_start + r0, a->range_count + r0,
-                     a->range_stride + r0};
+                     a->range_stride + r0, 0};
         const int64_t tail = h->tail[r];
         if (v.prefix_len < 0 || v.prefix_len > tail) return PASTA_E_INVAL;
         int64_t last = (int64_t)v.prefix_len - 1;
@@ -1199,12 +1200,13 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
           if (g.count < 1 || g.stride < 1 || g.start <= last) return PASTA_E_INVAL;
           last = (int64_t)g.start + (int64_t)(g.count - 1) * g.stride;
           if (last >= tail) return PASTA_E_INVAL;
+          v.range_tokens += g.count;
         }
         if (v.prefix_len == 0 && v.n_ranges == 0) return PASTA_E_INVAL;
       } else {
         const StreamState& ss = sstate(h, r, s);
         if (!ss.open) return PASTA_E_STATE;
-        v = ListView{ss.prefix_len, ss.ranges.data(), (int32_t)ss.ranges.size(), nullptr, nullptr, nullptr};
+        v = ListView{ss.prefix_len, ss.ranges.data(), (int32_t)ss.ranges.size(), nullptr, nullptr, nullptr, ss.range_tokens};
         const int skip = a->causal_skip ? a->causal_skip[i] : 0;
         if (skip < 0) return PASTA_E_INVAL;
         if (skip > 0) {  // a view without the stream's `skip` newest rows: they are the largest slots of its list
@@ -1219,7 +1221,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
             if (trim.back().count == 0) trim.pop_back();
           }
           if (left > ss.prefix_len) return PASTA_E_INVAL;
-          v = ListView{ss.prefix_len - left, trim.data() + t0, (int32_t)(trim.size() - t0), nullptr, nullptr, nullptr};
+          v = ListView{ss.prefix_len - left, trim.data() + t0, (int32_t)(trim.size() - t0), nullptr, nullptr, nullptr, ss.range_tokens - (skip - left)};
         }
         if (v.prefix_len == 0 && v.n_ranges == 0) return PASTA_E_INVAL;
       }
@@ -1247,7 +1249,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
           const Range g = lv[i].at(k);
           for (int j = 0; j < g.count; ++j) m[(int64_t)g.start + (int64_t)j * g.stride] = 1;
         }
-        lv[i] = ListView{(int32_t)h->tail[a->request_id[i]], nullptr, 0, nullptr, nullptr, nullptr};
+        lv[i] = ListView{(int32_t)h->tail[a->request_id[i]], nullptr, 0, nullptr, nullptr, nullptr, 0};
       }
       total_ranges = 0;
     }
@@ -1374,8 +1376,7 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
           for (int i = 0; i < n; ++i) {
             const ListView& v = lv[i];
             const int32_t pc = reqs[stream_req_idx[i]].pc;
-            int64_t priv = (int64_t)v.prefix_len - pc;
-            for (int k = 0; k < v.n_ranges; ++k) priv += v.at(k).count;
+            const int64_t priv = (int64_t)v.prefix_len - pc + v.range_tokens;
             whole_heads += v.prefix_len == pc;
             at.words += ((int64_t)v.n_ranges + (v.prefix_len > pc)) * (int64_t)(sizeof(DevRange) / 4);
             at.items += (priv + piece - 1) / piece;

@@ -479,6 +479,29 @@ def test_fp32_pieces_leave_room_for_the_lists_on_the_device():
     h.destroy()
 
 
+def test_planning_over_maintained_lists_does_not_walk_them():
+    """Eight streams of some 5000 ranges each: planning an fp32 x 128 step, whose piece length depends on the number of private tokens, takes
+    about as long as planning a bf16 one, which never looks at a range (the shortest of 200 calls each; a walk of the lists: 3 to 4 times)."""
+    import time
+    ev = np.random.default_rng(5).integers(1, 9, size=65536).astype(np.int32)
+    par = np.full(len(ev), -1, np.int32)
+    par[[int(np.argmax(ev == i)) for i in range(1, 9)]] = 0
+    best = {}
+    for dtype in ("bf16", "f32"):
+        h = _handle(dtype, pool_tokens=1 << 17, max_ranges=1 << 17)
+        _reserve(h, [0] * 512, [0] * 512)
+        _reserve(h, np.zeros(len(ev), np.int32), ev, par)
+        rid, sid, plan = np.zeros(8, np.int32), np.arange(1, 9, dtype=np.int32), np.zeros(8, np.int64)
+        assert sum(len(h.stream_list(0, i)[1]) for i in sid) > 30000
+        best[dtype] = 1.0
+        for _ in range(200):
+            t = time.perf_counter()
+            h.decode_step(0, rid, sid, None, None, flags=B.DECODE_PLAN_ONLY, dbg_plan=plan)
+            best[dtype] = min(best[dtype], time.perf_counter() - t)
+        h.destroy()
+    assert best["f32"] < 2 * best["bf16"], best
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_replay_plan_equals_the_oracles_interpreter(seed):
     """The library's trace replay (planning run: host bookkeeping only) against the oracle's
