@@ -63,3 +63,17 @@ def test_one_piece_per_thread_and_several(rope, more):
     else:
         _check_pool(w, s, op)
     s.close()
+
+
+def test_position_ids_that_jump_after_30_to_51_rows():
+    """Rows are looked at one at a time up to the 32nd of a run, 16 at a time behind it: runs that end around every such place."""
+    lengths = list(range(30, 52)) + [96, 97]
+    n = sum(lengths)
+    w = W.Workload(name="jumps", dtype="f32", Hq=1, Hkv=1, D=64, scale=1.0, seed=10, max_requests=1, pool_tokens=1088, max_streams=2)
+    w.ev_request, w.ev_stream, w.ev_parent, w.n_prefill = np.zeros(n, np.int32), np.zeros(n, np.int32), np.full(n, -1, np.int32), n
+    pos = np.concatenate([1000 * (k % 7) + np.arange(m, dtype=np.int32) for k, m in enumerate(lengths)]).astype(np.int32)
+    s, op = _session(w, rope_theta=THETA), OraclePool(w)
+    s.append_events(n, flags=B.APPEND_ROPE, positions=pos)
+    op.append_events(n, positions=pos, theta=THETA)
+    _check_rope_pool(w, s, op, n)
+    s.close()

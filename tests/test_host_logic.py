@@ -615,6 +615,60 @@ def test_device_list_plans_have_a_fixed_size_and_failed_appends_leave_the_lists_
     h.destroy()
 
 
+def test_rows_that_go_on_are_counted_to_where_they_end():
+    """Rows of one stream behind each other are looked at one at a time up to the 32nd and 16 at a time behind it: another stream, another
+    request, a parent or a negative position id at any place around those ends them, or is refused."""
+    N, rope = 100, dict(flags=B.APPEND_ROPE)
+    for at in list(range(1, 4)) + list(range(28, 70)) + [95, 98, 99]:
+        for other in ("stream", "request", "parent", "position"):
+            h = _handle(pool_tokens=256, max_requests=2, max_streams=4, n_layers=2) if other != "position" else None
+            if other == "position":
+                cfg = B.make_config("bf16", 8, 2, 128, 1.0, n_layers=1, max_streams=2, max_ranges=64, pool_tokens=256, rope_theta=1e4)
+                h = B.PastaAttn(cfg, FAKE, FAKE, FAKE, B.query_workspace_bytes(cfg))
+                pos = np.arange(N, dtype=np.int32)
+                pos[at] = -1
+                with pytest.raises(B.PastaError) as e:
+                    h.append_kv(0, [0] * N, [0] * N, FAKE, FAKE, position=pos, **rope)
+                assert e.value.code == B.E_INVAL
+                h.destroy()
+                continue
+            req, sid, par = np.zeros(N, np.int32), np.zeros(N, np.int32), np.full(N, -1, np.int32)
+            {"stream": sid, "request": req, "parent": par}[other][at:at + 1 if other == "parent" else N] = 1
+            if other == "stream":
+                par[at] = 0
+            if other == "parent":
+                with pytest.raises(B.PastaError) as e:
+                    _reserve(h, req, sid, par)
+                assert e.value.code == B.E_INVAL and _reserve(h, [0], [0]).tolist() == [0]
+            else:
+                slots = _reserve(h, req, sid, par)
+                one = np.arange(N)
+                assert np.array_equal(slots, one if other == "stream" else np.concatenate([one[:at], one[:N - at]]))
+                assert h.stream_list(0, 0)[0] == at and h.stream_list(int(req[-1]), int(sid[-1]))[0] == (N if other == "stream" else N - at)
+            h.destroy()
+
+
+def test_a_long_prompts_rows_are_looked_at_several_at_a_time():
+    """A layer's append of 15000 rows of one stream (host side: slots and runs only) takes no longer than numpy takes to compare the two
+    index arrays with their first entries (the shortest of 200 each; one row at a time it took twice as long)."""
+    import time
+    n = 15000
+    h = _handle(n_layers=2)
+    rid, sid = np.zeros(n, np.int32), np.zeros(n, np.int32)
+    _reserve(h, rid, sid)
+    call = h.prepare_append(1, rid, sid, None, None, flags=B.APPEND_RESERVE_ONLY)
+    ours = theirs = 1.0
+    for _ in range(200):
+        t = time.perf_counter()
+        assert call() == 0
+        ours = min(ours, time.perf_counter() - t)
+        t = time.perf_counter()
+        assert (rid == rid[0]).all() and (sid == sid[0]).all()
+        theirs = min(theirs, time.perf_counter() - t)
+    assert ours < theirs, (ours, theirs)
+    h.destroy()
+
+
 def test_append_errors_are_those_of_the_first_row_that_cannot_be_taken():
     """Rows that one stream appends one behind the other: a layer-1 call that leaves the layer-0 rows behind long before
     the pool is full, and one that meets both at once; a row that opens a stream wrongly ahead of rows without room."""
