@@ -9,8 +9,8 @@
 // trips, kept to one -- what it needs of up to 32 streams rides in the kernel arguments -- or
 // two (the stream's record, then all its parts in one list).  The maximum
 // and the sum over the groups are taken by group 0 after one LDS exchange.
-// What bounds it is that chain and the start of its wavefronts, so a row gets the fewest threads that hold its parts in one
-// batch.  One head-dim element per thread, 1024 threads per row and the plan's 4 KB of arguments took 3.6 us in a kernel trace (17
+// What bounds it is that chain and the start of its wavefronts, so a row gets the fewest threads that hold the parts
+// of the launch's longest row in one batch.  One head-dim element per thread, 1024 threads per row and the plan's 4 KB of arguments took 3.6 us in a kernel trace (17
 // parts on each of 128 rows), this form takes 2.9.  Append and decode step of a layer by 256 / 128 / 64 threads (us; the form before):
 //   18 parts, 32 rows        7.9 / 7.8 / 8.3 (8.3)       35 parts, 64 rows     14.0 / 14.4 / 15.0 (14.4)
 //   17 parts, 512 rows      17.5 / 17.3 / 17.5 (18.4)    9 parts, 1024 rows    43.5 / 42.9 / 42.2 (43.3)

@@ -481,9 +481,12 @@ int launch_private(const pasta_attn* h, dim3 grid, hipStream_t st, const DecodeP
   return D == 64 ? launch_private_g<uint16_t, 64>(h->G, grid, st, p)
                  : launch_private_g<uint16_t, 128>(h->G, grid, st, p);
 }
-// grid = (Hkv, G, n); total_parts = partial rows that the launch reads, over all its output rows
-void launch_merge(const pasta_attn* h, dim3 grid, hipStream_t st, const MergeParams& p, int64_t total_parts) {
-  const int64_t rows = (int64_t)grid.x * grid.y * grid.z, parts = (total_parts + rows - 1) / rows;
+// grid = (Hkv, G, n); parts = the most partial rows that one of its output rows reads: such rows end the launch.  By the mean instead, rows
+// of few parts beside them leave them too few threads: append and decode step of a layer by the mean / by the most parts (us), 8 kv heads:
+//   16384 tokens and three requests of 512      26.2 / 24.7      32768 and fifteen of 512    41.0 / 38.4
+//   the same in fp32                            44.9 / 43.2      16384 and seven of 300, 2 streams each    27.0 / 25.4
+// (where both give one width, or all rows have as many parts, the same within noise).
+void launch_merge(const pasta_attn* h, dim3 grid, hipStream_t st, const MergeParams& p, int64_t parts) {
   if (h->cfg.dtype == PASTA_F32) {
     if (h->cfg.head_dim == 64) launch_merge_g<float, 64>(grid, st, p, parts);
     else launch_merge_g<float, 128>(grid, st, p, parts);
@@ -1859,9 +1862,9 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       if (rc != PASTA_OK) return rc;
     }
     if (ev1 && !ev_in_dispatch && hipEventRecord(ev1, st) != hipSuccess) return PASTA_E_DEVICE;
-    int64_t merge_parts = 0;  // every output row reads its request's prefix chunks and its stream's items
+    int64_t merge_parts = 0;  // every output row reads its request's prefix chunks and its stream's items: the most of them
     for (int i = 0; i < n; ++i)
-      merge_parts += (int64_t)(reqs[stream_req_idx[i]].n_chunks + streams[i].item_end - streams[i].item_begin) * c.n_q_heads;
+      merge_parts = std::max<int64_t>(merge_parts, reqs[stream_req_idx[i]].n_chunks + streams[i].item_end - streams[i].item_begin);
     if (!probe && !partials_only && !one) {
       MergeParams mp;  // (what is not filled in is not read)
       mp.out = p.out;
