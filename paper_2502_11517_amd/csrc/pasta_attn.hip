@@ -1340,10 +1340,12 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
     // More than 32 stacked rows per request: the rows go in groups of 32.  When EVERY request with a
     // shared prefix is that wide, the launch may take the form whose work-groups serve four row groups
     // each (one per wave, over shared tiles); otherwise each row group is a work-group of its own.
-    // The wide form pays where its waves are busy and its pipeline gets going -- every such request
-    // keeps three of four waves computing on average, and a chunk is four rounds or more -- and loses
-    // a few per cent elsewhere (measured on 12 to 32 streams over prefixes of 8k and 32k tokens); the
-    // caller may force either form.
+    // The wide form pays where its waves are busy and its work-groups are long -- every such request keeps three of four waves
+    // computing on average, and a chunk is 512 tokens, four times the ring of tiles, or more -- and loses elsewhere; the caller may
+    // force either form.  Append and decode step of a layer, 8 kv heads, four groups per work-group / one (us; streams x heads per kv head):
+    //   not taken: 8k tokens 12 x 4 20.6 / 17.9, 24 x 4 28.7 / 25.9, 32 x 4 34.8 / 29.8; 16k 16 x 4 28.4 / 28.0; 32k 16 x 4 37.0 / 37.2, 40 x 4 67.5 / 69.7
+    //   taken: 16k 24 x 4 35.2 / 34.1 (on the line), 32 x 4 38.9 / 40.5, 12 x 8 29.0 / 31.3; 32k 20 x 4 40.6 / 46.8, 24 x 4 42.4 / 51.8,
+    //     32 x 4 48.0 / 59.8, 48 x 4 68.3 / 75.9
     bool wide = mfma && !dense && pc_total > 0 && !(a->flags & PASTA_DECODE_ROW_GROUPS);
     const bool force_wide = a->flags & PASTA_DECODE_FOUR_GROUPS;
     if ((a->flags & PASTA_DECODE_ROW_GROUPS) && force_wide) return PASTA_E_INVAL;
@@ -1358,10 +1360,10 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
       const int64_t n_rg = (q.n_streams * G + 31) / 32;
       return wide ? (n_rg + 3) / 4 : n_rg;
     };
-    if (wide && !force_wide) {  // the chunk the wide form would get: at least four rounds of four 32-token blocks?
+    if (wide && !force_wide) {  // the chunk the wide form would get: at least sixteen tiles of 32 tokens?
       int64_t pw = 0;
       for (auto& q : reqs) pw += (int64_t)q.pc * row_units(q);
-      if (pw * Hkv / h->n_cus < 4 * 4 * 32) wide = false;
+      if (pw * Hkv / h->n_cus < 16 * 32) wide = false;
     }
     for (auto& q : reqs) pc_weighted += (int64_t)q.pc * row_units(q);
     // Chunking.  Every chunk costs one partial row per stacked query row (written here, read
