@@ -194,6 +194,7 @@ __device__ __forceinline__ void attn_item(const DecodeParams& p, AttnLds& lds, c
   pend0 = __builtin_amdgcn_readfirstlane(pend0);
   pend_src0 = __builtin_amdgcn_readfirstlane(pend_src0);
   listed = __builtin_amdgcn_readfirstlane((int)listed) != 0;
+  part_row0 = in_vector_registers(part_row0);
 
   // ---- block loads: lane -> piece (lane & 15) of rows (lane >> 4) + 4 i, i < 8
   const char* kb = reinterpret_cast<const char*>(p.k);

@@ -169,6 +169,13 @@ __device__ __forceinline__ S record(const_words table, int k) {
   for (int i = 0; i < kWords; ++i) x[i] = table[k * kWords + i];
   return __builtin_bit_cast(S, x);
 }
+// x as it is, in vector registers: a uniform value that a work-group needs once, at its end, leaves the scalar ones to its loops.  (Of
+// k_attn's forms for plans in the kernel arguments it ends 16 to 20 spills, and 20 bytes of scratch in the long one.)
+__device__ __forceinline__ long long in_vector_registers(long long x) {
+  uint32_t lo = (uint32_t)x, hi = (uint32_t)((unsigned long long)x >> 32);
+  asm("" : "+v"(lo), "+v"(hi));
+  return (long long)((unsigned long long)hi << 32 | lo);
+}
 // The request whose shared-prefix work-groups hold `wi`: the last whose wg_begin is not beyond it (one that has none shares its
 // wg_begin with the one behind it).  Lanes of a wave look at 64 requests at once: one after the other, each look a read that waits for
 // the one before, cost a work-group of the sixteenth request microseconds ahead of its first K/V request (append and decode step of
