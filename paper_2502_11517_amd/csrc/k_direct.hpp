@@ -26,7 +26,7 @@
 //   bf16, 32 heads on 8 x 64, 4096 tokens + 8 x 64 .. 512        27.9 -> 10.9
 // One block per wave in registers: with 32 stacked queries fp32 rows need 254 of the 256 registers without a second
 // one, and chunks are short enough here that most waves have only one.  (The rotated forms over 128 dims, which work
-// out angles between the loads, do not fit: 26 registers spilled in bf16, 33 in fp32.)
+// out angles between the loads, do not fit: 9 vector registers spilled in bf16, 17 in fp32.)
 #pragma once
 #include "k_plan.hpp"
 #include "k_rope.hpp"
