@@ -24,7 +24,7 @@
 //   fp32, 4 query heads on 1 x 64, 256 + 2 x 16 tokens           28.7 ->  9.1
 //   fp32, 32 heads on 8 x 128, 1024 tokens + 4 x 32 .. 256       45.8 -> 11.4
 //   bf16, 32 heads on 8 x 64, 4096 tokens + 8 x 64 .. 512        27.9 -> 10.9
-// One block per wave in registers: with 32 stacked queries fp32 rows need 254 of the 256 registers without a second
+// One block per wave in registers: with 32 stacked queries fp32 rows need 244 of the 256 registers without a second
 // one, and chunks are short enough here that most waves have only one.  (The rotated forms over 128 dims, which work
 // out angles between the loads, do not fit: 9 vector registers spilled in bf16, 17 in fp32.)
 #pragma once

@@ -1433,11 +1433,16 @@ int32_t decode_impl(pasta_attn* h, const pasta_decode_args* a, const bool no_all
         const int64_t counted_more = 8 + whole_heads * (int64_t)(sizeof(DevRange) / 4);
         auto leaves = [&](int64_t more) { return by_64.words + more > kInlineMetaWords && by_128.words + more <= kInlineMetaWords; };
         const bool left_inline = !leaves(0) && !(no_alloc && leaves(8)) && !(maintained && leaves(counted_more));
+        // Nor may a captured plan leave the arguments of k_plan: its words are relayed by a launch of their own then, on every replay (4 streams
+        // of 108 random-order tokens over 512, 2 kv heads: 14.9 us per replayed step, 12.3 by pieces of 128).
+        auto relayed = [&](int64_t w64, int64_t w128) { return w64 > kPlanWords && w128 <= kPlanWords; };
+        const bool relay_64 = (relayed(by_64.words + 1, by_128.words + 1) || (maintained && relayed(stream_words + by_64.items + 3, stream_words + by_128.items + 3))) &&
+                              !plan_only && stream_capturing(h);
         // (a list on the device can have an item more than here, its prefix's rest and its ranges apart; an entry per item goes with the words)
         const bool inline_64 = by_64.words + (maintained ? counted_more : 0) <= kInlineMetaWords && !(a->flags & PASTA_DECODE_DEVICE_LISTS);
         const bool fits_64 = (inline_64 || by_64.items + n <= h->plan_items_cap || by_128.items > h->plan_items_cap) &&
                              (by_64.words + by_64.items + counted_more + n) * 4 <= (int64_t)h->meta_bytes && by_64.rows + (int64_t)n * c.n_q_heads <= part_rows_cap;
-        if (fits_64 && left_inline && turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs)) priv_chunk = 64;
+        if (fits_64 && left_inline && !relay_64 && turn(by_64.wgs) == turn(by_128.wgs) && (turn(by_64.wgs) < 3 || 5 * by_64.wgs <= 7 * by_128.wgs)) priv_chunk = 64;
       }
       if (h->tune_prefix_chunk >= kTile) chunk_tokens = h->tune_prefix_chunk / kTile * kTile;
       if (one) priv_chunk = kOneTokens;  // a stream's whole list

@@ -8,6 +8,7 @@ import torch
 
 from paper_2502_11517_amd import binding as B
 from paper_2502_11517_amd import workloads as W
+from test_gpu_merge import launches_of
 from util import OraclePool, check_close, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,31 @@ def test_noalloc_takes_what_fits_by_pieces_of_128(length):
     check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
     assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= 1e-4
     s.close()
+
+
+@pytest.mark.parametrize("length,piece", [(103, 64), (108, 128)])  # by pieces of 64 the plan has 942 / 971 words, k_plan's arguments hold 960
+def test_captured_plans_stay_in_the_arguments_of_their_launch(length, piece):
+    from paper_2502_11517_amd.harness import Session, to_device, to_host_bits
+    w = W.single_request("pieces", "f32", 8, 2, 128, 1.0, 61, 512, [length] * 4, "random", k_std=128 ** -0.5)
+    ref, lse_ref = OraclePool(w).append_events(w.n_prefill).attention()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = Session(w)
+        s.append_events(w.n_prefill)
+        q = to_device(w.q(0), w.dtype, s.device)
+        out, lse = torch.empty_like(q), torch.empty(w.n, w.Hq, dtype=torch.float32, device=s.device)
+        step = lambda: s.h.decode_step(0, w.dec_request, w.dec_stream, q, out, lists=w.lists(0), out_lse=lse, flags=B.DECODE_ROW_GROUPS)  # noqa: E731
+        launches = launches_of(step)
+        assert len(launches) == 3, launches  # k_plan (a work-group per item, four at least), the attention launch, the merge
+        pl, offs, _, ct, _ = w.lists(0)
+        assert launches[0][0][0] == max(4, sum(-(-(int(pl[i] - pl.min()) + int(ct[offs[i]:offs[i + 1]].sum())) // piece) for i in range(w.n)))
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            step()
+        for _ in range(3):
+            out.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
+            assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= 1e-4
+        s.close()

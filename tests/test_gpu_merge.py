@@ -54,7 +54,7 @@ class _KernelNode(C.Structure):  # hipKernelNodeParams
     _fields_ = [("block", _Dim3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", _Dim3), ("params", C.c_void_p), ("shared", C.c_uint32)]
 
 
-def _launches(call):
+def launches_of(call):
     """(grid, threads) of every kernel that `call` launches on the current stream, in order, from a capture that is never run."""
     hip = C.CDLL(os.path.join(torch.__path__[0], "lib", "libamdhip64.so"))  # the runtime that the library is bound to, too
     g = torch.cuda.CUDAGraph(keep_graph=True)
@@ -101,7 +101,7 @@ def test_one_long_row_among_short_ones_sets_the_width(parts, dtype, D, n):
         assert plan[1] == parts + 2 * (n - 1) and plan[2] == 0
         check_close(to_f64(w, to_host_bits(out, w.dtype)), ref, w.dtype, "out")
         assert np.max(np.abs(lse.cpu().numpy() - lse_ref)) <= (2e-2 if dtype == "bf16" else 1e-4)
-        grid, threads = _launches(step)[-1]
+        grid, threads = launches_of(step)[-1]
         per_64 = 16 if D == 128 else 32
         assert grid == (1, 4, n) and threads == (64 if parts <= per_64 else 128 if parts <= 2 * per_64 else 256)
         s.close()
